@@ -262,8 +262,8 @@ tsdf_status tsdf_map_key_atomics(tsdf_map *m, int64_t *issued);
  * R' = exp([theta]x) R, t' = exp([theta]x) t + rho for d = (rho, theta);
  * at most `iterations` steps (fewer when under 6 points remain or the
  * system is singular). The map is only read. Normal-equation sums are
- * formed in a fixed order (per block, then blocks in order), so results do
- * not depend on scheduling. Synchronous on the map's stream. */
+ * formed in an order fixed by n_points alone, so results do not depend on
+ * scheduling. Synchronous on the map's stream. */
 typedef struct {
     int64_t points_used; /* at the returned pose */
     double cost;         /* sum of squared residuals there, m^2 */

@@ -154,19 +154,40 @@ struct InterpScan {
 };
 hipError_t launch_interp(const InterpScan &P, int64_t nvox, hipStream_t stream);
 
-// Point-to-TSDF registration sums (register.hip).
-constexpr int kRegSums = 29;  // H upper triangle (21), J^T r (6), sum r^2, points used
+// Point-to-TSDF registration (register.hip).
+constexpr int kRegSums = 29;       // H upper triangle (21), J^T r (6), sum r^2, points used
+constexpr int kRegRow = 32;        // the same, padded
+constexpr int kRegMaxBlocks = 256;  // more points than 256 blocks hold: several per thread
+constexpr int kRegFan = 16;        // blocks per arrival counter
+// Device memory of a map's registrations (zeroed once; every run leaves the
+// counters at zero).
+struct RegWork {
+    double M[12];  // the next launch's pose
+    double step;   // norm of the last step
+    int32_t it, stop;
+    uint32_t root, pad;
+    uint32_t ticket[32 * (kRegMaxBlocks / kRegFan)];  // each counter on a 128-byte line of its own
+    double rows[kRegMaxBlocks * kRegRow];
+};
+// Pinned host memory the last evaluation of a run writes.
+struct RegResult {
+    double M[12], sums[kRegSums], step;
+    int32_t it, done;
+};
 struct RegArgs {
-    double M[12];      // pose rows 0..2
+    double M[12];      // the first launch's pose, rows 0..2
     const float *xyz;  // device points
     int64_t n;
     const int16_t *sdf, *w;
     int32_t dims[3], origin[3];
+    int32_t ring0[3];  // floor_mod(origin, dims)
     int32_t tau;
-    double vs;
+    int32_t first, last;
+    double vs, damping;
+    RegWork *work;
+    RegResult *result;
 };
-int64_t reg_blocks(int64_t n);
-hipError_t launch_reg_sums(const RegArgs &A, double *partials, hipStream_t stream);
+hipError_t launch_reg_step(const RegArgs &A, hipStream_t stream);
 
 // Surface extraction of a box of the window (mesh.hip).
 struct MeshArgs {

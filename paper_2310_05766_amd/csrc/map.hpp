@@ -31,6 +31,9 @@ struct tsdf_map {
     unsigned long long *interp_ctr_host = nullptr;
     float *interp_pts = nullptr;                // device copy of host points
     int64_t interp_pts_cap = 0;                 // points
+    // registration: device state and rows of sums, pinned result
+    tsdf::RegWork *reg_work = nullptr;
+    tsdf::RegResult *reg_result = nullptr;
     // shift / readback staging
     int16_t *stage_dev = nullptr;  // [2][stage_cap]
     int16_t *stage_host = nullptr;

@@ -85,3 +85,36 @@ def test_registration_arguments():
     assert info["points"] == 0 and info["steps"] == 0 and np.array_equal(p, sc.pose)
     gm.close()
     om.close()
+
+
+@pytest.mark.parametrize("n", [1, 63, 65, 511, 513, 4095, 4097, 131073, 150001])
+def test_normal_equations_point_counts(n):
+    """Around a wave, a block, a group of eight blocks, and past the points
+    that the largest grid holds once (several per thread): one matrix row per
+    point, so that sums differ from the oracle's by their order alone."""
+    spec, sc, gm, om = _maps(1)
+    xyz = np.ascontiguousarray(np.resize(sc.xyz, (n, 3)))
+    P = _perturbed(sc.pose, 0.03, -0.02, 0.01)
+    g, o = gm.register_sums(xyz, P), om.reg_sums(xyz, P)
+    say(n, "points", o[28])
+    assert g[28] == o[28]
+    # n rounded additions at most in either order, of terms of one sign in
+    # sum 27 and bounded by the same magnitudes elsewhere
+    scale = np.abs(o[:28]).max()
+    assert np.all(np.abs(g[:28] - o[:28]) <= 2.0 * n * 2.0 ** -53 * scale)
+    assert np.array_equal(g, gm.register_sums(xyz, P))
+    gm.close()
+    om.close()
+
+
+def test_registration_longer_than_one_group_of_launches():
+    """More steps than are launched without waiting for the host, from the
+    same pose: the run goes on where it stopped."""
+    spec, sc, gm, om = _maps(1)
+    P0 = _perturbed(sc.pose, 0.04, -0.03, 0.02)
+    gp, gi = gm.register(sc.xyz, P0, 40, 1e-6)
+    op, oi = om.register(sc.xyz, P0, 40, 1e-6)
+    assert gi["steps"] == oi["steps"] == 40
+    assert abs(gi["points"] - oi["points"]) <= 2 and np.allclose(gp, op, rtol=0, atol=1e-7)
+    gm.close()
+    om.close()
