@@ -190,17 +190,23 @@ struct RegArgs {
 hipError_t launch_reg_step(const RegArgs &A, hipStream_t stream);
 
 // Surface extraction of a box of the window (mesh.hip).
+constexpr uint32_t kMeshUnit = 16;  // rows of cubes per workgroup
 struct MeshArgs {
     const int16_t *sdf, *w;
     int32_t dims[3];  // the window (slot = floor_mod(g, dims))
     int32_t lo[3];    // first cube's voxel
-    int64_t n[3];     // cubes per axis
-    int64_t ncubes;
+    int32_t s0[3];    // its slot per axis
+    int32_t n[3];     // cubes per axis
+    uint32_t nrows;   // n[0] * n[1]
     double vs;        // voxel size, metres
 };
-int64_t mesh_blocks(int64_t ncubes);
-hipError_t launch_mesh_count(const MeshArgs &A, uint32_t *block_tris, hipStream_t stream);
-hipError_t launch_mesh_emit(const MeshArgs &A, const uint64_t *block_base, float *out, hipStream_t stream);
+inline uint32_t mesh_units(uint32_t nrows) { return (nrows + kMeshUnit - 1) / kMeshUnit; }
+// Triangles per row of cubes and per unit of kMeshUnit rows.
+hipError_t launch_mesh_count(const MeshArgs &A, uint32_t *row_tris, uint32_t *unit_tris, hipStream_t stream);
+// Triangles of `units` units from unit0 on; unit_base: exclusive prefix of
+// unit_tris, with the total behind it; base: the first unit's.
+hipError_t launch_mesh_emit(const MeshArgs &A, const uint32_t *row_tris, const uint64_t *unit_base, uint32_t unit0,
+                            uint32_t units, uint64_t base, float *out, hipStream_t stream);
 
 // ---------------------------------------------------------------------------
 // Host-side store of 64^3-voxel chunks that left the window.

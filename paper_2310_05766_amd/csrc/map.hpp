@@ -34,7 +34,11 @@ struct tsdf_map {
     // registration: device state and rows of sums, pinned result
     tsdf::RegWork *reg_work = nullptr;
     tsdf::RegResult *reg_result = nullptr;
-    // shift / readback staging
+    // surface extraction: triangle counts and places, device and pinned host;
+    // device triangles on their way out (two pieces at most)
+    void *mesh_dev = nullptr, *mesh_host = nullptr, *mesh_tris = nullptr;
+    size_t mesh_dev_cap = 0, mesh_host_cap = 0, mesh_tris_cap = 0;
+    // shift / readback / mesh staging
     int16_t *stage_dev = nullptr;  // [2][stage_cap]
     int16_t *stage_host = nullptr;
     int64_t stage_cap = 0;  // voxels per array

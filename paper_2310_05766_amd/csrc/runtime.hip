@@ -10,6 +10,7 @@
 #include <memory>
 #include <new>
 
+#include "crew.hpp"
 #include "map.hpp"
 
 using namespace tsdf;
@@ -179,9 +180,25 @@ void chunk_give(tsdf_map *m, Chunk &c)
     c.buf = nullptr;
 }
 
+// Copies out of staging by several host threads (crew.hpp) from this many
+// bytes of a call on: below, the threads' start costs as much as they save.
+constexpr uint64_t kCrewBytes = (uint64_t)4 << 20;
+constexpr int kCrewHelpers = 7;
+
 // Staging of whole-chunk shifts: kShiftChunks chunks out and kShiftChunks in
 // per round trip (one chunk layer of a 512 x 512 x 128 window).
 constexpr int kShiftChunks = 16;
+
+// The stream whose copies run beside the map's own kernels.
+tsdf_status ensure_copy_stream(tsdf_map *m)
+{
+    if (m->copy_stream) return TSDF_OK;
+    if (hipStreamCreateWithFlags(&m->copy_stream, hipStreamNonBlocking) != hipSuccess) {  // default priority
+        m->copy_stream = nullptr;
+        return TSDF_ENOMEM;
+    }
+    return TSDF_OK;
+}
 
 tsdf_status ensure_chunk_stage(tsdf_map *m)
 {
@@ -200,7 +217,7 @@ tsdf_status ensure_chunk_stage(tsdf_map *m)
     ok = ok && hipMalloc(&m->clist_dev, 2 * kShiftChunks * sizeof(BoxXfer)) == hipSuccess;
     ok = ok && hipHostMalloc((void **)&m->clist_host, 2 * kShiftChunks * sizeof(BoxXfer), hipHostMallocDefault) ==
                    hipSuccess;
-    ok = ok && hipStreamCreateWithFlags(&m->copy_stream, hipStreamNonBlocking) == hipSuccess;  // default priority
+    ok = ok && ensure_copy_stream(m) == TSDF_OK;
     ok = ok && hipEventCreateWithFlags(&m->copy_done, hipEventDisableTiming) == hipSuccess;
     return ok ? TSDF_OK : TSDF_ENOMEM;
 }
@@ -223,6 +240,9 @@ void release(tsdf_map *m)
     if (m->interp_ctr) (void)hipFree(m->interp_ctr);
     if (m->interp_ctr_host) (void)hipHostFree(m->interp_ctr_host);
     if (m->interp_pts) (void)hipFree(m->interp_pts);
+    if (m->mesh_dev) (void)hipFree(m->mesh_dev);
+    if (m->mesh_host) (void)hipHostFree(m->mesh_host);
+    if (m->mesh_tris) (void)hipFree(m->mesh_tris);
     if (m->reg_work) (void)hipFree(m->reg_work);
     if (m->reg_result) (void)hipHostFree(m->reg_result);
     if (m->copy_stream) (void)hipStreamSynchronize(m->copy_stream);
@@ -789,54 +809,162 @@ tsdf_status tsdf_mesh(tsdf_map *m, const int32_t lo[3], const int32_t hi[3], flo
     MeshArgs A;
     A.sdf = m->sdf;
     A.w = m->w;
-    A.ncubes = 1;
+    int64_t nrows = 1;
     for (int a = 0; a < 3; ++a) {
         A.dims[a] = m->d.dims[a];
         A.lo[a] = lo[a];
-        A.n[a] = std::max<int64_t>(0, (int64_t)hi[a] - lo[a] - 1);
-        A.ncubes *= A.n[a];
+        A.s0[a] = (int32_t)floor_mod64(lo[a], m->d.dims[a]);
+        A.n[a] = std::max<int32_t>(0, hi[a] - lo[a] - 1);
+        if (a < 2) nrows *= A.n[a];
     }
+    A.nrows = (uint32_t)nrows;  // below 2^31, as the window's voxels are
     A.vs = m->d.voxel_size_m;
     *n_tris = 0;
-    if (A.ncubes == 0) return TSDF_OK;
-    const int64_t nb = mesh_blocks(A.ncubes);
-    uint32_t *bt = nullptr;
-    uint64_t *bb = nullptr;
-    float *out = nullptr;
-    std::vector<uint32_t> counts((size_t)nb);
-    std::vector<uint64_t> base((size_t)nb);
-    tsdf_status st = TSDF_OK;
-    auto done = [&](tsdf_status r) {
-        if (bt) (void)hipFree(bt);
-        if (bb) (void)hipFree(bb);
-        if (out) (void)hipFree(out);
-        return r;
-    };
-    if (hipMalloc(&bt, (size_t)nb * sizeof(uint32_t)) != hipSuccess) return done(TSDF_ENOMEM);
-    if (launch_mesh_count(A, bt, m->stream) != hipSuccess ||
-        hipMemcpyAsync(counts.data(), bt, (size_t)nb * sizeof(uint32_t), hipMemcpyDeviceToHost, m->stream) !=
-            hipSuccess ||
-        hipStreamSynchronize(m->stream) != hipSuccess)
-        return done(fail_device(m));
-    uint64_t total = 0;
-    for (int64_t b = 0; b < nb; ++b) {
-        base[(size_t)b] = total;
-        total += counts[(size_t)b];
+    if (nrows == 0 || A.n[2] == 0) return TSDF_OK;
+    // counts per row of cubes and per unit of rows; the units' places
+    const uint32_t units = mesh_units(A.nrows);
+    const size_t off_units = (size_t)A.nrows * 4, off_base = (off_units + (size_t)units * 4 + 7) / 8 * 8;
+    const size_t dev_bytes = off_base + ((size_t)units + 1) * 8, host_bytes = ((size_t)units + 1) * 16;
+    if (dev_bytes > m->mesh_dev_cap) {
+        if (m->mesh_dev) HIPCHK(m, hipFree(m->mesh_dev));
+        m->mesh_dev = nullptr;
+        m->mesh_dev_cap = 0;
+        if (hipMalloc(&m->mesh_dev, dev_bytes) != hipSuccess) return TSDF_ENOMEM;
+        m->mesh_dev_cap = dev_bytes;
     }
+    if (host_bytes > m->mesh_host_cap) {
+        if (m->mesh_host) HIPCHK(m, hipHostFree(m->mesh_host));
+        m->mesh_host = nullptr;
+        m->mesh_host_cap = 0;
+        if (hipHostMalloc(&m->mesh_host, host_bytes, hipHostMallocDefault) != hipSuccess) return TSDF_ENOMEM;
+        m->mesh_host_cap = host_bytes;
+    }
+    uint32_t *row_tris = (uint32_t *)m->mesh_dev, *unit_tris = (uint32_t *)((char *)m->mesh_dev + off_units);
+    uint64_t *unit_base = (uint64_t *)((char *)m->mesh_dev + off_base);
+    uint64_t *base = (uint64_t *)m->mesh_host;
+    const uint32_t *counts = (const uint32_t *)(base + units + 1);
+    HIPCHK(m, launch_mesh_count(A, row_tris, unit_tris, m->stream));
+    HIPCHK(m, hipMemcpyAsync((void *)counts, unit_tris, (size_t)units * 4, hipMemcpyDeviceToHost, m->stream));
+    HIPCHK(m, hipStreamSynchronize(m->stream));
+    uint64_t most = 0;
+    base[0] = 0;
+    for (uint32_t u = 0; u < units; ++u) {
+        base[u + 1] = base[u] + counts[u];
+        most = std::max<uint64_t>(most, counts[u]);
+    }
+    const uint64_t total = base[units];
     *n_tris = (int64_t)total;
-    if (!tris || total == 0) return done(TSDF_OK);  // a query of the count
-    if ((uint64_t)max_tris < total) return done(TSDF_ERANGE);
-    if (hipMalloc(&bb, (size_t)nb * sizeof(uint64_t)) != hipSuccess ||
-        hipMalloc(&out, (size_t)total * 9 * sizeof(float)) != hipSuccess)
-        return done(TSDF_ENOMEM);
-    if (hipMemcpyAsync(bb, base.data(), (size_t)nb * sizeof(uint64_t), hipMemcpyHostToDevice, m->stream) !=
-            hipSuccess ||
-        launch_mesh_emit(A, bb, out, m->stream) != hipSuccess ||
-        hipMemcpyAsync(tris, out, (size_t)total * 9 * sizeof(float), hipMemcpyDeviceToHost, m->stream) !=
-            hipSuccess ||
-        hipStreamSynchronize(m->stream) != hipSuccess)
-        st = fail_device(m);
-    return done(st);
+    if (!tris || total == 0) return TSDF_OK;  // a query of the count
+    if ((uint64_t)max_tris < total) return TSDF_ERANGE;
+    // The triangles are emitted in pieces of kPieceSlots slots of staging (one
+    // launch of a piece's size keeps the chip busy where a few rows hold a
+    // whole wall) into two device buffers in turn, and leave through a ring of
+    // kSlots pinned slots: while one slot's copy runs on the copy stream,
+    // earlier ones are copied to tris by several host threads.
+    constexpr int kSlots = 8, kAhead = 4, kPieceSlots = 16;
+    constexpr uint64_t kTri = 9 * sizeof(float);
+    tsdf_status st = ensure_stage(m, std::max<int64_t>({m->stage_cap, 16 * kChunkVox, (int64_t)(most * kTri * kSlots / 4 + 4)}), 0);
+    if (st == TSDF_OK) st = ensure_copy_stream(m);
+    if (st != TSDF_OK) return st;
+    // (a staged voxel is 4 bytes)
+    const uint64_t slot_bytes = (uint64_t)m->stage_cap * 4 / kSlots / 4 * 4, slot_tris = slot_bytes / kTri;
+    const uint64_t piece_bytes = kPieceSlots * slot_bytes;
+    struct Part {
+        uint32_t u0, u1;
+    };
+    std::vector<Part> parts;
+    for (uint32_t u = 0; u < units;) {
+        Part p{u, u};
+        while (p.u1 < units && base[p.u1 + 1] - base[p.u0] <= slot_tris) ++p.u1;
+        parts.push_back(p);
+        u = p.u1;
+    }
+    const uint64_t tri_bytes = parts.size() <= kPieceSlots ? total * kTri : 2 * piece_bytes;
+    if (tri_bytes > m->mesh_tris_cap) {
+        if (m->mesh_tris) HIPCHK(m, hipFree(m->mesh_tris));
+        m->mesh_tris = nullptr;
+        m->mesh_tris_cap = 0;
+        if (hipMalloc(&m->mesh_tris, tri_bytes) != hipSuccess) return TSDF_ENOMEM;
+        m->mesh_tris_cap = tri_bytes;
+    }
+    hipEvent_t emitted[2], copied[kSlots];
+    for (hipEvent_t &ev : emitted) ev = take_event(m);
+    for (hipEvent_t &ev : copied) ev = take_event(m);
+    // piece q: parts [q * kPieceSlots, ...)
+    auto first_of = [&](size_t q) { return std::min(parts.size(), q * kPieceSlots); };
+    auto emit = [&](size_t q) -> hipError_t {
+        const size_t k0 = first_of(q), k1 = first_of(q + 1);
+        if (k0 == k1) return hipSuccess;
+        const uint32_t u0 = parts[k0].u0, u1 = parts[k1 - 1].u1;
+        hipError_t e = hipSuccess;
+        if (base[u1] > base[u0])
+            e = launch_mesh_emit(A, row_tris, unit_base, u0, u1 - u0, base[u0],
+                                 (float *)((char *)m->mesh_tris + (q & 1) * piece_bytes), m->stream);
+        return e == hipSuccess ? hipEventRecord(emitted[q & 1], m->stream) : e;
+    };
+    auto start = [&](size_t k) -> hipError_t {
+        const int s = (int)(k % kSlots);
+        const size_t q = k / kPieceSlots, k0 = first_of(q);
+        hipError_t e = hipSuccess;
+        if (k == k0) e = hipStreamWaitEvent(m->copy_stream, emitted[q & 1], 0);
+        const uint64_t n = base[parts[k].u1] - base[parts[k].u0];
+        if (e == hipSuccess && n)
+            e = hipMemcpyAsync((char *)m->stage_host + s * slot_bytes,
+                               (char *)m->mesh_tris + (q & 1) * piece_bytes + (base[parts[k].u0] - base[parts[k0].u0]) * kTri,
+                               n * kTri, hipMemcpyDeviceToHost, m->copy_stream);
+        return e == hipSuccess ? hipEventRecord(copied[s], m->copy_stream) : e;
+    };
+    hipError_t e = hipMemcpyAsync(unit_base, base, ((size_t)units + 1) * 8, hipMemcpyHostToDevice, m->stream);
+    for (hipEvent_t ev : emitted)
+        if (!ev) e = hipErrorOutOfMemory;
+    for (hipEvent_t ev : copied)
+        if (!ev) e = hipErrorOutOfMemory;
+    for (size_t q = 0; q < 2 && e == hipSuccess; ++q) e = emit(q);
+    struct Copy {
+        char *dst;
+        const char *src;
+        PageParts pages;
+    } copy[kSlots];
+    Crew::Job job[kSlots];
+    {
+        Crew crew(total * kTri >= kCrewBytes ? kCrewHelpers : 0);
+        // kAhead copies are under way at any time; part k + kAhead takes the
+        // slot of part k + kAhead - kSlots
+        for (size_t k = 0; e == hipSuccess && k < kAhead && k < parts.size(); ++k) e = start(k);
+        for (size_t k = 0; e == hipSuccess && k < parts.size(); ++k) {
+            const int s = (int)(k % kSlots);
+            const uint64_t n = (base[parts[k].u1] - base[parts[k].u0]) * kTri;
+            if ((e = hipEventSynchronize(copied[s])) != hipSuccess) break;
+            // the last copy out of a piece's buffer is done: the piece after
+            // the next goes there
+            if ((k + 1) % kPieceSlots == 0 && (e = emit(k / kPieceSlots + 2)) != hipSuccess) break;
+            copy[s].dst = (char *)tris + base[parts[k].u0] * kTri;
+            copy[s].src = (const char *)m->stage_host + s * slot_bytes;
+            copy[s].pages = PageParts(copy[s].dst, n);
+            job[s].call = [](void *c, int64_t p) {
+                const Copy &C = *(const Copy *)c;
+                const uint64_t at = C.pages.first(p);
+                memcpy(C.dst + at, C.src + at, C.pages.size(p));
+            };
+            job[s].arg = &copy[s];
+            job[s].parts = copy[s].pages.count();
+            crew.post(&job[s]);
+            if (k + kAhead < parts.size()) {
+                crew.wait(&job[(k + kAhead) % kSlots]);
+                e = start(k + kAhead);
+            }
+        }
+        for (int s = 0; s < kSlots; ++s) crew.wait(&job[s]);
+    }
+    if (e != hipSuccess) {
+        (void)hipStreamSynchronize(m->stream);
+        (void)hipStreamSynchronize(m->copy_stream);
+    }
+    for (hipEvent_t ev : emitted)
+        if (ev) m->ev_pool.push_back(ev);
+    for (hipEvent_t ev : copied)
+        if (ev) m->ev_pool.push_back(ev);
+    return e == hipSuccess ? TSDF_OK : fail_device(m);
 }
 
 tsdf_status tsdf_map_get_interpolation(const tsdf_map *m, int64_t *delta_q20)

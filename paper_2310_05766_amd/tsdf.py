@@ -311,7 +311,7 @@ class TsdfMap:
         lo_a, hi_a = (C.c_int32 * 3)(*[int(v) for v in lo]), (C.c_int32 * 3)(*[int(v) for v in hi])
         n = C.c_int64()
         check(_abi.lib().tsdf_mesh(self._h, lo_a, hi_a, None, 0, C.byref(n)), "tsdf_mesh")
-        out = np.zeros((max(n.value, 1), 9), np.float32)
+        out = np.empty((max(n.value, 1), 9), np.float32)  # (written whole)
         check(_abi.lib().tsdf_mesh(self._h, lo_a, hi_a, out.ctypes.data_as(C.POINTER(C.c_float)), n.value,
                                    C.byref(n)), "tsdf_mesh")
         return out[:n.value].reshape(-1, 3, 3)

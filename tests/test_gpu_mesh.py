@@ -69,3 +69,51 @@ def test_mesh_after_shift_and_errors():
     assert rc == _abi.TSDF_ERANGE
     gm.close()
     om.close()
+
+
+def _random_pair(dims, origin, seen, seed):
+    """A GPU map on caller-owned arrays and an oracle map with the same random
+    voxels: a share `seen` of them observed, every sign pattern among them."""
+    import torch
+    from paper_2310_05766_amd.tsdf import TsdfMap
+    g = np.random.Generator(np.random.PCG64(seed))
+    w = (g.random(dims) < seen).astype(np.int16) * g.integers(1, 65, dims, dtype=np.int16)
+    sdf = np.where(w > 0, g.integers(-3072, 3073, dims), 0).astype(np.int16)
+    hi = tuple(origin[a] + dims[a] for a in range(3))
+    om = oracle.OracleMap(dims, origin, 0.05, 3072, 64)
+    om.set_voxels(origin, hi, sdf, w)
+    # slot s of an axis holds the voxel origin + (s - origin) mod n
+    ix = np.ix_(*[(np.arange(n) - o) % n for n, o in zip(dims, origin)])
+    arrays = [torch.from_numpy(np.ascontiguousarray(v[ix])).to("cuda") for v in (sdf, w)]
+    scratch = torch.zeros(TsdfMap.scratch_bytes(dims, origin, 0.05, 3072, 64), dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    return TsdfMap(dims, origin, 0.05, 3072, 64, arrays=(*arrays, scratch)), om
+
+
+@pytest.mark.parametrize("cubes", [(1, 1, 1), (3, 5, 62), (3, 5, 63), (2, 8, 64), (1, 17, 126), (5, 3, 127), (4, 4, 140)])
+def test_mesh_row_and_unit_edges(cubes):
+    """Rows of cubes around one and two spans of a wave, units of rows that
+    are cut, and the ring buffer's wrap inside the box: bit-identical."""
+    dims, origin = (9, 19, 143), (-4, -13, -61)
+    gm, om = _random_pair(dims, origin, 0.97, 5)
+    lo = tuple(origin[a] + (dims[a] - cubes[a]) // 2 for a in range(3))
+    hi = tuple(lo[a] + cubes[a] + 1 for a in range(3))
+    g, o = gm.mesh(lo, hi), om.mesh(lo, hi)
+    say(cubes, g.shape)
+    assert g.shape == o.shape and np.array_equal(g, o)
+    gm.close()
+    om.close()
+
+
+@pytest.mark.parametrize("dims", [(40, 44, 63), (60, 66, 150), (70, 90, 150)])
+def test_mesh_through_staging_slots(dims):
+    """Results of some, of more than one, and of more than two pieces of
+    staging: every slot and buffer is used again."""
+    origin = (-11, 5, -40)
+    gm, om = _random_pair(dims, origin, 0.92, 6)
+    hi = tuple(origin[a] + dims[a] for a in range(3))
+    g, o = gm.mesh(origin, hi), om.mesh(origin, hi)
+    say(dims, g.shape, g.nbytes)
+    assert g.shape == o.shape and np.array_equal(g, o)
+    gm.close()
+    om.close()
