@@ -347,3 +347,22 @@ def test_one_scan_and_multi_scan_batches_interleaved_on_one_stream(graphs):
         gm.close()
     finally:
         set_graph_launch(True)
+
+
+@pytest.mark.parametrize("n", [32767, 32768, 32769, 65535, 70001])
+@pytest.mark.parametrize("bin_block", [128, 256, 512])
+def test_every_point_is_binned_once(n, bin_block):
+    """Binning blocks take patches of 32 rows of a scan's points while whole
+    groups of 32 x 1024 points are left, then points in order: around the group
+    size, counts and maps are the oracle's (a point left out or taken twice
+    changes points_valid and visits)."""
+    dims, origin = (64, 72, 56), (-32, -36, -28)
+    om = oracle.OracleMap(dims, origin, 0.1, 3072, 64)
+    gm = gpu_map(dims, origin, 0.1, 3072, 64)
+    gm.set_blocks(bin_block, 0)
+    for k in range(2):
+        xyz, pose = synth.fuzz_scan((91, n, k), n, extent_m=3.0, nan_frac=0.02), synth.fuzz_pose((92, k), 0.5)
+        assert gm.integrate(xyz, pose, stats=True) == om.integrate(xyz, pose)
+    assert same(gm, om, dims)
+    gm.close()
+    om.close()
