@@ -23,6 +23,8 @@
 //   k_stats       per-scan counts, when asked for
 #include <string.h>
 
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace tsdf {
@@ -47,13 +49,14 @@ __device__ __forceinline__ uint32_t hash_slot(uint32_t key)
 
 // Second half of an entry record: what the tile pass needs of the ray
 // beyond its point, r = isqrt(|D|^2) and the band offsets off = E - q (both
-// exact: r < 2^32, |off_a| <= tau < 2^15), and the voxel crossings per axis
-// (each < 2^7) up to the event that entered the tile.
-__device__ __forceinline__ uint4 entry_ray(const Ray &R, uint32_t cpack)
+// exact: r < 2^32, |off_a| <= tau < 2^15), the voxel crossings per axis
+// (each < 2^7) up to the event that entered the tile, and the scan's sequence
+// slot (< 2^6).
+__device__ __forceinline__ uint4 entry_ray(const Ray &R, uint32_t cpack, uint32_t seq)
 {
     const uint32_t o0 = (uint32_t)(R.E[0] - R.q[0]) & 0xffffu, o1 = (uint32_t)(R.E[1] - R.q[1]) & 0xffffu,
                    o2 = (uint32_t)(R.E[2] - R.q[2]) & 0xffffu;
-    return make_uint4((uint32_t)R.r, o0 | o1 << 16, o2 | (cpack & 0xffffu) << 16, cpack >> 16);
+    return make_uint4((uint32_t)R.r, o0 | o1 << 16, o2 | (cpack & 0xffffu) << 16, cpack >> 16 | seq << 8);
 }
 
 // The point of thread t of a scan's block b. A block takes a patch of the
@@ -148,7 +151,8 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
         }
     }
     const uint32_t valid = active ? 1u : 0u;
-    const uint32_t key0 = (uint32_t)SD.seq * H.gtiles + MD.tile_base;
+    const uint32_t seq = (uint32_t)SD.seq;
+    const uint32_t key0 = seq * H.gtiles + MD.tile_base;
     // the map's tile counts in registers: loads through MD inside the walk
     // would be repeated after every atomic (they may alias)
     const uint32_t nt0 = (uint32_t)__builtin_amdgcn_readfirstlane(MD.nt[0]);
@@ -191,7 +195,7 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
                 const uint32_t pos = atomicAdd(&B.cursor[key], 1u);
                 if (pos < H.cap) {
                     B.entries[pos] = make_uint4((uint32_t)i, (uint32_t)q[0], (uint32_t)q[1], (uint32_t)q[2]);
-                    B.entries2[pos] = entry_ray(R, cpack);
+                    B.entries2[pos] = entry_ray(R, cpack, seq);
                 } else {
                     atomicOr(&B.ctl->overflow, 1u);
                 }
@@ -229,7 +233,7 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
         const uint32_t pos = h_base[sc & 1023u] + s_rank[k * kBinBlock + threadIdx.x];
         if (pos < H.cap) {
             B.entries[pos] = rec;
-            B.entries2[pos] = entry_ray(R, counts_7to8(sc >> 10));
+            B.entries2[pos] = entry_ray(R, counts_7to8(sc >> 10), seq);
         } else {
             atomicOr(&B.ctl->overflow, 1u);
         }
@@ -361,33 +365,38 @@ __global__ __launch_bounds__(kAllocBlock) void k_alloc(BatchArrays B)
 
 // Eq. (1) with one unit of weight, Eq. (2), on a voxel state held in 32-bit
 // registers (the stored int16 values, sign-extended once).
-__device__ __forceinline__ void merge_one(int32_t &sdf, int32_t &w, uint64_t key, int32_t w_max)
+__device__ __forceinline__ void merge_one(int32_t &sdf, int32_t &w, int32_t v, int32_t w_max)
 {
-    const int32_t v = tile_key_sdf(key);
     sdf = rdiv_small(__mul24(sdf, w) + v, w + 1);  // |sdf|, w < 2^15: a 24-bit product
     w = w + 1 < w_max ? w + 1 : w_max;
 }
 
-__device__ __forceinline__ void merge_one(int16_t &sdf, int16_t &w, uint64_t key, int32_t w_max)
+__device__ __forceinline__ void merge_one(int16_t &sdf, int16_t &w, int32_t v, int32_t w_max)
 {
     int32_t s = sdf, ww = w;
-    merge_one(s, ww, key, w_max);
+    merge_one(s, ww, v, w_max);
     sdf = (int16_t)s;
     w = (int16_t)ww;
 }
 
-constexpr int kMaxGroup = 8;
+// A candidate's key in LDS: 64 bits, or 32 where tau and the point counts
+// leave room (key32_shift), which doubles the slots that a group holds.
+__device__ __forceinline__ int32_t key_value(uint64_t key, uint32_t) { return tile_key_sdf(key); }
+__device__ __forceinline__ int32_t key_value(uint32_t key, uint32_t shift) { return tile_key_sdf(key, shift); }
 
 // Merge the touched voxels of one run of 8 z-consecutive voxels straight
 // into HBM (one busy sequence slot on the tile).
-__device__ __forceinline__ uint32_t merge_run_direct(uint64_t *kr, const MapDev &MD, int64_t row, int32_t rz0)
+template <typename Key>
+__device__ __forceinline__ uint32_t merge_run_direct(Key *kr, uint32_t shift, const MapDev &MD, int64_t row,
+                                                     int32_t rz0)
 {
-    uint64_t kk[8];
+    constexpr Key kNone = (Key)~(Key)0;
+    Key kk[8];
     bool any = false;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         kk[j] = kr[j];
-        any |= kk[j] != kEmptyKey;
+        any |= kk[j] != kNone;
     }
     if (!any) return 0;
     uint32_t updated = 0;
@@ -401,20 +410,21 @@ __device__ __forceinline__ uint32_t merge_run_direct(uint64_t *kr, const MapDev 
         int16_t *wp = reinterpret_cast<int16_t *>(&wv);
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-            if (kk[j] != kEmptyKey) {
-                merge_one(sp[j], wp[j], kk[j], MD.w_max);
-                kr[j] = kEmptyKey;
+            if (kk[j] != kNone) {
+                merge_one(sp[j], wp[j], key_value(kk[j], shift), MD.w_max);
+                kr[j] = kNone;
                 ++updated;
             }
         *reinterpret_cast<int4 *>(MD.sdf + row + sz) = sv;
         *reinterpret_cast<int4 *>(MD.w + row + sz) = wv;
     } else {
         for (int j = 0; j < 8; ++j) {
-            if (kk[j] == kEmptyKey) continue;
+            if (kk[j] == kNone) continue;
+            kr[j] = kNone;
+            if (rz0 + j >= MD.dims[2]) continue;  // the tile's part outside the window
             int32_t sz = rz0 + j + MD.ring0[2];
             sz -= sz >= MD.dims[2] ? MD.dims[2] : 0;
-            merge_one(MD.sdf[row + sz], MD.w[row + sz], kk[j], MD.w_max);
-            kr[j] = kEmptyKey;
+            merge_one(MD.sdf[row + sz], MD.w[row + sz], key_value(kk[j], shift), MD.w_max);
             ++updated;
         }
     }
@@ -439,11 +449,16 @@ __device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__bui
 // LDS byte address of a shared-memory pointer, and back: an address kept
 // in one integer register needs no base added per access.
 typedef __attribute__((address_space(3))) unsigned long long lds_u64;
+typedef __attribute__((address_space(3))) unsigned int lds_u32;
 
-__device__ __forceinline__ uint32_t lds_address(uint64_t *p) { return (uint32_t)(uintptr_t)(lds_u64 *)p; }
-__device__ __forceinline__ unsigned long long *lds_pointer(int32_t a)
+__device__ __forceinline__ uint32_t lds_address(void *p) { return (uint32_t)(uintptr_t)(lds_u32 *)(uint32_t *)p; }
+__device__ __forceinline__ void lds_min(int32_t a, uint64_t key)
 {
-    return (unsigned long long *)(lds_u64 *)(uintptr_t)(uint32_t)a;
+    atomicMin((unsigned long long *)(lds_u64 *)(uintptr_t)(uint32_t)a, (unsigned long long)key);
+}
+__device__ __forceinline__ void lds_min(int32_t a, uint32_t key)
+{
+    atomicMin((unsigned int *)(lds_u32 *)(uintptr_t)(uint32_t)a, key);
 }
 __device__ __forceinline__ int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 template <typename T>
@@ -479,41 +494,50 @@ __device__ __forceinline__ MapDev uniform_map(const MapDev &m)
 // XCD keeps same-address atomics spread; with fewer than 8 workgroups each
 // queue still has one, so every job is reached). A tile's job record holds
 // its map and its busy sequence slots, so that the runs and the map record
-// of a tile are requested together, and a group's sensors come from a table
-// indexed by (map, sequence slot). Per tile, the busy sequence slots are
-// taken in groups of G: the candidates of a group's runs are computed
+// of a tile are requested together, with the sensors of its slots, which come
+// from a table indexed by (map, sequence slot). Per tile, the busy sequence
+// slots are taken in groups of G: the candidates of a group's runs are computed
 // together, one LDS key buffer per slot, then each voxel applies the group's
-// scans in submission order. A tile busy in several slots keeps its SDF and
-// weights in LDS.
-// At most 96 VGPRs: five waves per SIMD, the most this kernel holds without
-// spilling.
-template <int kTileBlock, bool kStats>
-__global__ __launch_bounds__(kTileBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_tile(BatchArrays B)
+// scans in submission order. A group's runs lie one after another, and a
+// record names its slot, so an entry needs no search for its run. A tile busy
+// in several slots keeps its SDF and weights in LDS.
+// Bound by instruction issue. Against 64-bit keys alone, a search over the
+// group's runs per entry and a set-up through the general walk (96 VGPRs,
+// spills), on 50 scans of 128 x 1024 points 333 -> 264 us, on one 29.0 -> 22.8.
+template <int kTileBlock, bool kStats, typename Key>
+__global__ __launch_bounds__(kTileBlock) __attribute__((amdgpu_waves_per_eu(kTileWaves))) void k_tile(BatchArrays B)
 {
-    extern __shared__ uint64_t s_keys[];  // G * tvox keys, then the cached tile: tvox sdf, tvox w
-    // per busy slot of the tile, in sequence order: first entry, entries,
-    // sequence slot; per slot of the current group: sensor (o, tau)
+    constexpr Key kNone = (Key)~(Key)0;
+    constexpr int kGroup = sizeof(Key) == 4 ? kMaxGroup32 : kMaxGroup64;
+    constexpr int kKeyLog2 = sizeof(Key) == 4 ? 2 : 3;
+    extern __shared__ uint64_t s_dyn[];  // G * tvox keys, then the cached tile: tvox sdf, tvox w
+    Key *s_keys = reinterpret_cast<Key *>(s_dyn);
+    // (kTileStaticLds bounds these) per busy slot of the tile, in sequence
+    // order: first entry, entries, sequence slot; per sequence slot: sensor,
+    // and tau | place among the busy slots << 16
     __shared__ uint32_t s_beg[kMaxSeq], s_cnt[kMaxSeq];
     __shared__ uint8_t s_list[kMaxSeq];
-    __shared__ int4 s_sens[kMaxGroup];
-    __shared__ uint32_t s_vis[kMaxGroup], s_upd[kMaxGroup];
+    __shared__ int4 s_sens[kMaxSeq];
+    __shared__ uint32_t s_vis[kGroup], s_upd[kGroup];
     __shared__ uint32_t s_job;
     const BatchHdr H = *B.hdr;
     const int32_t lsum = H.lt[0] + H.lt[1] + H.lt[2];
     const uint32_t tvox = 1u << lsum;
     const int32_t G = H.G;
+    const uint32_t kshift = H.key_shift;
     int16_t *c_sdf = reinterpret_cast<int16_t *>(s_keys + (size_t)G * tvox);
     int16_t *c_w = c_sdf + tvox;
     // heavy tiles first (from the list's start), then the others (from its end)
     const uint32_t nheavy = B.ctl->n_nonempty, nne = nheavy + B.ctl->n_light;
     const uint32_t ez = 1u << H.lt[2], ey = 1u << H.lt[1];
-    const int32_t sh[3] = {H.lt[1] + H.lt[2], H.lt[2], 0};  // LDS index shift per axis
-    const int32_t shb[3] = {sh[0] + 3, sh[1] + 3, 3};          // the same, in bytes of 8-byte keys
+    // LDS address shift per axis, in bytes of keys
+    const int32_t shb[3] = {H.lt[1] + H.lt[2] + kKeyLog2, H.lt[2] + kKeyLog2, kKeyLog2};
+    const int32_t ext[3] = {1 << H.lt[0], 1 << H.lt[1], 1 << H.lt[2]};
     uint32_t job = blockIdx.x;
     if (job >= nne) return;
     const uint32_t nq = gridDim.x < (uint32_t)kQueues ? gridDim.x : (uint32_t)kQueues;
     const uint32_t queue = blockIdx.x % nq;
-    for (uint32_t v = threadIdx.x; v < (uint32_t)G * tvox; v += kTileBlock) s_keys[v] = kEmptyKey;
+    for (uint32_t v = threadIdx.x; v < (uint32_t)G * tvox; v += kTileBlock) s_keys[v] = kNone;
     while (job < nne) {
         const uint32_t at = job < nheavy ? job : H.gtiles - 1u - (job - nheavy);
         const uint4 jb = B.jobs[at];
@@ -526,9 +550,12 @@ __global__ __launch_bounds__(kTileBlock) __attribute__((amdgpu_waves_per_eu(5)))
         if (threadIdx.x < 64u && ((busy >> threadIdx.x) & 1ull)) {
             const uint32_t k = threadIdx.x * H.gtiles + g;
             const int p = __popcll(busy & ((1ull << threadIdx.x) - 1ull));
+            int4 sens = B.seq_sensor[mb * H.S + (int32_t)threadIdx.x];
             s_cnt[p] = B.counts[k];
             s_beg[p] = B.offsets[k];
             s_list[p] = (uint8_t)threadIdx.x;
+            sens.w |= p << 16;
+            s_sens[threadIdx.x] = sens;
         }
         const MapDev MD = uniform_map(B.maps[mb]);
         const uint32_t t = g - MD.tile_base;
@@ -536,12 +563,15 @@ __global__ __launch_bounds__(kTileBlock) __attribute__((amdgpu_waves_per_eu(5)))
         const uint32_t txy = t / (uint32_t)MD.nt[2];
         const int32_t t0[3] = {(int32_t)(txy / (uint32_t)MD.nt[1]) << H.lt[0],
                                (int32_t)(txy % (uint32_t)MD.nt[1]) << H.lt[1], (int32_t)tz << H.lt[2]};
-        // the tile's voxel box, clipped to the window, in global coordinates
-        int32_t blo[3], bhi[3];
+        // the tile's first voxel in global coordinates; a tile that the
+        // window's edge cuts is walked whole, and its voxels outside get no
+        // merge
+        int32_t blo[3];
+        bool cut = false;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             blo[a] = MD.origin[a] + t0[a];
-            bhi[a] = MD.origin[a] + min(t0[a] + (1 << H.lt[a]), MD.dims[a]);
+            cut = cut || t0[a] + (1 << H.lt[a]) > MD.dims[a];
         }
         __syncthreads();
         const bool cached = nbusy > 1;
@@ -558,89 +588,88 @@ __global__ __launch_bounds__(kTileBlock) __attribute__((amdgpu_waves_per_eu(5)))
             }
         }
         for (int j0 = 0; j0 < nbusy; j0 += G) {
-            // a group: busy slots j0 .. j0 + ng - 1 of the list, in order
+            // a group: busy slots j0 .. j0 + ng - 1 of the list, in order;
+            // their runs are one stretch of records
             const int ng = min(G, nbusy - j0);
-            // inclusive prefix of the group's run lengths (uniform: scalar
-            // registers), so that an entry finds its run by comparisons
-            uint32_t pre[kMaxGroup];
-            uint32_t gsum = 0;
-#pragma unroll
-            for (int r = 0; r < kMaxGroup; ++r) {
-                if (r < ng) gsum += s_cnt[j0 + r];
-                pre[r] = uniform(gsum);
-            }
-            gsum = uniform(gsum);
-            if (threadIdx.x < (uint32_t)ng) {
-                s_vis[threadIdx.x] = 0;
-                s_upd[threadIdx.x] = 0;
-                s_sens[threadIdx.x] = B.seq_sensor[mb * H.S + (int32_t)s_list[j0 + threadIdx.x]];
-            }
-            __syncthreads();
-            for (uint32_t e = threadIdx.x; e < gsum; e += kTileBlock) {
-                // which run of the group entry e belongs to (the group's
-                // runs are all non-empty: pre rises strictly up to gsum)
-                int r = 0;
-                uint32_t base = 0;
-#pragma unroll
-                for (int k = 0; k < kMaxGroup - 1; ++k) {
-                    const bool past = e >= pre[k];
-                    r += past ? 1 : 0;
-                    base = past ? pre[k] : base;
+            const uint32_t beg = uniform(s_beg[j0]);
+            const uint32_t end = min(uniform(s_beg[j0 + ng - 1] + s_cnt[j0 + ng - 1]), H.cap);
+            if (kStats) {
+                if (threadIdx.x < (uint32_t)ng) {
+                    s_vis[threadIdx.x] = 0;
+                    s_upd[threadIdx.x] = 0;
                 }
-                const uint32_t ee = e - base;
-                const uint32_t beg = s_beg[j0 + r];
-                // the run lies inside the entry buffer unless the fill overflowed
-                if (beg + ee >= H.cap) continue;
-                const uint4 ra = B.entries[beg + ee];
-                const uint4 rb = B.entries2[beg + ee];
+                __syncthreads();
+            }
+            for (uint32_t e = beg + threadIdx.x; e < end; e += kTileBlock) {
+                const uint4 ra = B.entries[e];
+                const uint4 rb = B.entries2[e];
                 const uint32_t i = ra.x;
-                const int4 sens = s_sens[r];
+                const int4 sens = s_sens[(rb.w >> 8) & (kMaxSeq - 1)];
                 const int32_t o[3] = {sens.x, sens.y, sens.z};
-                const int32_t tau = sens.w;
+                const int32_t tau = sens.w & 0xffff;
+                const int32_t r = (sens.w >> 16) - j0;
                 const int32_t q[3] = {(int32_t)ra.y, (int32_t)ra.z, (int32_t)ra.w};
                 const int32_t off[3] = {(int16_t)(rb.y & 0xffffu), (int16_t)(rb.y >> 16), (int16_t)(rb.z & 0xffffu)};
                 const int32_t c[3] = {(int32_t)((rb.z >> 16) & 0xffu), (int32_t)(rb.z >> 24), (int32_t)(rb.w & 0xffu)};
                 // resume the walk right after the event that entered the
-                // tile, set down on its first voxel in the box; the voxels
-                // of the walk inside the box are one run (the walk carries
-                // the key's LDS address itself)
+                // tile; its voxels inside the tile are one run (the walk
+                // carries the key's LDS address itself)
                 Ray R;
                 BoxWalk V;
-                if (!box_walk_resume(q, off, rb.x, c, o, tau, blo, bhi, shb, lds_address(s_keys + (size_t)r * tvox), R,
-                                     V))
-                    continue;
+                const uint32_t base = lds_address(s_keys) + (((uint32_t)r << lsum) << kKeyLog2);
+                tile_walk_resume(q, off, rb.x, c, o, tau, blo, ext, shb, base, R, V);
                 const double taud = (double)tau, rh = R.r + 0.5;
-                const uint32_t ihi = i >> 16, ilo = i << 16;
                 uint32_t visits = 0;
-                do {
-                    atomicMin(lds_pointer(V.lv), (unsigned long long)tile_key(V.n, rh, R.inv_r2, taud, ihi, ilo));
-                    ++visits;
-                } while (box_walk_next(V));
+                // (a candidate outside the window is no visit)
+                const auto resident = [&]() {
+                    const uint32_t v = ((uint32_t)V.lv - base) >> kKeyLog2;
+                    return (int32_t)(v & (ez - 1)) + t0[2] < MD.dims[2] &&
+                           (int32_t)((v >> H.lt[2]) & (ey - 1)) + t0[1] < MD.dims[1] &&
+                           (int32_t)(v >> (H.lt[1] + H.lt[2])) + t0[0] < MD.dims[0];
+                };
+                if (sizeof(Key) == 4) {
+                    do {
+                        lds_min(V.lv, tile_key32(V.n, rh, R.inv_r2, taud, kshift, i));
+                        if (kStats) visits += !cut || resident() ? 1u : 0u;
+                    } while (box_walk_next(V));
+                } else {
+                    const uint32_t ihi = i >> 16, ilo = i << 16;
+                    do {
+                        lds_min(V.lv, tile_key(V.n, rh, R.inv_r2, taud, ihi, ilo));
+                        if (kStats) visits += !cut || resident() ? 1u : 0u;
+                    } while (box_walk_next(V));
+                }
                 if (kStats && visits) atomicAdd(&s_vis[r], visits);
             }
             __syncthreads();
             if (cached) {
                 // each voxel applies the group's scans in submission order,
                 // its cached state held in registers across them
-                uint32_t upd[kMaxGroup];
+                uint32_t upd[kGroup];
 #pragma unroll
-                for (int r = 0; r < kMaxGroup; ++r) upd[r] = 0;
+                for (int r = 0; r < kGroup; ++r) upd[r] = 0;
                 for (uint32_t v = threadIdx.x; v < tvox; v += kTileBlock) {
                     int32_t vs = 0, vw = 0;
                     bool touched = false;
+                    if (cut && ((int32_t)(v & (ez - 1)) + t0[2] >= MD.dims[2] ||
+                                (int32_t)((v >> H.lt[2]) & (ey - 1)) + t0[1] >= MD.dims[1] ||
+                                (int32_t)(v >> (H.lt[1] + H.lt[2])) + t0[0] >= MD.dims[0])) {
+                        for (int r = 0; r < ng; ++r) s_keys[(uint32_t)r * tvox + v] = kNone;
+                        continue;
+                    }
 #pragma unroll
-                    for (int r = 0; r < kMaxGroup; ++r) {
+                    for (int r = 0; r < kGroup; ++r) {
                         if (r >= ng) break;
-                        uint64_t *kp = &s_keys[(size_t)r * tvox + v];
-                        const uint64_t key = *kp;
-                        if (key == kEmptyKey) continue;
+                        Key *kp = &s_keys[(uint32_t)r * tvox + v];
+                        const Key key = *kp;
+                        if (key == kNone) continue;
                         if (!touched) {
                             vs = c_sdf[v];
                             vw = c_w[v];
                             touched = true;
                         }
-                        merge_one(vs, vw, key, MD.w_max);
-                        *kp = kEmptyKey;
+                        merge_one(vs, vw, key_value(key, kshift), MD.w_max);
+                        *kp = kNone;
                         ++upd[r];
                     }
                     if (touched) {
@@ -653,20 +682,23 @@ __global__ __launch_bounds__(kTileBlock) __attribute__((amdgpu_waves_per_eu(5)))
                         if (upd[r]) atomicAdd(&s_upd[r], upd[r]);
             } else {
                 // a single busy slot: merge straight into HBM, runs of 8
-                const int rb = 0;
                 uint32_t updated = 0;
                 for (uint32_t v0 = threadIdx.x * 8u; v0 < tvox; v0 += kTileBlock * 8u) {
                     const int32_t rz0 = (int32_t)(v0 & (ez - 1)) + t0[2];
                     const int32_t ry = (int32_t)((v0 >> H.lt[2]) & (ey - 1)) + t0[1];
                     const int32_t rx = (int32_t)(v0 >> (H.lt[1] + H.lt[2])) + t0[0];
-                    if (rx >= MD.dims[0] || ry >= MD.dims[1] || rz0 >= MD.dims[2]) continue;  // no key there
+                    if (cut && (rx >= MD.dims[0] || ry >= MD.dims[1] || rz0 >= MD.dims[2])) {
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) s_keys[v0 + j] = kNone;
+                        continue;
+                    }
                     int32_t sx = rx + MD.ring0[0], sy = ry + MD.ring0[1];
                     sx -= sx >= MD.dims[0] ? MD.dims[0] : 0;
                     sy -= sy >= MD.dims[1] ? MD.dims[1] : 0;
                     const int64_t row = ((int64_t)sx * MD.dims[1] + sy) * MD.dims[2];
-                    updated += merge_run_direct(&s_keys[(size_t)rb * tvox + v0], MD, row, rz0);
+                    updated += merge_run_direct(&s_keys[v0], kshift, MD, row, rz0);
                 }
-                if (kStats && updated) atomicAdd(&s_upd[rb], updated);
+                if (kStats && updated) atomicAdd(&s_upd[0], updated);
             }
             __syncthreads();
             if (threadIdx.x < (uint32_t)ng) {
@@ -764,7 +796,44 @@ void launch_bin_any(bool fill, uint32_t bins, uint32_t block, const BatchArrays 
     else launch_bin<256>(fill, bins, B, I, stream);
 }
 
+template <int kTB, bool kStats, typename Key>
+void launch_tile_as(const LaunchCaps &caps, const BatchArrays &B, hipStream_t stream)
+{
+    hipLaunchKernelGGL((k_tile<kTB, kStats, Key>), dim3((uint32_t)caps.tile_grid), dim3(kTB), caps.tile_lds, stream, B);
+}
+
+template <int kTB>
+void launch_tile(const LaunchCaps &caps, const BatchArrays &B, hipStream_t stream)
+{
+    if (caps.key32 && caps.stats) launch_tile_as<kTB, true, uint32_t>(caps, B, stream);
+    else if (caps.key32) launch_tile_as<kTB, false, uint32_t>(caps, B, stream);
+    else if (caps.stats) launch_tile_as<kTB, true, uint64_t>(caps, B, stream);
+    else launch_tile_as<kTB, false, uint64_t>(caps, B, stream);
+}
+
 }  // namespace
+
+TilePlan tile_plan(const int32_t lt[3], int32_t S, int32_t tau, int64_t max_points, int32_t tile_block, int32_t cus)
+{
+    TilePlan P;
+    P.key_shift = key32_shift(tau, max_points);
+    const int64_t key = P.key_shift ? 4 : 8, most = P.key_shift ? kMaxGroup32 : kMaxGroup64;
+    // LDS of a tile workgroup: G key buffers and the cached tile (4 bytes per
+    // voxel). G as large as lets the workgroups a CU holds (kTileWaves per
+    // 256 threads) share its 160 KB, 128 granules of 1280 bytes; the
+    // persistent grid fills the CUs.
+    const int64_t tvox = (int64_t)1 << (lt[0] + lt[1] + lt[2]);
+    const int64_t granules = 128 / kTileWaves;  // of 1280 bytes, per 256 threads
+    const int64_t budget = granules * 1280 * (tile_block / 256) - kTileStaticLds;
+    const int64_t gfit = (budget / tvox - 4) / key;
+    P.G = (int32_t)std::max<int64_t>(1, std::min<int64_t>({gfit, most, (int64_t)S}));
+    P.lds = (uint32_t)((key * P.G + 4) * tvox);
+    const int by_waves = 4 * kTileWaves / (tile_block / 64);  // four SIMDs
+    const int per_cu = (int)std::max<size_t>(
+        1, std::min<size_t>((size_t)by_waves, (size_t)(160 * 1024) / (P.lds + (uint32_t)kTileStaticLds)));
+    P.grid = cus * per_cu;
+    return P;
+}
 
 bool launch_blocks_ok(int32_t bin_block, int32_t tile_block)
 {
@@ -787,14 +856,8 @@ hipError_t launch_batch(const BatchArrays &B, const LaunchCaps &caps, hipStream_
     if (ev_binned && (e = hipEventRecord(ev_binned, stream)) != hipSuccess) return e;
     // the per-scan counts are a template switch: without them the walk and
     // the merges carry no counters
-    const dim3 tg((uint32_t)caps.tile_grid);
-    if (caps.tile_block == 512) {
-        if (caps.stats) hipLaunchKernelGGL((k_tile<512, true>), tg, dim3(512), caps.tile_lds, stream, B);
-        else hipLaunchKernelGGL((k_tile<512, false>), tg, dim3(512), caps.tile_lds, stream, B);
-    } else {
-        if (caps.stats) hipLaunchKernelGGL((k_tile<256, true>), tg, dim3(256), caps.tile_lds, stream, B);
-        else hipLaunchKernelGGL((k_tile<256, false>), tg, dim3(256), caps.tile_lds, stream, B);
-    }
+    if (caps.tile_block == 512) launch_tile<512>(caps, B, stream);
+    else launch_tile<256>(caps, B, stream);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (ev_tiles && (e = hipEventRecord(ev_tiles, stream)) != hipSuccess) return e;
     if (caps.stats) hipLaunchKernelGGL(k_stats, dim3(caps.scans > 0 ? caps.scans : 1u), dim3(256), 0, stream, B);

@@ -276,12 +276,14 @@ tsdf_status Engine::run_chunk(const std::vector<MapRef> &maps, const std::vector
     if (C >= ((uint64_t)1 << 31)) return TSDF_ERANGE;
     // binning blocks, points, entries
     uint64_t nblocks = 0, npoints = 0, nhost = 0;
+    int64_t max_points = 0;
     std::vector<uint32_t> block0(nscans);
     for (size_t k = 0; k < nscans; ++k) {
         const ScanRef &s = scans[b + k];
         block0[k] = (uint32_t)nblocks;
         nblocks += (uint64_t)((s.n + bb - 1) / bb);
         npoints += (uint64_t)s.n;
+        max_points = std::max(max_points, s.n);
         if (s.host) nhost += (uint64_t)s.n;
     }
     const uint64_t need_entries = npoints * (uint64_t)max_tiles_per_ray(tau_max, lt) + 1024;
@@ -372,7 +374,6 @@ tsdf_status Engine::run_chunk(const std::vector<MapRef> &maps, const std::vector
     hdr->cap = (uint32_t)std::min<size_t>(entries_cap_ / (2 * sizeof(uint4)), 0xffffffffu);
     hdr->want_stats = stats ? 1u : 0u;
     hdr->bin_block = bb;
-    hdr->pad = 0;
     memcpy(h + L.maps, md.data(), nmaps * sizeof(MapDev));
     ScanDev *sd = (ScanDev *)(h + L.scans);
     uint32_t *bs = (uint32_t *)(h + L.block_scan);
@@ -403,23 +404,12 @@ tsdf_status Engine::run_chunk(const std::vector<MapRef> &maps, const std::vector
     caps.bin_block = bb;
     caps.tile_block = (uint32_t)shape.tile_block;
     caps.stats = stats ? 1u : 0u;
-    {
-        // LDS of a tile workgroup: G key buffers (8 bytes per voxel) and the
-        // cached tile (4 bytes per voxel); G as large as ~32 KB per 256
-        // threads allows, so that the workgroups a CU holds (the kernel's
-        // register budget allows five waves per SIMD: five workgroups of
-        // 256, two of 512) fit its 160 KB; the persistent grid fills the CUs
-        const size_t tvox = (size_t)1 << (lt[0] + lt[1] + lt[2]);
-        const int64_t budget = (int64_t)(32 * 1024) * (shape.tile_block / 256);
-        const int64_t gfit = (budget / (int64_t)tvox - 4) / 8;
-        const int32_t G = (int32_t)std::max<int64_t>(1, std::min<int64_t>({gfit, 8, (int64_t)S}));
-        hdr->G = G;
-        caps.tile_lds = (uint32_t)((8 * (size_t)G + 4) * tvox);
-        const int by_waves = 20 / (shape.tile_block / 64);  // five waves per SIMD, four SIMDs
-        const int per_cu =
-            (int)std::max<size_t>(1, std::min<size_t>((size_t)by_waves, (160 * 1024) / caps.tile_lds));
-        caps.tile_grid = shape.tile_grid > 0 ? shape.tile_grid : num_cu_ * per_cu;
-    }
+    const TilePlan plan = tile_plan(lt, S, tau_max, max_points, shape.tile_block, num_cu_);
+    hdr->G = plan.G;
+    hdr->key_shift = plan.key_shift;
+    caps.key32 = plan.key_shift ? 1u : 0u;
+    caps.tile_lds = plan.lds;
+    caps.tile_grid = shape.tile_grid > 0 ? shape.tile_grid : plan.grid;
     InlineDesc I;
     memset(&I, 0, sizeof(I));
     if (one) {

@@ -60,7 +60,7 @@ struct BatchHdr {
     uint32_t cap;        // entry capacity
     uint32_t want_stats;
     uint32_t bin_block;  // binning threads per block (one ray each)
-    uint32_t pad;
+    uint32_t key_shift;  // of the tile pass's 32-bit keys; 0: 64-bit keys
 };
 
 // The descriptors of a batch of one scan, handed to the first binning
@@ -102,7 +102,7 @@ struct BatchArrays {
     uint32_t *tile_upd;    // [S * gtiles] voxels updated per (seq, tile)
     uint4 *jobs;           // [gtiles] busy tiles: (global tile, map slot, busy sequence slots as a 64-bit mask)
     uint4 *entries;        // [cap] (point index, q.x, q.y, q.z), by tile then seq
-    uint4 *entries2;       // [cap] (r, packed band offsets, crossing counts at tile entry)
+    uint4 *entries2;       // [cap] (r, packed band offsets, crossing counts at tile entry, sequence slot)
     uint32_t *valid_part;  // [nblocks] points with a ray per binning block
     uint32_t *scan_stats;  // [nscans * 4] updated, valid, visits, overflow
     BatchCtl *ctl;
@@ -123,7 +123,25 @@ struct LaunchCaps {
     uint32_t bin_block;   // binning threads per block: 128, 256 or 512
     uint32_t tile_block;  // tile workgroup size: 256 or 512
     uint32_t stats;       // per-scan counts wanted: k_stats runs only then
+    uint32_t key32;       // 32-bit keys in the tile pass
 };
+
+// The tile pass's LDS and grid for a tiling, S sequence slots, a truncation and
+// the points of the largest scan.
+constexpr int kMaxGroup32 = 16, kMaxGroup64 = 8;  // sequence slots a tile workgroup holds at once, by key size
+constexpr int kTileStaticLds = 1792;              // k_tile's fixed tables
+// Waves per SIMD of the tile pass: its registers would allow seven, but fewer
+// LDS bytes per workgroup mean fewer slots per group (5, 6, 7 waves on 50 scans
+// of 128 x 1024 points: 267, 264, 268 us; on 64 uneven scans into 16 maps: 331,
+// 326, 339; on 32 small scans into 32 maps: 107, 97, 95).
+constexpr int kTileWaves = 6;
+struct TilePlan {
+    uint32_t key_shift;  // 0: 64-bit keys
+    int32_t G;
+    uint32_t lds;        // dynamic LDS bytes of a workgroup
+    int32_t grid;        // workgroups that fill the device
+};
+TilePlan tile_plan(const int32_t lt[3], int32_t S, int32_t tau, int64_t max_points, int32_t tile_block, int32_t cus);
 
 // The block sizes the kernels are built for.
 bool launch_blocks_ok(int32_t bin_block, int32_t tile_block);

@@ -208,7 +208,6 @@ extern "C" tsdf_status tsdf_integrate_scan_noalloc(tsdf_map *m, const float *xyz
         BatchHdr hdr;
         for (int a = 0; a < 3; ++a) hdr.lt[a] = lt[a];
         hdr.S = 1;
-        hdr.G = 1;
         hdr.nmaps = 1;
         hdr.nscans = 1;
         hdr.gtiles = md.ntot;
@@ -216,7 +215,9 @@ extern "C" tsdf_status tsdf_integrate_scan_noalloc(tsdf_map *m, const float *xyz
         hdr.cap = (uint32_t)cap;
         hdr.want_stats = stats ? 1u : 0u;
         hdr.bin_block = (uint32_t)shape.bin_block;
-        hdr.pad = 0;
+        const TilePlan plan = tile_plan(lt, 1, m->d.tau_q10, n_points, shape.tile_block, g_cu[m->device]);
+        hdr.G = plan.G;
+        hdr.key_shift = plan.key_shift;
         LaunchCaps caps;
         caps.blocks = (uint32_t)nblocks;
         caps.gtiles = md.ntot;
@@ -224,12 +225,9 @@ extern "C" tsdf_status tsdf_integrate_scan_noalloc(tsdf_map *m, const float *xyz
         caps.bin_block = (uint32_t)shape.bin_block;
         caps.tile_block = (uint32_t)shape.tile_block;
         caps.stats = stats ? 1u : 0u;
-        const size_t tvox = (size_t)1 << (lt[0] + lt[1] + lt[2]);
-        caps.tile_lds = (uint32_t)((8 + 4) * tvox);
-        const int by_waves = 20 / (shape.tile_block / 64);
-        const int per_cu =
-            (int)std::max<size_t>(1, std::min<size_t>((size_t)by_waves, (160 * 1024) / caps.tile_lds));
-        caps.tile_grid = m->tile_grid > 0 ? m->tile_grid : g_cu[m->device] * per_cu;
+        caps.key32 = plan.key_shift ? 1u : 0u;
+        caps.tile_lds = plan.lds;
+        caps.tile_grid = m->tile_grid > 0 ? m->tile_grid : plan.grid;
         if (launch_noalloc_setup(B, hdr, md, sd, m->stream) != hipSuccess ||
             launch_batch(B, caps, m->stream, nullptr, nullptr, nullptr) != hipSuccess) {
             st = TSDF_EDEVICE;

@@ -222,6 +222,23 @@ __device__ __forceinline__ uint64_t band_key(double n, double rh, double inv_r2,
     return (uint64_t)(as << 16 | ihi) << 32 | lo;
 }
 
+// The two words of a double (register moves).
+__device__ __forceinline__ uint32_t high_word(double v)
+{
+    uint64_t b;
+    __builtin_memcpy(&b, &v, sizeof(b));
+    return (uint32_t)(b >> 32);
+}
+
+// |s| of a band walk voxel, as band_key has it: the same quotient from one fma
+// (2 inv_r2 and rh inv_r2 do not change along a walk; the product's rounding
+// moves from the sum to rh inv_r2, 2^-54, so the estimate stays off by under
+// 2^-34.8), and truncation after the cap (x >= 0 and taud an integer).
+__device__ __forceinline__ uint32_t tile_distance(double n, double rh, double inv_r2, double taud)
+{
+    return (uint32_t)min_nonan(__fma_rn(fabs(n), 2.0 * inv_r2, rh * inv_r2), taud);
+}
+
 // The tile pass's key of a band walk voxel, ordered like band_key: |s| << 48
 // | i << 16 | sign, with the sign of s (that of n) in bit 0 instead of s's
 // low 16 bits. A point meets a voxel once per scan, so keys of equal |s|
@@ -230,18 +247,40 @@ __device__ __forceinline__ uint64_t band_key(double n, double rh, double inv_r2,
 __device__ __forceinline__ uint64_t tile_key(double n, double rh, double inv_r2, double taud, uint32_t ihi,
                                              uint32_t ilo)
 {
-    const double k = floor(__fma_rn(2.0, fabs(n), rh) * inv_r2);
-    const uint32_t as = (uint32_t)min_nonan(k, taud);
-    uint64_t nb;
-    __builtin_memcpy(&nb, &n, sizeof(nb));  // n's bits (a register move)
-    const uint32_t lo = ilo | (uint32_t)(nb >> 63);
+    const uint32_t as = tile_distance(n, rh, inv_r2, taud);
+    const uint32_t lo = ilo | high_word(n) >> 31;
     return (uint64_t)(as << 16 | ihi) << 32 | lo;
 }
 
-// s of a tile_key: |s| with the sign of bit 0.
+// The same in 32 bits, |s| << shift | i << 1 | sign, for scans whose tau and
+// point count leave room (key32_shift).
+__device__ __forceinline__ uint32_t tile_key32(double n, double rh, double inv_r2, double taud, uint32_t shift,
+                                               uint32_t i)
+{
+    const uint32_t as = tile_distance(n, rh, inv_r2, taud);
+    return as << shift | (uint32_t)(((uint64_t)i << 32 | high_word(n)) >> 31);  // i << 1 | sign in one funnel shift
+}
+
+// The shift of 32-bit keys for truncation tau and scans of at most n points,
+// or 0 where they do not fit: 1 + the bits of the largest index, such that the
+// largest key stays below ~0 (no key).
+inline uint32_t key32_shift(int32_t tau, int64_t n)
+{
+    uint32_t bits = 0;
+    while (bits < 32 && ((uint64_t)1 << bits) < (uint64_t)(n > 0 ? n : 1)) ++bits;
+    const uint64_t top = ((uint64_t)(uint32_t)tau << (bits + 1)) | (((uint64_t)1 << (bits + 1)) - 1);
+    return top < 0xffffffffull ? bits + 1 : 0;
+}
+
+// s of a tile key: |s| with the sign of bit 0.
 __device__ __forceinline__ int32_t tile_key_sdf(uint64_t key)
 {
     const int32_t as = (int32_t)(key >> 48);
+    return (key & 1u) ? -as : as;
+}
+__device__ __forceinline__ int32_t tile_key_sdf(uint32_t key, uint32_t shift)
+{
+    const int32_t as = (int32_t)(key >> shift);
     return (key & 1u) ? -as : as;
 }
 
@@ -461,12 +500,42 @@ __device__ __forceinline__ bool walk_enter_box(Walk &W, const int32_t lo[3], con
 // The walk carries the LDS byte address of the voxel's key (a buffer in z
 // fastest layout) instead of its coordinates. Magnitudes: T' < 2^53 (T < 2^52, and a box
 // exit lies at most 64 crossings past the current time).
+//
+// A step adds e times an increment, e = 1 on the axes that cross and 0 on the
+// others, as one fma per value. One register serves all three kinds: the word
+// 0x3f800000 is the high word of the double 2^-7 and the float 1, so times and
+// numerator carry increments scaled by 2^7 (exact), and the address, below
+// 2^23, is kept as the float whose bits are the address (a denormal, whose
+// sums are exact), with no conversion either way.
+constexpr uint32_t kStepOne = 0x3f800000u;
+constexpr double kStepScale = 128.0;
+
+__device__ __forceinline__ float int_bits(int32_t v)
+{
+    float f;
+    __builtin_memcpy(&f, &v, sizeof(f));
+    return f;
+}
+__device__ __forceinline__ int32_t float_bits(float f)
+{
+    int32_t v;
+    __builtin_memcpy(&v, &f, sizeof(v));
+    return v;
+}
+
 struct BoxWalk {
-    double T[3], dT[3];
+    double T[3], dT[3];  // dT, dn: times 2^7
     double lim;
     double n, dn[3];
-    int32_t lv, dlv[3];
+    int32_t lv;          // the bits of a float
+    float dlv[3];
 };
+
+// An address increment of +-d (0 < d < 2^23) as a float in denormal units.
+__device__ __forceinline__ float step_address(bool up, int32_t d)
+{
+    return int_bits(up ? d : (int32_t)(0x80000000u | (uint32_t)d));
+}
 
 // From a voxel walk that walk_enter_box has placed inside [lo, hi); sh[a] is
 // the byte shift of axis a in a key buffer at LDS address base.
@@ -477,22 +546,18 @@ __device__ __forceinline__ void box_walk_from(const Walk &W, const int32_t lo[3]
     V.lv = (int32_t)base;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        V.lv += (W.g[a] - lo[a]) << sh[a];
-        if (W.step[a] == 0) {
-            V.T[a] = INFINITY;
-            V.dT[a] = 0.0;
-            V.dn[a] = 0.0;
-            V.dlv[a] = 0;
-            continue;
-        }
+        const int32_t rel = W.g[a] - lo[a];
         const bool up = W.step[a] > 0;
-        V.T[a] = 2.0 * W.T[a] + (up ? 0.0 : 1.0);
-        V.dT[a] = 2.0 * W.dT[a];
-        V.dn[a] = up ? W.dn[a] : -W.dn[a];
-        V.dlv[a] = up ? (1 << sh[a]) : -(1 << sh[a]);
-        // crossings until the walk leaves the box on this axis (at least one)
-        const int32_t k = up ? hi[a] - W.g[a] : W.g[a] - lo[a] + 1;
-        first_exit = min_nonan(first_exit, V.T[a] + (double)(k - 1) * V.dT[a]);  // never NaN
+        V.lv += rel << sh[a];
+        // (an axis that never crosses has T = inf, and its increments are
+        // never added)
+        V.T[a] = W.step[a] != 0 ? 2.0 * W.T[a] + (up ? 0.0 : 1.0) : INFINITY;
+        V.dT[a] = 2.0 * kStepScale * W.dT[a];
+        V.dn[a] = -kStepScale * fabs(W.dn[a]);  // every step moves along D
+        V.dlv[a] = step_address(up, 1 << sh[a]);
+        // crossings after the next until the walk leaves the box on this axis
+        const int32_t k = up ? hi[a] - 1 - W.g[a] : rel;
+        first_exit = min_nonan(first_exit, __fma_rn((double)k, 2.0 * W.dT[a], V.T[a]));  // never NaN
     }
     V.lim = min_nonan(2.0 * W.lam, first_exit - 1.0);
     V.n = W.n;
@@ -504,70 +569,97 @@ __device__ __forceinline__ void box_walk_from(const Walk &W, const int32_t lo[3]
 // ray as make_ray gives it, with inv_r2 = refined_rcp(2r) as band_key
 // wants) and V, the state that walk_init, walk_advance(c), walk_enter_box
 // and box_walk_from give, with the resumed voxel walk formed directly
-// (crossing times and distance numerator at c crossings) instead of by a
-// walk from S; walk_enter_box only moves it where the tile is clipped by the
-// window's edge. false when no voxel of the walk lies in the box [lo, hi).
+// (crossing times and distance numerator at c crossings, about 120
+// instructions) instead of by a walk from S. The voxel at c crossings must
+// lie in the box of ext voxels at lo: it does in the whole tile that was
+// entered, whose part outside the window the tile pass walks as well.
 // Integer ranges: |q|, |o| < 2^30, so D and the voxel offsets q - c fit
 // int32 (|q - c| stays within a voxel diagonal of the band, below 2^17);
 // the products below are exact in float64 (< 2^52).
+__device__ __forceinline__ void tile_walk_resume(const int32_t q[3], const int32_t off[3], uint32_t r,
+                                                 const int32_t c[3], const int32_t o[3], int32_t tau,
+                                                 const int32_t lo[3], const int32_t ext[3], const int32_t sh[3],
+                                                 uint32_t base, Ray &R, BoxWalk &V)
+{
+    R.r = (double)r;
+    R.r2 = 2.0 * R.r;
+    R.inv_r2 = refined_rcp(R.r2);
+    const bool near = r <= (uint32_t)tau;
+    int32_t L[3];
+    double f[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const int32_t D = q[a] - o[a];
+        R.q[a] = q[a];
+        R.D[a] = (double)D;
+        R.E[a] = q[a] + off[a];
+        R.S[a] = near ? o[a] : q[a] - off[a];
+        L[a] = near ? D + off[a] : 2 * off[a];
+        const int32_t len = L[a] < 0 ? -L[a] : L[a];
+        f[a] = (double)(len > 1 ? len : 1);
+    }
+    const double other[3] = {f[1] * f[2], f[0] * f[2], f[0] * f[1]};
+    double first_exit = INFINITY;
+    V.lv = (int32_t)base;
+    V.n = 0.0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const bool up = L[a] > 0;
+        const int32_t g0 = R.S[a] >> 10;  // arithmetic shift: floor division
+        const int32_t g = up ? g0 + c[a] : g0 - c[a], rel = g - lo[a];
+        // distance from S to the face ahead of the current voxel, c[a] cells
+        // past the first
+        const int32_t x = R.S[a] - 1024 * g;
+        const int32_t num = up ? 1024 - x : x;
+        V.T[a] = L[a] != 0 ? __fma_rn((double)(2 * num), other[a], up ? 0.0 : 1.0) : INFINITY;
+        V.dT[a] = 2048.0 * kStepScale * other[a];
+        V.dn[a] = -1024.0 * kStepScale * fabs(R.D[a]);
+        V.n = __fma_rn((double)(q[a] - 1024 * g - 512), R.D[a], V.n);
+        V.lv += rel << sh[a];
+        V.dlv[a] = step_address(up, 1 << sh[a]);
+        const int32_t k = up ? ext[a] - 1 - rel : rel;
+        first_exit = min_nonan(first_exit, __fma_rn((double)k, 2048.0 * other[a], V.T[a]));
+    }
+    V.lim = min_nonan(2.0 * (f[0] * other[0]), first_exit - 1.0);
+}
+
+// The same for any box [lo, hi), by the general functions where the voxel at
+// c crossings lies outside it; false when no voxel of the walk lies in the box.
 __device__ __forceinline__ bool box_walk_resume(const int32_t q[3], const int32_t off[3], uint32_t r,
                                                 const int32_t c[3], const int32_t o[3], int32_t tau,
                                                 const int32_t lo[3], const int32_t hi[3], const int32_t sh[3],
                                                 uint32_t base, Ray &R, BoxWalk &V)
 {
-    R.r = (double)r;
-    R.r2 = 2.0 * R.r;
-    R.inv_r2 = refined_rcp(R.r2);
-    const bool near = R.r <= (double)tau;
+    const int32_t ext[3] = {hi[0] - lo[0], hi[1] - lo[1], hi[2] - lo[2]};
+    tile_walk_resume(q, off, r, c, o, tau, lo, ext, sh, base, R, V);
     Walk W;
-    double f[3];
+    walk_init(R, W);
+    walk_advance(W, c);
     bool inside = true;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        R.q[a] = q[a];
-        R.D[a] = (double)(q[a] - o[a]);
-        R.E[a] = q[a] + off[a];
-        R.S[a] = near ? o[a] : q[a] - off[a];
-        const int32_t L = R.E[a] - R.S[a];
-        W.step[a] = L > 0 ? 1 : (L < 0 ? -1 : 0);
-        f[a] = L != 0 ? (double)(L < 0 ? -L : L) : 1.0;
-        W.g[a] = (R.S[a] >> 10) + W.step[a] * c[a];  // arithmetic shift: floor division
-        inside = inside && W.g[a] >= lo[a] && W.g[a] < hi[a];
-    }
-    const double other[3] = {f[1] * f[2], f[0] * f[2], f[0] * f[1]};
-    W.lam = f[0] * f[1] * f[2];
-    double n = 0.0;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        n += (double)(q[a] - 1024 * W.g[a] - 512) * R.D[a];
-        // distance from S to the first face ahead, then c[a] whole cells
-        const int32_t g0 = R.S[a] >> 10;
-        const int32_t ahead = W.step[a] > 0 ? 1024 * (g0 + 1) - R.S[a] : R.S[a] - 1024 * g0;
-        W.T[a] = W.step[a] != 0 ? (double)(ahead + 1024 * c[a]) * other[a] : INFINITY;
-        W.dT[a] = 1024.0 * other[a];
-        W.dn[a] = -1024.0 * R.D[a];
-    }
-    W.n = n;
-    if (!inside && !walk_enter_box(W, lo, hi)) return false;
+    for (int a = 0; a < 3; ++a) inside = inside && W.g[a] >= lo[a] && W.g[a] < hi[a];
+    if (inside) return true;
+    if (!walk_enter_box(W, lo, hi)) return false;
     box_walk_from(W, lo, hi, sh, base, V);
     return true;
 }
 
-// Advance to the next voxel of the box; false when the walk leaves the box
+// Advance to the next voxel; false when the walk leaves the box
 // or the segment ends (the state then holds a step past the end, never used:
-// stepping without a branch costs less than testing first).
+// stepping without a branch costs less than testing first). 18 instructions.
 __device__ __forceinline__ bool box_walk_next(BoxWalk &V)
 {
     const double tm = min_nonan(V.T[0], min_nonan(V.T[1], V.T[2]));
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        // x + (0 or 1) dx as one fma: exact (the sums are integers below
-        // 2^53, and an axis that never crosses has dT = dn = 0)
-        const bool e = V.T[a] == tm;
-        const double ef = e ? 1.0 : 0.0;
-        V.T[a] = __fma_rn(ef, V.dT[a], V.T[a]);
-        V.n = __fma_rn(ef, V.dn[a], V.n);
-        V.lv += e ? V.dlv[a] : 0;
+        // exact: the sums are integers below 2^53 (2^23 for the address)
+        const uint32_t one = V.T[a] == tm ? kStepOne : 0u;
+        const uint64_t word = (uint64_t)one << 32;
+        double e;
+        __builtin_memcpy(&e, &word, sizeof(e));
+        V.T[a] = __fma_rn(e, V.dT[a], V.T[a]);
+        V.n = __fma_rn(e, V.dn[a], V.n);
+        V.lv = float_bits(__builtin_fmaf(int_bits((int32_t)one), V.dlv[a], int_bits(V.lv)));
     }
     return tm <= V.lim;
 }

@@ -366,3 +366,27 @@ def test_every_point_is_binned_once(n, bin_block):
     assert same(gm, om, dims)
     gm.close()
     om.close()
+
+
+@pytest.mark.parametrize("tau,n", [(5120, 1 << 18), (5120, (1 << 18) + 1), (8190, 1 << 18), (8191, 1 << 18),
+                                   (32767, 1 << 15), (32767, (1 << 15) + 1), (1, 1), (4095, 4097)])
+def test_key_widths_of_the_tile_pass(tau, n):
+    """On both sides of where the tile pass's keys fit 32 bits (bits of tau,
+    bits of the largest point index, one for the sign; no key may equal the
+    empty one), on a window whose edges cut tiles: one slot per tile and
+    several, ties of |s| among many points of one voxel decided by the index."""
+    from paper_2310_05766_amd.tsdf import integrate_batch
+    dims, origin = (41, 39, 35), (-20, -19, -17)
+    om = oracle.OracleMap(dims, origin, 0.1, tau, 64)
+    gm = gpu_map(dims, origin, 0.1, tau, 64)
+    scans = [(synth.fuzz_scan((93, tau, k), n if k == 0 else 3000, extent_m=2.5, nan_frac=0.02, grid_snap=0.05),
+              synth.fuzz_pose((94, k), 0.3)) for k in range(3)]
+    ost = [om.integrate(x, p) for x, p in scans]
+    assert gm.integrate(*scans[0], stats=True) == ost[0]
+    assert integrate_batch([(gm, x, p) for x, p in scans[1:]], stats=True) == ost[1:]
+    assert same(gm, om, dims)
+    ost = [om.integrate(x, p) for x, p in scans]
+    assert integrate_batch([(gm, x, p) for x, p in scans], stats=True) == ost
+    assert same(gm, om, dims)
+    gm.close()
+    om.close()
