@@ -302,9 +302,10 @@ tsdf_status tsdf_mesh(tsdf_map *m, const int32_t lo[3], const int32_t hi[3], flo
  * 2^9..2^12 voxels per tile; a tile's candidate keys live in 8 bytes of LDS
  * per voxel), handled by tile_workgroups persistent workgroups (0: as many
  * as fit the device). log2_tile = {0, 0, 0}, the initial setting, lets the
- * library choose per call (16 x 16 x 8 tiles for tsdf_integrate_scan,
- * 8 x 8 x 8 for tsdf_integrate_batch, whose tiling is that of its first
- * scan's map); tsdf_map_get_tiling then reports {0, 0, 0}. The arithmetic,
+ * library choose per call (16 x 16 x 8 tiles for tsdf_integrate_scan; for
+ * tsdf_integrate_batch by the most scans of one map, 16 x 16 x 16 down to
+ * 8 x 8 x 8; a batch's tiling is that of its first scan's map);
+ * tsdf_map_get_tiling then reports {0, 0, 0}. The arithmetic,
  * and so every result, is the same for every tiling. */
 tsdf_status tsdf_map_set_tiling(tsdf_map *m, const int32_t log2_tile[3], int32_t tile_workgroups);
 tsdf_status tsdf_map_get_tiling(const tsdf_map *m, int32_t log2_tile[3], int32_t *tile_workgroups);

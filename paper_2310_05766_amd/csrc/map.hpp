@@ -87,24 +87,44 @@ struct Guard {
 
 // Tiles of 2^lt voxels: every lt in [2, 6], the z edge at least 8 (merge
 // runs), 2^9..2^12 voxels per tile (12 bytes of LDS per voxel).
-// Tilings used while a map has none set: scan-by-scan calls do best with
-// few, large tiles (per-tile fixed costs dominate one scan's work); batches
-// with many scans per tile do best with 8^3 tiles.
-inline constexpr int32_t kPlainTiling[3] = {4, 4, 3};
+// Tilings used while a map has none set, by the most scans that one map has in
+// the call. A larger tile has fewer fixed costs per scan, a smaller one holds
+// more scans' keys at once; the tile pass's time, us (tiles of 8x8x8, 16x8x8,
+// 16x16x8, 16x16x16 voxels):
+//   1 scan    32 maps, 16 x 1024 points each     184 148 129 106
+//             4 maps, 64 x 1024                   69  61  59  55
+//             1 map, 128 x 1024                   52  47  44  45
+//             1 map, 16 x 1024                    26  25  24  26
+//   2 scans   1 map, 128 x 1024                   76  69  68  75
+//   4 scans   16 maps, uneven                    665 605 567 608
+//             4 maps, 64 x 1024                  128 120 129 145
+//   8 scans   1 map, 128 x 1024                  147 145 158 191
+//             16 maps, 32 x 1024                 466 430 416 473
+//   16 scans  4 maps, 64 x 1024                  259 262 293 378
+//   50 scans  1 map, 128 x 1024                  502 517 583 817
+// (whole calls). One scan per map of more than kManyPoints points together
+// takes the largest tiles: the busy tiles are then many more than workgroups.
+inline constexpr int32_t kScanTiling[3] = {4, 4, 3};
+inline constexpr int32_t kManyScansTiling[3] = {4, 4, 4};
+inline constexpr int32_t kFewSeqTiling[3] = {4, 3, 3};
 inline constexpr int32_t kBatchTiling[3] = {3, 3, 3};
+inline constexpr int64_t kManyPoints = 131072;
+inline constexpr int32_t kFewSeq = 8;
 
-inline const int32_t *tiling_for(const tsdf_map *m, bool batch)
+// seq: the most scans of one map in the call; points: of all its scans.
+inline const int32_t *tiling_for(const tsdf_map *m, int32_t seq, int64_t points)
 {
     if (m->lt[0] != 0) return m->lt;
-    return batch ? kBatchTiling : kPlainTiling;
+    if (seq <= 1) return points > kManyPoints ? kManyScansTiling : kScanTiling;
+    return seq <= kFewSeq ? kFewSeqTiling : kBatchTiling;
 }
 
 // The launch shape of an integration on this map (a batch takes its first
 // scan's map's).
-inline LaunchShape launch_shape(const tsdf_map *m, bool batch)
+inline LaunchShape launch_shape(const tsdf_map *m, int32_t seq, int64_t points)
 {
     LaunchShape sh;
-    const int32_t *lt = tiling_for(m, batch);
+    const int32_t *lt = tiling_for(m, seq, points);
     for (int a = 0; a < 3; ++a) sh.lt[a] = lt[a];
     sh.tile_grid = m->tile_grid;
     sh.bin_block = m->bin_block > 0 ? m->bin_block : kBinBlock;

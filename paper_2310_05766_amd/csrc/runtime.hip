@@ -1023,7 +1023,8 @@ tsdf_status tsdf_integrate_scan(tsdf_map *m, const float *xyz, int64_t n_points,
     if (keyvol_path(m)) return integrate_interp(m, xyz, n_points, kind == TSDF_PTR_HOST, pose, stats);
     std::vector<MapRef> maps{map_ref(m)};
     std::vector<ScanRef> scans{ScanRef{0, xyz, n_points, kind == TSDF_PTR_HOST, pose}};
-    tsdf_status st = m->engine->run(maps, scans, launch_shape(m, false), stats);
+    // (one tiling for scans of any size, as the allocation-free call has it)
+    tsdf_status st = m->engine->run(maps, scans, launch_shape(m, 1, 0), stats);
     if (st == TSDF_EDEVICE) m->poisoned = true;
     return st;
 }
@@ -1081,6 +1082,9 @@ tsdf_status tsdf_integrate_batch(const tsdf_scan_desc *scans, int32_t count, tsd
     std::vector<ScanRef> refs;
     std::unordered_map<const tsdf_map *, int32_t> idx;
     std::vector<std::unique_ptr<Guard>> guards;
+    std::vector<int32_t> per_map;
+    int32_t seq = 0;
+    int64_t points = 0;
     for (int32_t k = 0; k < count; ++k) {
         tsdf_map *m = scans[k].map;
         if (!m) return TSDF_EINVAL;
@@ -1091,7 +1095,10 @@ tsdf_status tsdf_integrate_batch(const tsdf_scan_desc *scans, int32_t count, tsd
             if (m->poisoned) return TSDF_EDEVICE;
             it = idx.emplace(m, (int32_t)maps.size()).first;
             maps.push_back(map_ref(m));
+            per_map.push_back(0);
         }
+        seq = std::max(seq, ++per_map[(size_t)it->second]);
+        points += std::max<int64_t>(scans[k].n_points, 0);
         refs.push_back(ScanRef{it->second, scans[k].xyz, scans[k].n_points, kind == TSDF_PTR_HOST, scans[k].pose});
     }
     hipStream_t s = hip_stream ? (hipStream_t)hip_stream : maps[0].stream;
@@ -1108,7 +1115,7 @@ tsdf_status tsdf_integrate_batch(const tsdf_scan_desc *scans, int32_t count, tsd
         eng = slot.get();
     }
     const tsdf_map *first = scans[0].map;
-    tsdf_status st = eng->run(maps, refs, launch_shape(first, true), stats);
+    tsdf_status st = eng->run(maps, refs, launch_shape(first, seq, points), stats);
     if (st == TSDF_EDEVICE)
         for (int32_t k = 0; k < count; ++k) scans[k].map->poisoned = true;
     return st;

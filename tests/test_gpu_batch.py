@@ -390,3 +390,24 @@ def test_key_widths_of_the_tile_pass(tau, n):
     assert same(gm, om, dims)
     gm.close()
     om.close()
+
+
+@pytest.mark.parametrize("maps,per_map,n", [(3, 1, 43690), (3, 1, 43691), (2, 2, 5000), (2, 8, 3000), (2, 9, 3000)])
+def test_automatic_tilings(maps, per_map, n):
+    """A batch's tiling follows from the most scans of one map and, for one
+    scan each, from the points of all (more than 131,072): on both sides of
+    each line, counts and maps are the oracle's."""
+    from paper_2310_05766_amd.tsdf import integrate_batch
+    dims, origin = (50, 46, 37), (-25, -23, -18)
+    gms = [gpu_map(dims, origin, 0.1, 4000, 64) for _ in range(maps)]
+    oms = [oracle.OracleMap(dims, origin, 0.1, 4000, 64) for _ in range(maps)]
+    items, ost = [], []
+    for k in range(maps * per_map):
+        x, p = synth.fuzz_scan((95, n, k), n, extent_m=2.5, nan_frac=0.02), synth.fuzz_pose((96, k), 0.3)
+        items.append((gms[k % maps], x, p))
+        ost.append(oms[k % maps].integrate(x, p))
+    assert integrate_batch(items, stats=True) == ost
+    for g, o in zip(gms, oms):
+        assert same(g, o, dims)
+        g.close()
+        o.close()
