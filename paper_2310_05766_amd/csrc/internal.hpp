@@ -262,11 +262,19 @@ struct BoxXfer {
     int64_t off;
 };
 // Slot of a global voxel: floor_mod(g, dims) per axis.
-// pack: stage <- window (and, with clear, the window voxels are reset to 0);
+// pack: stage <- window, whose voxels are reset to 0;
 // unpack: window <- stage, or <- 0 when stage_sdf is null.
 hipError_t launch_pack_boxes(const BoxXfer *boxes_dev, int32_t nboxes, int64_t max_box_vox, int16_t *sdf,
-                             int16_t *w, const int32_t dims[3], int16_t *stage_sdf, int16_t *stage_w, bool clear,
-                             hipStream_t stream);
+                             int16_t *w, const int32_t dims[3], int16_t *stage_sdf, int16_t *stage_w, hipStream_t stream);
+// Lines [line0, line0 + lines) of a box of the window, line = x * ny + y, nz
+// voxels each: out gets their sdf values, then their weights, both dense.
+struct LinesXfer {
+    const int16_t *sdf, *w;
+    int32_t dims[3];  // the window
+    int32_t s0[3];    // slot of the box's first voxel per axis
+    uint32_t ny, nz;  // the box
+};
+hipError_t launch_pack_lines(const LinesXfer &A, uint32_t line0, uint32_t lines, int16_t *out, hipStream_t stream);
 // Whole chunks of a window whose dims are multiples of 64 (chunks_dev[j].lo:
 // the chunk's global origin), staged chunk by chunk in the store's layout
 // (stage + j * 2 * kChunkVox: sdf, then w). pack clears the window voxels and

@@ -439,14 +439,14 @@ tsdf_status for_batches(tsdf_map *m, const std::vector<Box> &pieces, Fn fn)
     return TSDF_OK;
 }
 
-// Device -> host: pieces of the window into host arrays via staging.
-tsdf_status stage_out(tsdf_map *m, int32_t nb, int64_t total, int64_t maxv, bool clear)
+// Device -> host staging: pieces that leave the window.
+tsdf_status stage_out(tsdf_map *m, int32_t nb, int64_t total, int64_t maxv)
 {
     int16_t *dsdf = m->stage_dev, *dw = m->stage_dev + m->stage_cap;
     HIPCHK(m, hipMemcpyAsync(m->boxes_dev, m->boxes_host, (size_t)nb * sizeof(BoxXfer), hipMemcpyHostToDevice,
                              m->stream));
     HIPCHK(m, prof_start(m, TSDF_KERNEL_PACK));
-    HIPCHK(m, launch_pack_boxes(m->boxes_dev, nb, maxv, m->sdf, m->w, m->d.dims, dsdf, dw, clear, m->stream));
+    HIPCHK(m, launch_pack_boxes(m->boxes_dev, nb, maxv, m->sdf, m->w, m->d.dims, dsdf, dw, m->stream));
     HIPCHK(m, prof_stop(m, TSDF_KERNEL_PACK));
     HIPCHK(m, hipMemcpyAsync(m->stage_host, dsdf, (size_t)total * sizeof(int16_t), hipMemcpyDeviceToHost,
                              m->stream));
@@ -454,6 +454,37 @@ tsdf_status stage_out(tsdf_map *m, int32_t nb, int64_t total, int64_t maxv, bool
                              hipMemcpyDeviceToHost, m->stream));
     HIPCHK(m, hipStreamSynchronize(m->stream));
     return TSDF_OK;
+}
+
+// A result that leaves through a ring of pinned slots (the map's staging):
+// start(k) enqueues whatever brings part k into slot k % kSlots and records
+// copied[k % kSlots] behind it; once that is seen, seen(k) may enqueue more
+// and bind(k, job) describes the host copies of the part, which the crew's
+// threads share. kAhead parts are on their way at any time, and part k +
+// kAhead takes the slot of part k + kAhead - kSlots, so that copies of the
+// link, page faults and copies of the host all overlap.
+constexpr int kSlots = 8, kAhead = 4;
+
+uint64_t slot_bytes(const tsdf_map *m) { return (uint64_t)m->stage_cap * 4 / kSlots / 16 * 16; }  // a staged voxel: 4 bytes
+
+template <class Start, class Seen, class Bind>
+hipError_t through_slots(size_t parts, Crew &crew, const hipEvent_t copied[kSlots], Start start, Seen seen, Bind bind)
+{
+    Crew::Job job[kSlots];
+    hipError_t e = hipSuccess;
+    for (size_t k = 0; e == hipSuccess && k < kAhead && k < parts; ++k) e = start(k);
+    for (size_t k = 0; e == hipSuccess && k < parts; ++k) {
+        const int s = (int)(k % kSlots);
+        if ((e = hipEventSynchronize(copied[s])) != hipSuccess || (e = seen(k)) != hipSuccess) break;
+        bind(k, &job[s]);
+        crew.post(&job[s]);
+        if (k + kAhead < parts) {
+            crew.wait(&job[(k + kAhead) % kSlots]);
+            e = start(k + kAhead);
+        }
+    }
+    for (Crew::Job &j : job) crew.wait(&j);
+    return e;
 }
 
 bool all_zero(const int16_t *a, const int16_t *b, int64_t n)
@@ -858,17 +889,15 @@ tsdf_status tsdf_mesh(tsdf_map *m, const int32_t lo[3], const int32_t hi[3], flo
     if ((uint64_t)max_tris < total) return TSDF_ERANGE;
     // The triangles are emitted in pieces of kPieceSlots slots of staging (one
     // launch of a piece's size keeps the chip busy where a few rows hold a
-    // whole wall) into two device buffers in turn, and leave through a ring of
-    // kSlots pinned slots: while one slot's copy runs on the copy stream,
-    // earlier ones are copied to tris by several host threads.
-    constexpr int kSlots = 8, kAhead = 4, kPieceSlots = 16;
+    // whole wall) into two device buffers in turn, and leave through the pinned
+    // slots on the copy stream.
+    constexpr size_t kPieceSlots = 16;
     constexpr uint64_t kTri = 9 * sizeof(float);
-    tsdf_status st = ensure_stage(m, std::max<int64_t>({m->stage_cap, 16 * kChunkVox, (int64_t)(most * kTri * kSlots / 4 + 4)}), 0);
+    tsdf_status st =
+        ensure_stage(m, std::max<int64_t>({m->stage_cap, 16 * kChunkVox, (int64_t)(most * kTri + 16) * kSlots / 4}), 0);
     if (st == TSDF_OK) st = ensure_copy_stream(m);
     if (st != TSDF_OK) return st;
-    // (a staged voxel is 4 bytes)
-    const uint64_t slot_bytes = (uint64_t)m->stage_cap * 4 / kSlots / 4 * 4, slot_tris = slot_bytes / kTri;
-    const uint64_t piece_bytes = kPieceSlots * slot_bytes;
+    const uint64_t slot = slot_bytes(m), slot_tris = slot / kTri, piece_bytes = kPieceSlots * slot;
     struct Part {
         uint32_t u0, u1;
     };
@@ -909,7 +938,7 @@ tsdf_status tsdf_mesh(tsdf_map *m, const int32_t lo[3], const int32_t hi[3], flo
         if (k == k0) e = hipStreamWaitEvent(m->copy_stream, emitted[q & 1], 0);
         const uint64_t n = base[parts[k].u1] - base[parts[k].u0];
         if (e == hipSuccess && n)
-            e = hipMemcpyAsync((char *)m->stage_host + s * slot_bytes,
+            e = hipMemcpyAsync((char *)m->stage_host + s * slot,
                                (char *)m->mesh_tris + (q & 1) * piece_bytes + (base[parts[k].u0] - base[parts[k0].u0]) * kTri,
                                n * kTri, hipMemcpyDeviceToHost, m->copy_stream);
         return e == hipSuccess ? hipEventRecord(copied[s], m->copy_stream) : e;
@@ -920,41 +949,32 @@ tsdf_status tsdf_mesh(tsdf_map *m, const int32_t lo[3], const int32_t hi[3], flo
     for (hipEvent_t ev : copied)
         if (!ev) e = hipErrorOutOfMemory;
     for (size_t q = 0; q < 2 && e == hipSuccess; ++q) e = emit(q);
-    struct Copy {
-        char *dst;
-        const char *src;
-        PageParts pages;
-    } copy[kSlots];
-    Crew::Job job[kSlots];
-    {
+    if (e == hipSuccess) {
+        struct Copy {
+            char *dst;
+            const char *src;
+            PageParts pages;
+        } copy[kSlots];
         Crew crew(total * kTri >= kCrewBytes ? kCrewHelpers : 0);
-        // kAhead copies are under way at any time; part k + kAhead takes the
-        // slot of part k + kAhead - kSlots
-        for (size_t k = 0; e == hipSuccess && k < kAhead && k < parts.size(); ++k) e = start(k);
-        for (size_t k = 0; e == hipSuccess && k < parts.size(); ++k) {
-            const int s = (int)(k % kSlots);
-            const uint64_t n = (base[parts[k].u1] - base[parts[k].u0]) * kTri;
-            if ((e = hipEventSynchronize(copied[s])) != hipSuccess) break;
-            // the last copy out of a piece's buffer is done: the piece after
-            // the next goes there
-            if ((k + 1) % kPieceSlots == 0 && (e = emit(k / kPieceSlots + 2)) != hipSuccess) break;
-            copy[s].dst = (char *)tris + base[parts[k].u0] * kTri;
-            copy[s].src = (const char *)m->stage_host + s * slot_bytes;
-            copy[s].pages = PageParts(copy[s].dst, n);
-            job[s].call = [](void *c, int64_t p) {
-                const Copy &C = *(const Copy *)c;
-                const uint64_t at = C.pages.first(p);
-                memcpy(C.dst + at, C.src + at, C.pages.size(p));
-            };
-            job[s].arg = &copy[s];
-            job[s].parts = copy[s].pages.count();
-            crew.post(&job[s]);
-            if (k + kAhead < parts.size()) {
-                crew.wait(&job[(k + kAhead) % kSlots]);
-                e = start(k + kAhead);
-            }
-        }
-        for (int s = 0; s < kSlots; ++s) crew.wait(&job[s]);
+        e = through_slots(
+            parts.size(), crew, copied, start,
+            [&](size_t k) -> hipError_t {
+                // the last copy out of a piece's buffer is done: the piece
+                // after the next goes there
+                return (k + 1) % kPieceSlots == 0 ? emit(k / kPieceSlots + 2) : hipSuccess;
+            },
+            [&](size_t k, Crew::Job *job) {
+                Copy &C = copy[k % kSlots];
+                C.dst = (char *)tris + base[parts[k].u0] * kTri;
+                C.src = (const char *)m->stage_host + (k % kSlots) * slot;
+                C.pages = PageParts(C.dst, (base[parts[k].u1] - base[parts[k].u0]) * kTri);
+                job->call = [](void *c, int64_t p) {
+                    const Copy &C = *(const Copy *)c;
+                    memcpy(C.dst + C.pages.first(p), C.src + C.pages.first(p), C.pages.size(p));
+                };
+                job->arg = &C;
+                job->parts = C.pages.count();
+            });
     }
     if (e != hipSuccess) {
         (void)hipStreamSynchronize(m->stream);
@@ -1220,7 +1240,7 @@ tsdf_status tsdf_shift(tsdf_map *m, const int32_t new_origin[3])
 
     // 2. other leaving pieces: pack (and clear) -> host staging -> store
     st = for_batches(m, lpart, [&](const std::vector<Box> &batch, int32_t nb, int64_t total, int64_t maxv) {
-        tsdf_status s = stage_out(m, nb, total, maxv, true);
+        tsdf_status s = stage_out(m, nb, total, maxv);
         if (s != TSDF_OK) return s;
         const int16_t *hs = m->stage_host, *hw = m->stage_host + m->stage_cap;
         for (int32_t k = 0; k < nb; ++k) {
@@ -1333,47 +1353,175 @@ tsdf_status tsdf_readback(tsdf_map *m, const int32_t lo[3], const int32_t hi[3],
     }
     if (req.empty()) return TSDF_OK;
     const int64_t ny = hi[1] - lo[1], nz = hi[2] - lo[2];
-    // stored or unseen voxels first
-    std::vector<Box> pieces;
-    chunk_pieces(req, pieces);
-    for (const Box &b : pieces) {
-        auto it = m->store.find(key_of(b.lo));
-        for (int32_t x = b.lo[0]; x < b.hi[0]; ++x)
-            for (int32_t y = b.lo[1]; y < b.hi[1]; ++y) {
-                const int64_t dst = ((int64_t)(x - lo[0]) * ny + (y - lo[1])) * nz + (b.lo[2] - lo[2]);
-                const size_t nb = (size_t)(b.hi[2] - b.lo[2]) * sizeof(int16_t);
-                if (it == m->store.end()) {
-                    memset(sdf_out + dst, 0, nb);
-                    memset(w_out + dst, 0, nb);
-                } else {
-                    const int64_t src = chunk_off(x, y, b.lo[2]);
-                    memcpy(sdf_out + dst, it->second.sdf() + src, nb);
-                    memcpy(w_out + dst, it->second.w() + src, nb);
-                }
-            }
-    }
-    // then the resident part, from the device
+    int16_t *const out[2] = {sdf_out, w_out};
     const Box res = intersect(req, window_box(m->d.origin, m->d.dims));
-    std::vector<Box> rp;
-    chunk_pieces(res, rp);
-    return for_batches(m, rp, [&](const std::vector<Box> &batch, int32_t nb, int64_t total, int64_t maxv) {
-        tsdf_status s = stage_out(m, nb, total, maxv, false);
-        if (s != TSDF_OK) return s;
-        const int16_t *hs = m->stage_host, *hw = m->stage_host + m->stage_cap;
-        for (int32_t k = 0; k < nb; ++k) {
-            const Box &b = batch[k];
-            const int64_t off = m->boxes_host[k].off;
-            const int32_t ey = b.hi[1] - b.lo[1], ez = b.hi[2] - b.lo[2];
-            for (int32_t x = b.lo[0]; x < b.hi[0]; ++x)
-                for (int32_t y = b.lo[1]; y < b.hi[1]; ++y) {
-                    const int64_t src = off + ((int64_t)(x - b.lo[0]) * ey + (y - b.lo[1])) * ez;
-                    const int64_t dst = ((int64_t)(x - lo[0]) * ny + (y - lo[1])) * nz + (b.lo[2] - lo[2]);
-                    memcpy(sdf_out + dst, hs + src, (size_t)ez * sizeof(int16_t));
-                    memcpy(w_out + dst, hw + src, (size_t)ez * sizeof(int16_t));
+
+    // Voxels that are not resident: from the store's chunks, else zero. The
+    // chunks of the box first, then planes of x shared out among the threads.
+    int32_t c0[3], cn[3];
+    for (int a = 0; a < 3; ++a) {
+        c0[a] = (int32_t)floor_div64(lo[a], kChunk);
+        cn[a] = (int32_t)floor_div64((int64_t)hi[a] - 1, kChunk) - c0[a] + 1;
+    }
+    std::vector<const Chunk *> chunks((size_t)cn[0] * cn[1] * cn[2], nullptr);
+    if (!m->store.empty())
+        for (int32_t x = 0; x < cn[0]; ++x)
+            for (int32_t y = 0; y < cn[1]; ++y)
+                for (int32_t z = 0; z < cn[2]; ++z) {
+                    auto it = m->store.find(ChunkKey{c0[0] + x, c0[1] + y, c0[2] + z});
+                    if (it != m->store.end()) chunks[((size_t)x * cn[1] + y) * cn[2] + z] = &it->second;
                 }
+    auto fill_span = [&](int which, int32_t x, int32_t y, int32_t z0, int32_t z1) {
+        int16_t *line = out[which] + ((int64_t)(x - lo[0]) * ny + (y - lo[1])) * nz;
+        const Chunk *const *row = chunks.data() + ((floor_div64(x, kChunk) - c0[0]) * cn[1] + (floor_div64(y, kChunk) - c0[1])) * cn[2];
+        for (int32_t z = z0; z < z1;) {
+            const int64_t cz = floor_div64(z, kChunk);
+            const int32_t end = (int32_t)std::min<int64_t>(z1, (cz + 1) * kChunk);
+            const Chunk *c = row[cz - c0[2]];
+            if (!c) {
+                memset(line + (z - lo[2]), 0, (size_t)(end - z) * sizeof(int16_t));
+            } else {
+                const int16_t *src = (which ? c->w() : c->sdf()) + chunk_off(x, y, z);
+                if (end - z == kChunk) memcpy(line + (z - lo[2]), src, kChunk * sizeof(int16_t));
+                else memcpy(line + (z - lo[2]), src, (size_t)(end - z) * sizeof(int16_t));
+            }
+            z = end;
         }
-        return TSDF_OK;
-    });
+    };
+    auto fill_plane = [&](int which, int32_t x) {
+        const bool cut = !res.empty() && x >= res.lo[0] && x < res.hi[0];
+        bool any = false;  // a stored chunk in this plane
+        const Chunk *const *plane = chunks.data() + (floor_div64(x, kChunk) - c0[0]) * cn[1] * cn[2];
+        for (int32_t k = 0; k < cn[1] * cn[2]; ++k) any = any || plane[k];
+        if (!cut && !any) {
+            memset(out[which] + (int64_t)(x - lo[0]) * ny * nz, 0, (size_t)(ny * nz) * sizeof(int16_t));
+            return;
+        }
+        for (int32_t y = lo[1]; y < hi[1]; ++y) {
+            if (cut && y >= res.lo[1] && y < res.hi[1]) {
+                fill_span(which, x, y, lo[2], res.lo[2]);
+                fill_span(which, x, y, res.hi[2], hi[2]);
+            } else {
+                fill_span(which, x, y, lo[2], hi[2]);
+            }
+        }
+    };
+    // planes that hold something else than resident voxels, in parts of about
+    // one 2 MiB page of one array
+    std::vector<int32_t> planes;
+    const bool whole = !res.empty() && res.lo[1] == lo[1] && res.hi[1] == hi[1] && res.lo[2] == lo[2] && res.hi[2] == hi[2];
+    for (int32_t x = lo[0]; x < hi[0]; ++x)
+        if (!(whole && x >= res.lo[0] && x < res.hi[0])) planes.push_back(x);
+    const int64_t per = std::max<int64_t>(1, (int64_t)PageParts::kPage / (ny * nz * (int64_t)sizeof(int16_t)));
+    const int64_t groups = ((int64_t)planes.size() + per - 1) / per;
+    auto fill_part = [&](int64_t p) {
+        const int64_t g = p / 2;
+        for (int64_t k = g * per; k < std::min<int64_t>((int64_t)planes.size(), (g + 1) * per); ++k)
+            fill_plane((int)(p & 1), planes[(size_t)k]);
+    };
+    Crew::Job fill;
+    fill.call = [](void *f, int64_t p) { (*(decltype(fill_part) *)f)(p); };
+    fill.arg = &fill_part;
+    fill.parts = 2 * groups;
+
+    // The resident part: lines of z, packed densely on the device a slot at a
+    // time; the box's first array, then its second.
+    const int64_t rn[3] = {res.empty() ? 0 : res.hi[0] - res.lo[0], res.hi[1] - res.lo[1], res.hi[2] - res.lo[2]};
+    const int64_t lines = res.empty() ? 0 : rn[0] * rn[1];
+    tsdf_status st = TSDF_OK;
+    int64_t per_slot = 1;
+    if (lines > 0) {
+        // (a slot holds a line at least)
+        st = ensure_stage(m, std::max<int64_t>({m->stage_cap, 16 * kChunkVox, (rn[2] + 8) * kSlots}), 0);
+        if (st != TSDF_OK) return st;
+        per_slot = (int64_t)(slot_bytes(m) / ((uint64_t)rn[2] * 4));
+    }
+    const uint64_t slot = lines > 0 ? slot_bytes(m) : 0;
+    LinesXfer A;
+    A.sdf = m->sdf;
+    A.w = m->w;
+    for (int a = 0; a < 3; ++a) {
+        A.dims[a] = m->d.dims[a];
+        A.s0[a] = (int32_t)floor_mod64(res.lo[a], m->d.dims[a]);
+    }
+    A.ny = (uint32_t)std::max<int64_t>(rn[1], 1);
+    A.nz = (uint32_t)std::max<int64_t>(rn[2], 1);
+    hipEvent_t copied[kSlots];
+    for (hipEvent_t &ev : copied) ev = take_event(m);
+    hipError_t e = hipSuccess;
+    for (hipEvent_t ev : copied)
+        if (!ev) e = hipErrorOutOfMemory;
+    struct Copy {
+        const int16_t *src;        // the part's first array, then its second
+        int64_t l0, n;             // its lines
+        PageParts pages[2];        // where a part's lines are one stretch of the result
+    } copy[kSlots];
+    auto dst_of = [&](int which, int64_t l) {
+        const int64_t x = res.lo[0] + l / rn[1] - lo[0], y = res.lo[1] + l % rn[1] - lo[1];
+        return out[which] + (x * ny + y) * nz + (res.lo[2] - lo[2]);
+    };
+    auto copy_part = [&](const Copy &C, int64_t p) {
+        if (whole) {
+            const int which = p < C.pages[0].count() ? 0 : 1;
+            const int64_t q = which ? p - C.pages[0].count() : p;
+            memcpy((char *)dst_of(which, C.l0) + C.pages[which].first(q),
+                   (const char *)(C.src + (which ? C.n * rn[2] : 0)) + C.pages[which].first(q), C.pages[which].size(q));
+            return;
+        }
+        // a part per 512 lines of an array
+        const int64_t a0 = p / 2 * 512, a1 = std::min<int64_t>(C.n, a0 + 512);
+        const int which = (int)(p & 1);
+        for (int64_t l = a0; l < a1; ++l)
+            memcpy(dst_of(which, C.l0 + l), C.src + (which ? C.n * rn[2] : 0) + l * rn[2], (size_t)rn[2] * sizeof(int16_t));
+    };
+    struct Bound {
+        decltype(copy_part) *fn;
+        const Copy *c;
+    } bound[kSlots];
+    const size_t parts = (size_t)((lines + per_slot - 1) / per_slot);
+    if (e == hipSuccess) {
+        Crew crew(req.count() * 4 >= (int64_t)kCrewBytes ? kCrewHelpers : 0);
+        e = through_slots(
+            parts, crew, copied,
+            [&](size_t k) -> hipError_t {
+                const int s = (int)(k % kSlots);
+                const int64_t l0 = (int64_t)k * per_slot, n = std::min<int64_t>(per_slot, lines - l0);
+                int16_t *dev = (int16_t *)((char *)m->stage_dev + s * slot);
+                hipError_t e = prof_start(m, TSDF_KERNEL_PACK);
+                if (e == hipSuccess) e = launch_pack_lines(A, (uint32_t)l0, (uint32_t)n, dev, m->stream);
+                if (e == hipSuccess) e = prof_stop(m, TSDF_KERNEL_PACK);
+                if (e == hipSuccess)
+                    e = hipMemcpyAsync((char *)m->stage_host + s * slot, dev, (size_t)(n * rn[2]) * 4,
+                                       hipMemcpyDeviceToHost, m->stream);
+                return e == hipSuccess ? hipEventRecord(copied[s], m->stream) : e;
+            },
+            [&](size_t k) -> hipError_t {
+                if (k == 0) crew.post(&fill);  // (behind the first part: the link is busy by now)
+                return hipSuccess;
+            },
+            [&](size_t k, Crew::Job *job) {
+                Copy &C = copy[k % kSlots];
+                C.src = (const int16_t *)((const char *)m->stage_host + (k % kSlots) * slot);
+                C.l0 = (int64_t)k * per_slot;
+                C.n = std::min<int64_t>(per_slot, lines - C.l0);
+                if (whole) {
+                    for (int w = 0; w < 2; ++w)
+                        C.pages[w] = PageParts(dst_of(w, C.l0), (uint64_t)(C.n * rn[2]) * sizeof(int16_t));
+                    job->parts = C.pages[0].count() + C.pages[1].count();
+                } else {
+                    job->parts = (C.n + 511) / 512 * 2;
+                }
+                bound[k % kSlots] = Bound{&copy_part, &C};
+                job->call = [](void *b, int64_t p) { (*((Bound *)b)->fn)(*((Bound *)b)->c, p); };
+                job->arg = &bound[k % kSlots];
+            });
+        if (parts == 0) crew.post(&fill);
+        crew.wait(&fill);
+    }
+    if (e != hipSuccess) (void)hipStreamSynchronize(m->stream);
+    for (hipEvent_t ev : copied)
+        if (ev) m->ev_pool.push_back(ev);
+    return e == hipSuccess ? TSDF_OK : fail_device(m);
 }
 
 tsdf_status tsdf_batch_profile(void *hip_stream, int32_t on)

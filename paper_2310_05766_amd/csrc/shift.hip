@@ -24,8 +24,7 @@ __device__ __forceinline__ int32_t fmod_pos(int32_t a, int32_t n)
 
 __global__ __launch_bounds__(kBlock) void k_pack(const BoxXfer *__restrict__ boxes, int16_t *__restrict__ sdf,
                                                  int16_t *__restrict__ w, int32_t nx, int32_t ny, int32_t nz,
-                                                 int16_t *__restrict__ stage_sdf, int16_t *__restrict__ stage_w,
-                                                 int clear)
+                                                 int16_t *__restrict__ stage_sdf, int16_t *__restrict__ stage_w)
 {
     const BoxXfer b = boxes[blockIdx.y];
     const int64_t total = (int64_t)b.ext[0] * b.ext[1] * b.ext[2];
@@ -38,10 +37,8 @@ __global__ __launch_bounds__(kBlock) void k_pack(const BoxXfer *__restrict__ box
                              fmod_pos(b.lo[2] + z, nz);
         stage_sdf[b.off + j] = sdf[slot];
         stage_w[b.off + j] = w[slot];
-        if (clear) {
-            sdf[slot] = 0;
-            w[slot] = 0;
-        }
+        sdf[slot] = 0;
+        w[slot] = 0;
     }
 }
 
@@ -119,6 +116,22 @@ __global__ __launch_bounds__(kBlock) void k_unpack_chunks(const BoxXfer *__restr
     }
 }
 
+// A thread per voxel (neighbouring lanes along z, across the ends of lines):
+// the copy to the host takes several times as long.
+__global__ __launch_bounds__(kBlock) void k_pack_lines(LinesXfer A, uint32_t line0, uint32_t count, int16_t *out)
+{
+    const uint32_t j = blockIdx.x * kBlock + threadIdx.x;
+    if (j >= count) return;
+    const uint32_t l = line0 + j / A.nz, z = j % A.nz;
+    int32_t sx = A.s0[0] + (int32_t)(l / A.ny), sy = A.s0[1] + (int32_t)(l % A.ny), sz = A.s0[2] + (int32_t)z;
+    sx -= sx >= A.dims[0] ? A.dims[0] : 0;
+    sy -= sy >= A.dims[1] ? A.dims[1] : 0;
+    sz -= sz >= A.dims[2] ? A.dims[2] : 0;
+    const uint32_t slot = ((uint32_t)sx * (uint32_t)A.dims[1] + (uint32_t)sy) * (uint32_t)A.dims[2] + (uint32_t)sz;
+    out[j] = A.sdf[slot];
+    out[(size_t)count + j] = A.w[slot];
+}
+
 uint32_t grid_x(int64_t max_box_vox)
 {
     int64_t blocks = (max_box_vox + kBlock - 1) / kBlock;
@@ -130,12 +143,19 @@ uint32_t grid_x(int64_t max_box_vox)
 }  // namespace
 
 hipError_t launch_pack_boxes(const BoxXfer *boxes_dev, int32_t nboxes, int64_t max_box_vox, int16_t *sdf,
-                             int16_t *w, const int32_t dims[3], int16_t *stage_sdf, int16_t *stage_w, bool clear,
-                             hipStream_t stream)
+                             int16_t *w, const int32_t dims[3], int16_t *stage_sdf, int16_t *stage_w, hipStream_t stream)
 {
     if (nboxes <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_pack, dim3(grid_x(max_box_vox), (uint32_t)nboxes), dim3(kBlock), 0, stream, boxes_dev, sdf,
-                       w, dims[0], dims[1], dims[2], stage_sdf, stage_w, clear ? 1 : 0);
+                       w, dims[0], dims[1], dims[2], stage_sdf, stage_w);
+    return hipGetLastError();
+}
+
+hipError_t launch_pack_lines(const LinesXfer &A, uint32_t line0, uint32_t lines, int16_t *out, hipStream_t stream)
+{
+    const uint32_t count = lines * A.nz;  // a slot of staging: below 2^31
+    if (count == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_pack_lines, dim3((count + kBlock - 1) / kBlock), dim3(kBlock), 0, stream, A, line0, count, out);
     return hipGetLastError();
 }
 

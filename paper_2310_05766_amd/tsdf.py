@@ -240,8 +240,9 @@ class TsdfMap:
         lo_ = (C.c_int32 * 3)(*[int(v) for v in lo])
         hi_ = (C.c_int32 * 3)(*[int(v) for v in hi])
         shape = tuple(int(h) - int(l) for l, h in zip(lo, hi))
-        sdf = np.zeros(shape, dtype=np.int16)
-        w = np.zeros(shape, dtype=np.int16)
+        # (written whole; huge pages for large boxes)
+        sdf = np.empty(shape, dtype=np.int16)
+        w = np.empty(shape, dtype=np.int16)
         check(_abi.lib().tsdf_readback(self._h, lo_, hi_, sdf.ctypes.data_as(C.POINTER(C.c_int16)),
                                        w.ctypes.data_as(C.POINTER(C.c_int16))), "tsdf_readback")
         return sdf, w

@@ -1,0 +1,70 @@
+"""Readback of boxes that lie in the window, in the chunk store, in neither,
+and across them: the resident part leaves through staging slots, the rest is
+filled by host threads. Equal to the oracle's readback voxel by voxel."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+DIMS, ORIGIN, MOVED = (210, 190, 122), (-100, -90, -60), (-100 + 77, -90 - 35, -60 + 9)
+
+
+@pytest.fixture(scope="module")
+def pair():
+    """A GPU map on caller-owned arrays and an oracle map, the same random
+    voxels in both, then a shift by no multiple of a chunk."""
+    import torch
+    from paper_2310_05766_amd.tsdf import TsdfMap
+    g = np.random.Generator(np.random.PCG64(8))
+    w = (g.random(DIMS) < 0.6).astype(np.int16) * g.integers(1, 65, DIMS, dtype=np.int16)
+    w[:, :64] = 0  # and some chunks that hold nothing
+    sdf = np.where(w > 0, g.integers(-3072, 3073, DIMS), 0).astype(np.int16)
+    om = oracle.OracleMap(DIMS, ORIGIN, 0.05, 3072, 64)
+    om.set_voxels(ORIGIN, tuple(ORIGIN[a] + DIMS[a] for a in range(3)), sdf, w)
+    ix = np.ix_(*[(np.arange(n) - o) % n for n, o in zip(DIMS, ORIGIN)])
+    arrays = [torch.from_numpy(np.ascontiguousarray(v[ix])).to("cuda") for v in (sdf, w)]
+    scratch = torch.zeros(TsdfMap.scratch_bytes(DIMS, ORIGIN, 0.05, 3072, 64), dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    gm = TsdfMap(DIMS, ORIGIN, 0.05, 3072, 64, arrays=(*arrays, scratch))
+    gm.shift(MOVED)
+    om.shift(MOVED)
+    yield gm, om
+    gm.close()
+    om.close()
+
+
+def _box(lo, size):
+    return tuple(lo), tuple(l + s for l, s in zip(lo, size))
+
+
+@pytest.mark.parametrize("lo,size", [
+    (MOVED, DIMS),                                     # the window: many slots, one stretch of the result
+    (MOVED, (1, 1, 1)),
+    ((MOVED[0] + 3, MOVED[1], MOVED[2]), (7, 190, 122)),  # whole planes
+    ((MOVED[0] + 5, MOVED[1] + 6, MOVED[2] + 7), (200, 180, 110)),  # lines
+    (ORIGIN, DIMS),                                    # half window, half store
+    ((ORIGIN[0] - 40, ORIGIN[1] - 70, ORIGIN[2] - 20), (300, 330, 180)),  # beyond both on every side
+    ((ORIGIN[0], 0, 0), (60, 64, 1)),                  # the store alone, lines of one voxel
+    ((5000, -7000, 12), (130, 5, 65)),                 # neither
+    ((MOVED[0] - 1, MOVED[1] - 1, MOVED[2] - 1), (2, 2, 2)),  # a corner of the window
+])
+def test_readback_boxes(pair, lo, size):
+    gm, om = pair
+    lo, hi = _box(lo, size)
+    for _ in range(2):  # (staging is used again)
+        for g, o in zip(gm.readback(lo, hi), om.readback(lo, hi)):
+            assert g.shape == o.shape and np.array_equal(g, o)
+
+
+def test_readback_of_nothing_and_errors(pair):
+    from paper_2310_05766_amd import TsdfError
+    gm, _ = pair
+    assert gm.readback((1, 2, 3), (1, 5, 6))[0].shape == (0, 3, 3)
+    with pytest.raises(TsdfError):
+        import ctypes as C
+        from paper_2310_05766_amd import _abi
+        lo, hi = (C.c_int32 * 3)(0, 0, 0), (C.c_int32 * 3)(1, -1, 1)
+        one = np.zeros(1, np.int16).ctypes.data_as(C.POINTER(C.c_int16))
+        _abi.check(_abi.lib().tsdf_readback(gm.handle, lo, hi, one, one), "tsdf_readback")
