@@ -218,7 +218,7 @@ tsdf_status tsdf_profile_enable(tsdf_map *m, int32_t on);
  * (else TSDF_EINVAL). The first
  * call that turns it on allocates an 8-byte key per voxel of the window
  * (TSDF_ENOMEM if that fails). Interpolating maps take their own
- * integration path (one thread per ray, 64-bit atomicMin on the key
+ * integration path (several threads per ray, atomicMin on the key
  * volume); in tsdf_integrate_batch their scans run one by one, in order, on
  * their map's stream, ordered after the batch stream's earlier work and
  * before its later work. */
@@ -244,11 +244,12 @@ tsdf_status tsdf_map_set_carving(tsdf_map *m, int32_t on);
 /* 1 when carving is on, else 0. */
 tsdf_status tsdf_map_get_carving(const tsdf_map *m, int32_t *on);
 
-/* The number of 64-bit atomicMin operations the key-volume paths
+/* The number of atomicMin operations the key-volume paths
  * (interpolation, carving) of this map have issued on its key volume since
  * the previous call (or since the key volume was allocated), then restarts
  * the count. These paths skip an atomic that could not lower the key it
- * read, so the count is at most the visits. Waits for the map's stream;
+ * read, and merge a block's candidates before they issue any, so the count is
+ * at most the visits. Waits for the map's stream;
  * 0 for a map that never used the key volume. */
 tsdf_status tsdf_map_key_atomics(tsdf_map *m, int64_t *issued);
 

@@ -59,28 +59,6 @@ __device__ __forceinline__ uint4 entry_ray(const Ray &R, uint32_t cpack, uint32_
     return make_uint4((uint32_t)R.r, o0 | o1 << 16, o2 | (cpack & 0xffffu) << 16, cpack >> 16 | seq << 8);
 }
 
-// The point of thread t of a scan's block b. A block takes a patch of the
-// scan, kPatchRows runs of points kPatchStride apart, instead of one run: in
-// an organised scan (ring by ring, about a thousand columns to a ring) those
-// are neighbouring rings, whose points share tiles, so that a block meets
-// fewer tiles, sends fewer atomics and writes longer stretches of a run. Runs
-// of 1, 4, 8, 16 and 32 rows on 50 scans of 128 x 1024 points: count 123, 103,
-// 106, 103, 103 us, fill 153, 156, 157, 138, 131 us; on 64 uneven room scans
-// count + fill 378, -, 377, 359, 343 us. (A scan of another width, or no
-// organised scan, loses nothing: a row is still a run of points.)
-constexpr uint32_t kPatchRows = 32, kPatchStride = 1024;
-
-template <int kBinBlock>
-__device__ __forceinline__ int64_t patch_point(uint32_t b, int64_t n)
-{
-    constexpr uint32_t kPatch = kPatchRows * kPatchStride;  // points that a group of blocks shares out
-    constexpr uint32_t kRun = kBinBlock / kPatchRows, kGroup = kPatch / kBinBlock;
-    static_assert(kRun * kPatchRows == kBinBlock && kGroup * kRun == kPatchStride, "a group covers its points once");
-    const int64_t g0 = (int64_t)(b / kGroup) * kPatch;
-    if (g0 + kPatch > n) return (int64_t)b * kBinBlock + threadIdx.x;  // the last points: in order
-    return g0 + threadIdx.x / kRun * kPatchStride + b % kGroup * kRun + threadIdx.x % kRun;
-}
-
 // kInline (counting pass only): the batch is one scan whose descriptors are
 // I, not yet in memory.
 template <bool kFill, int kBinBlock, bool kInline>
@@ -132,7 +110,7 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
     const uint32_t s = inl ? 0u : B.block_scan[blockIdx.x];
     const ScanDev &SD = inl ? I.scan : B.scans[s];
     const MapDev &MD = inl ? I.map : B.maps[SD.map];
-    const int64_t i = patch_point<kBinBlock>(blockIdx.x - SD.block0, SD.n);
+    const int64_t i = patch_point<kBinBlock>(blockIdx.x - SD.block0, threadIdx.x, SD.n);
     const RayParams rp = SD.rp;
     Ray R;
     Walk W, Wv;  // the walk on the tile grid; the voxel walk's start (fill)

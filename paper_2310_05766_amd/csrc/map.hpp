@@ -25,10 +25,11 @@ struct tsdf_map {
     // own path through a key volume over the window, interp.hip)
     int64_t interp_dq = 0;                     // delta_z of Eq. (3), 1/2^20 units; 0: off
     bool carve = false;                        // rays longer than tau walked from the sensor
-    unsigned long long *interp_keys = nullptr;  // [nvox], EMPTY between scans
+    unsigned long long *interp_keys = nullptr;  // key volume, all ~0 between scans
     uint8_t *interp_touched = nullptr;          // [ceil(nvox / 64)], 0 between scans
-    unsigned long long *interp_ctr = nullptr;   // device counters (3)
+    unsigned long long *interp_ctr = nullptr;   // device counters (kCtrKinds * kCtrWords)
     unsigned long long *interp_ctr_host = nullptr;
+    int64_t atomics_seen = 0;                   // atomics counted up to the last tsdf_map_key_atomics
     float *interp_pts = nullptr;                // device copy of host points
     int64_t interp_pts_cap = 0;                 // points
     // registration: device state and rows of sums, pinned result

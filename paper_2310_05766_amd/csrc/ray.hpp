@@ -859,4 +859,140 @@ __device__ __forceinline__ bool free_walk_next(FreeWalk &F)
     return m != 0;
 }
 
+// ---------------------------------------------------------------------------
+// The free walk of a near ray (|S_a - o_a| and |D_a| below 2^25 on every axis,
+// 32,768 voxels), restricted to the voxels whose candidate is +tau: the same
+// voxels as FreeWalk's with u >= kFreeBias, in float64 throughout. Crossing
+// times scaled by the other axis' length, n and H stay below 2^52, so every
+// product and sum is exact. A step needs neither the coordinates nor a test
+// which crossing was an axis' last: each axis counts down to the crossing that
+// leaves the box or, inside it, to the first one past the segment's end, which
+// comes after all others in the walk's order. Carries an index into a dense
+// array over the box's window instead of the coordinates.
+// ---------------------------------------------------------------------------
+struct FreeRun {
+    double C01, C02, C12, K[3];
+    double n, dn[3];  // n - H of the current voxel, and its change per step
+    int32_t cnt[3], didx[3];
+    uint32_t idx;
+};
+constexpr int32_t kNearSide = 1 << 25;
+
+// Whether a ray's free segment is near enough for FreeRun.
+__device__ __forceinline__ bool free_run_near(const Ray &R, const RayParams &P)
+{
+    bool near = true;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const int64_t L = (int64_t)R.S[a] - P.o[a];
+        near = near && L < kNearSide && L > -kNearSide && fabs(R.D[a]) < (double)kNearSide;
+    }
+    return near;
+}
+
+// floor(num / den) + 1 for |num| < 2^52, 0 < den < 2^36 (num >= 0) and a
+// quotient below 2^26, else 0: an estimate within one and an exact correction
+// each way (the products are integers below 2^53).
+__device__ __forceinline__ double floor_div_up(double num, double den)
+{
+    double k = floor(num * approx_rcp(den));
+    k -= k * den > num ? 1.0 : 0.0;
+    k -= k * den > num ? 1.0 : 0.0;
+    k += (k + 1.0) * den <= num ? 1.0 : 0.0;
+    k += (k + 1.0) * den <= num ? 1.0 : 0.0;
+    return num < 0.0 ? 0.0 : k + 1.0;
+}
+
+// Sets the run down on the segment's first voxel in [lo, hi) (long_walk_init's
+// steps; stride: of the dense array, w0: its window's first voxel); false when
+// no voxel of the segment lies in the box or its first is not +tau.
+__device__ __forceinline__ bool free_run_init(const Ray &R, const RayParams &P, const int32_t lo[3],
+                                              const int32_t hi[3], const int32_t w0[3], const int32_t stride[3],
+                                              FreeRun &F)
+{
+    double absL[3], T[3], kin[3], N[3], X[3];
+    double dec[3];
+    int32_t g0[3], step[3];
+    bool hit = true;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const int32_t L = R.S[a] - P.o[a];
+        g0[a] = P.o[a] >> 10;  // arithmetic shift: floor division
+        const int32_t gB = R.S[a] >> 10;
+        step[a] = L > 0 ? 1 : (L < 0 ? -1 : 0);
+        absL[a] = (double)(L < 0 ? -L : L);
+        dec[a] = L < 0 ? 1.0 : 0.0;
+        const int32_t n = gB > g0[a] ? gB - g0[a] : g0[a] - gB;
+        T[a] = (double)(L >= 0 ? (g0[a] + 1) * 1024 - P.o[a] : P.o[a] - g0[a] * 1024);
+        const int32_t in = L > 0 ? lo[a] - g0[a] : (L < 0 ? g0[a] - (hi[a] - 1) : 0);
+        const int32_t k = in > 0 ? in : 0;
+        const int32_t x = L > 0 ? hi[a] - g0[a] : (L < 0 ? g0[a] - lo[a] + 1 : 0x7fffffff);
+        hit = hit && x > 0 && k <= n && (L != 0 || (g0[a] >= lo[a] && g0[a] < hi[a]));
+        kin[a] = (double)k;
+        N[a] = (double)n;
+        X[a] = (double)x;
+    }
+    if (!hit) return false;
+    // the entry event: the latest of the axes' entering crossings
+    bool any = false;
+    double Te = 0.0, Le = 0.0, de = 0.0;
+    int e = -1;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const double Ta = __fma_rn(1024.0, kin[a] - 1.0, T[a]);
+        const double d = __fma_rn(Ta, Le, -(Te * absL[a]));
+        const bool later = kin[a] > 0.0 && (!any || d > 0.0 || (d == 0.0 && dec[a] > de));
+        any = any || kin[a] > 0.0;
+        Te = later ? Ta : Te;
+        Le = later ? absL[a] : Le;
+        de = later ? dec[a] : de;
+        e = later ? a : e;
+    }
+    double n = 0.0;
+    F.idx = 0;
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+        // crossings of b at or before the entry event
+        double k = 0.0;
+        if (any) {
+            const double num = __fma_rn(Te, absL[b], -(T[b] * Le)) - (dec[b] > de ? 1.0 : 0.0);
+            k = floor_div_up(num, 1024.0 * Le);
+            k = k < N[b] ? k : N[b];
+            k = e == b ? kin[b] : k;
+        }
+        if (k >= X[b]) return false;  // left the box before it entered on another axis
+        const int32_t g = g0[b] + step[b] * (int32_t)k;
+        T[b] = __fma_rn(1024.0, k, T[b]);
+        F.cnt[b] = (int32_t)((X[b] <= N[b] ? X[b] : N[b] + 1.0) - k);
+        F.K[b] = 2048.0 * absL[b];
+        F.dn[b] = -1024.0 * fabs(R.D[b]);
+        F.didx[b] = step[b] * stride[b];
+        F.idx += (uint32_t)(g - w0[b]) * (uint32_t)stride[b];
+        n = __fma_rn((double)(R.q[b] - 1024 * g - 512), R.D[b], n);
+    }
+    F.C01 = 2.0 * __fma_rn(T[0], absL[1], -(T[1] * absL[0])) + (dec[0] - dec[1]);
+    F.C02 = 2.0 * __fma_rn(T[0], absL[2], -(T[2] * absL[0])) + (dec[0] - dec[2]);
+    F.C12 = 2.0 * __fma_rn(T[1], absL[2], -(T[2] * absL[1])) + (dec[1] - dec[2]);
+    F.n = n - ((double)P.tau * R.r - floor(0.5 * R.r));  // H as in FreeWalk
+    return F.n >= 0.0;
+}
+
+// Next voxel; false past the box, the segment's end, or the last +tau voxel
+// (the state then holds a step past the end, never used).
+__device__ __forceinline__ bool free_run_next(FreeRun &F)
+{
+    const bool s0 = F.C01 <= 0.0 && F.C02 <= 0.0, s1 = F.C01 >= 0.0 && F.C12 <= 0.0, s2 = F.C02 >= 0.0 && F.C12 >= 0.0;
+    const double e0 = s0 ? 1.0 : 0.0, e1 = s1 ? 1.0 : 0.0, e2 = s2 ? 1.0 : 0.0;
+    F.C01 = __fma_rn(e1, -F.K[0], __fma_rn(e0, F.K[1], F.C01));
+    F.C02 = __fma_rn(e2, -F.K[0], __fma_rn(e0, F.K[2], F.C02));
+    F.C12 = __fma_rn(e2, -F.K[1], __fma_rn(e1, F.K[2], F.C12));
+    F.n = __fma_rn(e0, F.dn[0], __fma_rn(e1, F.dn[1], __fma_rn(e2, F.dn[2], F.n)));
+    F.idx += (uint32_t)((s0 ? F.didx[0] : 0) + (s1 ? F.didx[1] : 0) + (s2 ? F.didx[2] : 0));
+    F.cnt[0] -= s0 ? 1 : 0;
+    F.cnt[1] -= s1 ? 1 : 0;
+    F.cnt[2] -= s2 ? 1 : 0;
+    const int32_t c = F.cnt[0] < F.cnt[1] ? F.cnt[0] : F.cnt[1];
+    return F.n >= 0.0 && (c < F.cnt[2] ? c : F.cnt[2]) > 0;
+}
+
 }  // namespace tsdf

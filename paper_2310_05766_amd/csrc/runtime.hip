@@ -584,6 +584,14 @@ tsdf_status tsdf_map_destroy(tsdf_map *m)
 // Whether the map's scans take the key-volume path (interp.hip).
 static bool keyvol_path(const tsdf_map *m) { return m->interp_dq > 0 || m->carve; }
 
+// A kind's counters, as last copied to the host.
+static int64_t counter_sum(const tsdf_map *m, int kind)
+{
+    unsigned long long sum = 0;
+    for (uint32_t k = 0; k < kCtrLines; ++k) sum += m->interp_ctr_host[kind * kCtrWords + k * kCtrStride];
+    return (int64_t)sum;
+}
+
 // One scan through the key-volume path, on the map's stream.
 static tsdf_status integrate_interp(tsdf_map *m, const float *xyz, int64_t n, bool host, const double pose[16],
                              tsdf_scan_stats *stats)
@@ -613,6 +621,10 @@ static tsdf_status integrate_interp(tsdf_map *m, const float *xyz, int64_t n, bo
     P.keys = m->interp_keys;
     P.touched = m->interp_touched;
     P.counters = m->interp_ctr;
+    P.want_stats = stats ? 1 : 0;
+    P.key_shift = key32_shift(P.rp.tau, n);
+    P.keys32 = (uint32_t *)m->interp_keys;
+    P.marks = (uint8_t *)m->interp_keys + key_marks_offset(m->nvox);
     P.xyz = xyz;
     if (host && n > 0) {
         if (n > m->interp_pts_cap) {
@@ -629,18 +641,17 @@ static tsdf_status integrate_interp(tsdf_map *m, const float *xyz, int64_t n, bo
         HIPCHK(m, hipStreamSynchronize(m->stream));
         P.xyz = m->interp_pts;
     }
-    // the first three counters are per scan; the atomics counter (fourth)
-    // adds up until tsdf_map_key_atomics reads it
-    HIPCHK(m, launch_fill_u32((uint32_t *)m->interp_ctr, 6, 0u, m->stream));
+    // (the first three kinds are per scan, the atomics add up)
+    if (stats) HIPCHK(m, launch_fill_u32((uint32_t *)m->interp_ctr, (int64_t)(3 * kCtrWords * 2), 0u, m->stream));
     HIPCHK(m, launch_interp(P, m->nvox, m->stream));
     if (stats) {
-        HIPCHK(m, hipMemcpyAsync(m->interp_ctr_host, m->interp_ctr, 3 * sizeof(unsigned long long),
+        HIPCHK(m, hipMemcpyAsync(m->interp_ctr_host, m->interp_ctr, 3 * kCtrWords * sizeof(unsigned long long),
                                  hipMemcpyDeviceToHost, m->stream));
         HIPCHK(m, hipStreamSynchronize(m->stream));
         stats->points_in = n;
-        stats->points_valid = (int64_t)m->interp_ctr_host[0];
-        stats->visits = (int64_t)m->interp_ctr_host[1];
-        stats->voxels_updated = (int64_t)m->interp_ctr_host[2];
+        stats->points_valid = counter_sum(m, kCtrValid);
+        stats->visits = counter_sum(m, kCtrVisits);
+        stats->voxels_updated = counter_sum(m, kCtrUpdated);
     }
     return TSDF_OK;
 }
@@ -649,14 +660,15 @@ static tsdf_status integrate_interp(tsdf_map *m, const float *xyz, int64_t n, bo
 static tsdf_status ensure_key_volume(tsdf_map *m)
 {
     if (m->interp_keys) return TSDF_OK;
-    if (hipMalloc(&m->interp_keys, (size_t)m->nvox * sizeof(unsigned long long)) != hipSuccess) {
+    if (hipMalloc(&m->interp_keys, key_volume_bytes(m->nvox)) != hipSuccess) {
         m->interp_keys = nullptr;
         return TSDF_ENOMEM;
     }
     const int64_t runs = (m->nvox + 63) / 64;
     const size_t touched_bytes = (size_t)((runs + 3) / 4 * 4);
-    if (hipMalloc(&m->interp_ctr, 4 * sizeof(unsigned long long)) != hipSuccess) m->interp_ctr = nullptr;
-    if (hipHostMalloc(&m->interp_ctr_host, 4 * sizeof(unsigned long long), hipHostMallocDefault) != hipSuccess)
+    if (hipMalloc(&m->interp_ctr, kCtrKinds * kCtrWords * sizeof(unsigned long long)) != hipSuccess) m->interp_ctr = nullptr;
+    if (hipHostMalloc(&m->interp_ctr_host, kCtrKinds * kCtrWords * sizeof(unsigned long long), hipHostMallocDefault) !=
+        hipSuccess)
         m->interp_ctr_host = nullptr;
     if (hipMalloc(&m->interp_touched, touched_bytes) != hipSuccess) m->interp_touched = nullptr;
     if (!m->interp_ctr || !m->interp_ctr_host || !m->interp_touched) {
@@ -670,9 +682,9 @@ static tsdf_status ensure_key_volume(tsdf_map *m)
         m->interp_keys = nullptr;
         return TSDF_ENOMEM;
     }
-    HIPCHK(m, launch_fill_u32((uint32_t *)m->interp_keys, m->nvox * 2, 0xffffffffu, m->stream));
+    HIPCHK(m, launch_fill_u32((uint32_t *)m->interp_keys, (int64_t)(key_volume_bytes(m->nvox) / 4), 0xffffffffu, m->stream));
     HIPCHK(m, launch_fill_u32((uint32_t *)m->interp_touched, (int64_t)(touched_bytes / 4), 0u, m->stream));
-    HIPCHK(m, launch_fill_u32((uint32_t *)m->interp_ctr, 8, 0u, m->stream));
+    HIPCHK(m, launch_fill_u32((uint32_t *)m->interp_ctr, (int64_t)(kCtrKinds * kCtrWords * 2), 0u, m->stream));
     return TSDF_OK;
 }
 
@@ -1017,11 +1029,12 @@ tsdf_status tsdf_map_key_atomics(tsdf_map *m, int64_t *issued)
     if (m->poisoned) return TSDF_EDEVICE;
     *issued = 0;
     if (!m->interp_ctr) return TSDF_OK;  // no key volume yet: nothing issued
-    HIPCHK(m, hipMemcpyAsync(m->interp_ctr_host + 3, m->interp_ctr + 3, sizeof(unsigned long long),
-                             hipMemcpyDeviceToHost, m->stream));
+    HIPCHK(m, hipMemcpyAsync(m->interp_ctr_host + kCtrAtomics * kCtrWords, m->interp_ctr + kCtrAtomics * kCtrWords,
+                             kCtrWords * sizeof(unsigned long long), hipMemcpyDeviceToHost, m->stream));
     HIPCHK(m, hipStreamSynchronize(m->stream));
-    *issued = (int64_t)m->interp_ctr_host[3];
-    HIPCHK(m, launch_fill_u32((uint32_t *)(m->interp_ctr + 3), 2, 0u, m->stream));
+    const int64_t total = counter_sum(m, kCtrAtomics);
+    *issued = total - m->atomics_seen;
+    m->atomics_seen = total;
     return TSDF_OK;
 }
 

@@ -342,7 +342,7 @@ class TsdfMap:
         return bool(v.value)
 
     def key_atomics(self) -> int:
-        """64-bit atomics the key-volume paths issued since the last call."""
+        """Atomics the key-volume paths issued since the last call."""
         v = C.c_int64()
         check(_abi.lib().tsdf_map_key_atomics(self._h, C.byref(v)), "tsdf_map_key_atomics")
         return int(v.value)

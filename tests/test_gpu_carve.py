@@ -242,3 +242,40 @@ def test_carving_degenerate_cases():
         assert same(gm, om, dims)
         gm.close()
         om.close()
+
+
+@pytest.mark.parametrize("dims,tau,widths", [((40, 36, 64), 32767, (1 << 15, (1 << 15) + 1, 900)),
+                                             ((37, 41, 29), 32767, ((1 << 15) + 1, 1 << 15, 900)),
+                                             ((21, 30, 128), 2048, (70000, 1, 63, 65))])
+def test_key_widths_of_the_key_volume(dims, tau, widths):
+    """On both sides of where the key volume's keys fit 32 bits, in turn on one
+    map (each width finds the volume as the other left it), carved and
+    interpolated; windows whose rows are whole runs of 64 voxels and windows
+    whose rows are not, before and after a shift that turns the ring; scans of
+    whole patches of points, of less and of a single point."""
+    origin = tuple(-(d // 2) for d in dims)
+    om = oracle.OracleMap(dims, origin, 0.1, tau, 64)
+    gm = gpu_map(dims, origin, 0.1, tau, 64)
+    for step in range(3):
+        say("key widths", dims, tau, "step", step)
+        if step == 1:
+            assert gm.set_carving(False) is False
+            om.set_carving(False)
+            gm.set_interpolation(20.0, 8)
+            om.set_interpolation(20.0, 8)
+        else:
+            gm.set_interpolation(0.0, 0)
+            om.set_interpolation(0.0, 0)
+            gm.set_carving(True)
+            om.set_carving(True)
+        if step == 2:
+            to = tuple(origin[a] + (5, -3, 7)[a] for a in range(3))
+            gm.shift(to)
+            om.shift(to)
+        for k, n in enumerate(widths + widths[:2]):
+            xyz = synth.fuzz_scan((99, step, k), n, extent_m=2.5, nan_frac=0.02, grid_snap=0.05 if k % 2 else None)
+            pose = synth.fuzz_pose((100, step, k), 0.5)
+            assert gm.integrate(xyz, pose, stats=True) == om.integrate(xyz, pose), (step, n)
+        assert same(gm, om, dims)
+    gm.close()
+    om.close()

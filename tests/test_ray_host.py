@@ -9,7 +9,8 @@ g++ compiles csrc/ray.hpp with its one inline-asm minimum replaced.
   rounding, with perturbed reciprocal estimates;
 * free_walk_check: carving's free-space walk, clipped to random boxes and to
   the carving scan's slabs, against the oracle's segment voxels and keys
-  (the oracle is compiled with gcc and linked in)."""
+  (the oracle is compiled with gcc and linked in);
+* free_run_check: the near free walk of carving against the free-space walk."""
 import os
 import shutil
 import subprocess
@@ -83,5 +84,16 @@ def test_merge_divisions_exact(build):
     """Eq. (1)'s division as the merges run it, exact against integer
     rounding."""
     out = subprocess.run([build("rdiv_check"), "5"], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout + out.stderr
+    assert "mismatches 0" in out.stdout
+
+
+@pytest.mark.parametrize("seed", [1, 2])
+def test_near_free_walk_matches_the_general_one(build, seed):
+    """Carving's near free walk (FreeRun, float64) visits exactly the +tau
+    voxels of the general free walk (FreeWalk, 64-bit integers), in order,
+    over random boxes and slabs, with ties, flat axes and perturbed
+    reciprocals."""
+    out = subprocess.run([build("free_run_check"), str(seed), "60000"], capture_output=True, text=True)
     assert out.returncode == 0, out.stdout + out.stderr
     assert "mismatches 0" in out.stdout
