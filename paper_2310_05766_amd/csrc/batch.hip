@@ -21,6 +21,14 @@
 //                 to its first voxel in the tile (exact crossing counts) and
 //                 walks the tile; candidates meet in LDS; then the merge
 //   k_stats       per-scan counts, when asked for
+//
+// Where each map has one scan, binning is one pass (the engine says when):
+//   k_bin<once>   the walk once; each block writes its entries, tile by tile,
+//                 into a region of its own and adds a segment of them to the
+//                 list of each tile it met; who adds a tile's first one lists
+//                 the tile as busy
+//   k_tile_once   k_tile for these lists
+// (128 x 1024 points: 12.6 us, where count, runs and fill took 6.4 + 5.7 + 11.2.)
 #include <string.h>
 
 #include <algorithm>
@@ -59,11 +67,40 @@ __device__ __forceinline__ uint4 entry_ray(const Ray &R, uint32_t cpack, uint32_
     return make_uint4((uint32_t)R.r, o0 | o1 << 16, o2 | (cpack & 0xffffu) << 16, cpack >> 16 | seq << 8);
 }
 
-// kInline (counting pass only): the batch is one scan whose descriptors are
+enum { kCount = 0, kFillRuns = 1, kOnce = 2 };
+
+// A tile with this many entries or more is listed first: the persistent tile
+// pass then starts the longest tiles early instead of ending on one of them.
+constexpr uint32_t kHeavyTile = 2048;
+
+// Adds a block's segment of n entries to a tile's list. A tile is listed as
+// busy by its first segment (`first` is then set, and the caller does it), and
+// once more, among the heavy ones, by the segment that makes it heavy: the tile
+// pass takes it from there and skips it among the others.
+__device__ __forceinline__ void add_segment(const BatchArrays &B, BatchCtl *ctl, uint32_t tile, uint32_t map,
+                                            uint32_t pos, uint32_t n, uint32_t node, bool &first)
+{
+    TileList *L = &B.lists[tile];
+    const unsigned long long old =
+        atomicAdd(reinterpret_cast<unsigned long long *>(L), (unsigned long long)n << 32 | 1ull);
+    const uint32_t k = (uint32_t)old, total = (uint32_t)(old >> 32);
+    if (k < kSegs) L->seg[k] = make_uint2(pos, n);
+    else B.nodes[node] = make_uint4(atomicExch(&L->chain[(k - kSegs) % kChains], node + 1u), pos, n, 0u);
+    first = k == 0u;
+    if (total < kHeavyTile && total + n >= kHeavyTile) {
+        const uint32_t h = atomicAdd(&ctl->n_nonempty, 1u);
+        B.offsets[h] = tile;
+        B.cursor[h] = map;
+    }
+}
+
+// kInline (the first pass only): the batch is one scan whose descriptors are
 // I, not yet in memory.
-template <bool kFill, int kBinBlock, bool kInline>
+template <int kMode, int kBinBlock, bool kInline>
 __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
 {
+    constexpr bool kFill = kMode != kCount;       // writes records
+    constexpr bool kFirst = kMode != kFillRuns;   // counts valid points
     // the block's (sequence slot, tile) keys: a hash table of two slots per
     // point of the block (a block of 256 OS1-128 points meets about 100
     // tiles), so that clearing and flushing it stays cheap; keys that find it
@@ -77,10 +114,10 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
     // per emitted entry: hash slot | crossing counts (7 bits per axis) << 10, and rank
     __shared__ uint32_t s_slot[kFill ? kMaxEmit * kBinBlock : 1];
     __shared__ uint16_t s_rank[kFill ? kMaxEmit * kBinBlock : 1];
-    __shared__ uint32_t s_valid;
+    __shared__ uint32_t s_valid, s_extra, s_new, s_job, s_sum[kBinBlock / 64];
     // a one-scan batch's descriptors come with the counting launch, which
     // stores them for the kernels after it
-    constexpr bool inl = !kFill && kInline;
+    constexpr bool inl = kFirst && kInline;
     const BatchHdr H = inl ? I.hdr : *B.hdr;
     if (inl && blockIdx.x == 0 && threadIdx.x == 0) {
         *B.hdr = I.hdr;
@@ -88,7 +125,7 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
         B.scans[0] = I.scan;
         B.seq_sensor[0] = make_int4(I.scan.rp.o[0], I.scan.rp.o[1], I.scan.rp.o[2], I.scan.rp.tau);
     }
-    if (!kFill && blockIdx.x == 0 && threadIdx.x == 0) {
+    if (kMode == kCount && blockIdx.x == 0 && threadIdx.x == 0) {
         // the allocation counters of the previous batch are done with (the
         // grid always has a block 0, also for a batch without points)
         B.ctl->n_nonempty = 0;
@@ -102,11 +139,11 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
         h_key[j] = 0;
         h_cnt[j] = 0;
     }
-    if (threadIdx.x == 0) s_valid = 0;
+    if (threadIdx.x == 0) s_valid = s_extra = s_new = 0;
     __syncthreads();
 
     // (a one-scan batch's block table is written here, for the fill)
-    if (inl && threadIdx.x == 0) B.block_scan[blockIdx.x] = 0u;
+    if (inl && kMode == kCount && threadIdx.x == 0) B.block_scan[blockIdx.x] = 0u;
     const uint32_t s = inl ? 0u : B.block_scan[blockIdx.x];
     const ScanDev &SD = inl ? I.scan : B.scans[s];
     const MapDev &MD = inl ? I.map : B.maps[SD.map];
@@ -136,6 +173,10 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
     const uint32_t nt0 = (uint32_t)__builtin_amdgcn_readfirstlane(MD.nt[0]);
     const uint32_t nt1 = (uint32_t)__builtin_amdgcn_readfirstlane(MD.nt[1]);
     const uint32_t nt2 = (uint32_t)__builtin_amdgcn_readfirstlane(MD.nt[2]);
+    // one pass: this block's region of the entries, its nodes, the counters
+    const uint32_t region = kMode == kOnce ? blockIdx.x * kBinBlock * H.emit : 0u;
+    const uint32_t node0 = kMode == kOnce ? blockIdx.x * nodes_per_block(kBinBlock, H.emit) : 0u;
+    BatchCtl *ctl = kMode == kOnce ? B.ctl + H.once : B.ctl;
     int ne = 0;
     uint32_t listed = 0;  // fill: bit k set when entry k was listed in LDS (not sent straight to its run)
     double t_in = -1.0;  // event that entered the current tile (none for the first)
@@ -169,6 +210,13 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
                     s_rank[ne * kBinBlock + threadIdx.x] = (uint16_t)rank;
                     listed |= 1u << ne;
                 }
+            } else if (kMode == kOnce) {  // a segment of its own, from the region's end
+                const uint32_t x = atomicAdd(&s_extra, 1u), pos = region + kBinBlock * H.emit - 1u - x;
+                B.entries[pos] = make_uint4((uint32_t)i, (uint32_t)q[0], (uint32_t)q[1], (uint32_t)q[2]);
+                B.entries2[pos] = entry_ray(R, cpack, seq);
+                bool first;
+                add_segment(B, ctl, key, (uint32_t)SD.map, pos, 1u, node0 + 2u * kBinBlock + x, first);
+                if (first) B.jobs[atomicAdd(&ctl->n_light, 1u)] = make_uint4(key, (uint32_t)SD.map, 0u, 0u);
             } else if (kFill) {  // table full or very long band: straight to the tile's run
                 const uint32_t pos = atomicAdd(&B.cursor[key], 1u);
                 if (pos < H.cap) {
@@ -184,8 +232,38 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
         }
         active = walk_next_event(W, t_in, typ_in);
     }
-    if (!kFill && valid) atomicAdd(&s_valid, 1u);
+    if (kFirst && valid) atomicAdd(&s_valid, 1u);
     __syncthreads();
+    if (kMode == kOnce) {
+        // the block's entries in the order of its table: two slots per thread
+        const uint32_t j0 = 2u * threadIdx.x, c0 = h_cnt[j0], c1 = h_cnt[j0 + 1u];
+        uint32_t p = c0 + c1;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t v = (uint32_t)__shfl_up((int)p, off);
+            if (lane() >= (uint32_t)off) p += v;
+        }
+        if (lane() == 63u) s_sum[threadIdx.x / 64] = p;
+        __syncthreads();
+        for (uint32_t w = 0; w < threadIdx.x / 64; ++w) p += s_sum[w];
+        const uint32_t at = region + p - c0 - c1;
+        h_base[j0] = at;
+        h_base[j0 + 1u] = at + c0;
+        bool f0 = false, f1 = false;
+        if (c0) add_segment(B, ctl, h_key[j0] - 1u, (uint32_t)SD.map, at, c0, node0 + j0, f0);
+        if (c1) add_segment(B, ctl, h_key[j0 + 1u] - 1u, (uint32_t)SD.map, at + c0, c1, node0 + j0 + 1u, f1);
+        // one atomic for all tiles that this block lists
+        uint32_t r = 0;
+        if (f0 || f1) r = atomicAdd(&s_new, (f0 ? 1u : 0u) + (f1 ? 1u : 0u));
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            if (s_new) s_job = atomicAdd(&ctl->n_light, s_new);
+            B.valid_part[blockIdx.x] = s_valid;
+        }
+        __syncthreads();
+        if (f0) B.jobs[s_job + r++] = make_uint4(h_key[j0] - 1u, (uint32_t)SD.map, 0u, 0u);
+        if (f1) B.jobs[s_job + r] = make_uint4(h_key[j0 + 1u] - 1u, (uint32_t)SD.map, 0u, 0u);
+    } else {
     // one global atomic per distinct key of this block
     for (uint32_t j = threadIdx.x; j < kHashSlots; j += kBinBlock) {
         const uint32_t k1 = h_key[j];
@@ -193,6 +271,7 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
         if (k1 == 0u || c == 0u) continue;
         if (kFill) h_base[j] = atomicAdd(&B.cursor[k1 - 1u], c);
         else atomicAdd(&B.counts[k1 - 1u], c);
+    }
     }
     if (!kFill) {
         if (threadIdx.x == 0) B.valid_part[blockIdx.x] = s_valid;
@@ -238,10 +317,6 @@ __device__ __forceinline__ int32_t map_of_tile(const BatchArrays &B, int32_t nma
 // sequence slots, so that the chains of count loads stay short.
 constexpr int kAllocTiles = kAllocBlock / 4;
 constexpr int kAllocPer = kMaxSeq / 4;  // sequence slots per lane, at most
-// A tile with this many entries or more is listed first: the persistent tile
-// pass then starts the longest tiles early instead of ending on one of them.
-constexpr uint32_t kHeavyTile = 2048;
-
 __global__ __launch_bounds__(kAllocBlock) void k_alloc(BatchArrays B)
 {
     __shared__ uint32_t s_w[3][kAllocBlock / 64];  // per wave: entries, heavy tiles, light tiles
@@ -467,6 +542,75 @@ __device__ __forceinline__ MapDev uniform_map(const MapDev &m)
     return u;
 }
 
+// One entry's candidates, from its record to the keys of its slot at `base`:
+// the walk is resumed right after the event that entered the tile; its voxels
+// inside the tile are one run (the walk carries the key's LDS address itself).
+// Returns the visits when kStats. (t0: the tile's first voxel in the window,
+// blo: in global coordinates.)
+template <bool kStats, typename Key>
+__device__ __forceinline__ uint32_t walk_entry(const uint4 &ra, const uint4 &rb, const int32_t o[3], int32_t tau,
+                                               uint32_t base, const BatchHdr &H, const MapDev &MD,
+                                               const int32_t t0[3], const int32_t blo[3], const int32_t ext[3],
+                                               const int32_t shb[3], bool cut)
+{
+    constexpr int kKeyLog2 = sizeof(Key) == 4 ? 2 : 3;
+    const uint32_t i = ra.x;
+    const int32_t q[3] = {(int32_t)ra.y, (int32_t)ra.z, (int32_t)ra.w};
+    const int32_t off[3] = {(int16_t)(rb.y & 0xffffu), (int16_t)(rb.y >> 16), (int16_t)(rb.z & 0xffffu)};
+    const int32_t c[3] = {(int32_t)((rb.z >> 16) & 0xffu), (int32_t)(rb.z >> 24), (int32_t)(rb.w & 0xffu)};
+    Ray R;
+    BoxWalk V;
+    tile_walk_resume(q, off, rb.x, c, o, tau, blo, ext, shb, base, R, V);
+    const double taud = (double)tau, rh = R.r + 0.5;
+    uint32_t visits = 0;
+    // (a candidate outside the window is no visit)
+    const auto resident = [&]() {
+        const uint32_t v = ((uint32_t)V.lv - base) >> kKeyLog2;
+        return (int32_t)(v & ((1u << H.lt[2]) - 1u)) + t0[2] < MD.dims[2] &&
+               (int32_t)((v >> H.lt[2]) & ((1u << H.lt[1]) - 1u)) + t0[1] < MD.dims[1] &&
+               (int32_t)(v >> (H.lt[1] + H.lt[2])) + t0[0] < MD.dims[0];
+    };
+    if (sizeof(Key) == 4) {
+        do {
+            lds_min(V.lv, tile_key32(V.n, rh, R.inv_r2, taud, H.key_shift, i));
+            if (kStats) visits += !cut || resident() ? 1u : 0u;
+        } while (box_walk_next(V));
+    } else {
+        const uint32_t ihi = i >> 16, ilo = i << 16;
+        do {
+            lds_min(V.lv, tile_key(V.n, rh, R.inv_r2, taud, ihi, ilo));
+            if (kStats) visits += !cut || resident() ? 1u : 0u;
+        } while (box_walk_next(V));
+    }
+    return visits;
+}
+
+// A tile with one busy sequence slot: its keys straight into HBM, runs of 8;
+// the voxels updated.
+template <int kTileBlock, typename Key>
+__device__ __forceinline__ uint32_t merge_tile_direct(Key *keys, uint32_t tvox, const BatchHdr &H, const MapDev &MD,
+                                                      const int32_t t0[3], bool cut)
+{
+    constexpr Key kNone = (Key)~(Key)0;
+    uint32_t updated = 0;
+    for (uint32_t v0 = threadIdx.x * 8u; v0 < tvox; v0 += kTileBlock * 8u) {
+        const int32_t rz0 = (int32_t)(v0 & ((1u << H.lt[2]) - 1u)) + t0[2];
+        const int32_t ry = (int32_t)((v0 >> H.lt[2]) & ((1u << H.lt[1]) - 1u)) + t0[1];
+        const int32_t rx = (int32_t)(v0 >> (H.lt[1] + H.lt[2])) + t0[0];
+        if (cut && (rx >= MD.dims[0] || ry >= MD.dims[1] || rz0 >= MD.dims[2])) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) keys[v0 + j] = kNone;
+            continue;
+        }
+        int32_t sx = rx + MD.ring0[0], sy = ry + MD.ring0[1];
+        sx -= sx >= MD.dims[0] ? MD.dims[0] : 0;
+        sy -= sy >= MD.dims[1] ? MD.dims[1] : 0;
+        const int64_t row = ((int64_t)sx * MD.dims[1] + sy) * MD.dims[2];
+        updated += merge_run_direct(&keys[v0], H.key_shift, MD, row, rz0);
+    }
+    return updated;
+}
+
 // Persistent tile pass. Workgroup b first takes busy tile b, then pulls
 // further tiles from queue b % nq, nq = min(8, workgroups) (one queue per
 // XCD keeps same-address atomics spread; with fewer than 8 workgroups each
@@ -581,42 +725,12 @@ __global__ __launch_bounds__(kTileBlock) __attribute__((amdgpu_waves_per_eu(kTil
             for (uint32_t e = beg + threadIdx.x; e < end; e += kTileBlock) {
                 const uint4 ra = B.entries[e];
                 const uint4 rb = B.entries2[e];
-                const uint32_t i = ra.x;
                 const int4 sens = s_sens[(rb.w >> 8) & (kMaxSeq - 1)];
                 const int32_t o[3] = {sens.x, sens.y, sens.z};
-                const int32_t tau = sens.w & 0xffff;
                 const int32_t r = (sens.w >> 16) - j0;
-                const int32_t q[3] = {(int32_t)ra.y, (int32_t)ra.z, (int32_t)ra.w};
-                const int32_t off[3] = {(int16_t)(rb.y & 0xffffu), (int16_t)(rb.y >> 16), (int16_t)(rb.z & 0xffffu)};
-                const int32_t c[3] = {(int32_t)((rb.z >> 16) & 0xffu), (int32_t)(rb.z >> 24), (int32_t)(rb.w & 0xffu)};
-                // resume the walk right after the event that entered the
-                // tile; its voxels inside the tile are one run (the walk
-                // carries the key's LDS address itself)
-                Ray R;
-                BoxWalk V;
                 const uint32_t base = lds_address(s_keys) + (((uint32_t)r << lsum) << kKeyLog2);
-                tile_walk_resume(q, off, rb.x, c, o, tau, blo, ext, shb, base, R, V);
-                const double taud = (double)tau, rh = R.r + 0.5;
-                uint32_t visits = 0;
-                // (a candidate outside the window is no visit)
-                const auto resident = [&]() {
-                    const uint32_t v = ((uint32_t)V.lv - base) >> kKeyLog2;
-                    return (int32_t)(v & (ez - 1)) + t0[2] < MD.dims[2] &&
-                           (int32_t)((v >> H.lt[2]) & (ey - 1)) + t0[1] < MD.dims[1] &&
-                           (int32_t)(v >> (H.lt[1] + H.lt[2])) + t0[0] < MD.dims[0];
-                };
-                if (sizeof(Key) == 4) {
-                    do {
-                        lds_min(V.lv, tile_key32(V.n, rh, R.inv_r2, taud, kshift, i));
-                        if (kStats) visits += !cut || resident() ? 1u : 0u;
-                    } while (box_walk_next(V));
-                } else {
-                    const uint32_t ihi = i >> 16, ilo = i << 16;
-                    do {
-                        lds_min(V.lv, tile_key(V.n, rh, R.inv_r2, taud, ihi, ilo));
-                        if (kStats) visits += !cut || resident() ? 1u : 0u;
-                    } while (box_walk_next(V));
-                }
+                const uint32_t visits =
+                    walk_entry<kStats, Key>(ra, rb, o, sens.w & 0xffff, base, H, MD, t0, blo, ext, shb, cut);
                 if (kStats && visits) atomicAdd(&s_vis[r], visits);
             }
             __syncthreads();
@@ -659,23 +773,7 @@ __global__ __launch_bounds__(kTileBlock) __attribute__((amdgpu_waves_per_eu(kTil
                     for (int r = 0; r < ng; ++r)
                         if (upd[r]) atomicAdd(&s_upd[r], upd[r]);
             } else {
-                // a single busy slot: merge straight into HBM, runs of 8
-                uint32_t updated = 0;
-                for (uint32_t v0 = threadIdx.x * 8u; v0 < tvox; v0 += kTileBlock * 8u) {
-                    const int32_t rz0 = (int32_t)(v0 & (ez - 1)) + t0[2];
-                    const int32_t ry = (int32_t)((v0 >> H.lt[2]) & (ey - 1)) + t0[1];
-                    const int32_t rx = (int32_t)(v0 >> (H.lt[1] + H.lt[2])) + t0[0];
-                    if (cut && (rx >= MD.dims[0] || ry >= MD.dims[1] || rz0 >= MD.dims[2])) {
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) s_keys[v0 + j] = kNone;
-                        continue;
-                    }
-                    int32_t sx = rx + MD.ring0[0], sy = ry + MD.ring0[1];
-                    sx -= sx >= MD.dims[0] ? MD.dims[0] : 0;
-                    sy -= sy >= MD.dims[1] ? MD.dims[1] : 0;
-                    const int64_t row = ((int64_t)sx * MD.dims[1] + sy) * MD.dims[2];
-                    updated += merge_run_direct(&s_keys[v0], kshift, MD, row, rz0);
-                }
+                const uint32_t updated = merge_tile_direct<kTileBlock, Key>(s_keys, tvox, H, MD, t0, cut);
                 if (kStats && updated) atomicAdd(&s_upd[0], updated);
             }
             __syncthreads();
@@ -702,6 +800,144 @@ __global__ __launch_bounds__(kTileBlock) __attribute__((amdgpu_waves_per_eu(kTil
         // next tile from this workgroup's queue
         if (threadIdx.x == 0)
             s_job = gridDim.x + queue + nq * atomicAdd(&B.ctl->work[queue * kQueueStride], 1u);
+        __syncthreads();
+        job = uniform(s_job);
+    }
+}
+
+// The tile pass for the lists of one binning pass (one scan per map): jobs and
+// queues as in k_tile. A tile's segments are gathered by the first wave, up to
+// 64 at a time: those of the list, then three nodes of each chain (a chain is a
+// load after a load, so 16 are followed together); an entry finds its segment
+// in their prefix sums. Bound by latency: each tile is a chain of dependent
+// loads, as in k_tile, for a hundred entries (128 x 1024 points: 22.6 us against
+// k_tile's 24.0, which had its runs laid out for it by two launches more).
+template <int kTileBlock, bool kStats, typename Key>
+__global__ __launch_bounds__(kTileBlock) __attribute__((amdgpu_waves_per_eu(kTileWaves))) void k_tile_once(BatchArrays B)
+{
+    constexpr Key kNone = (Key)~(Key)0;
+    constexpr int kKeyLog2 = sizeof(Key) == 4 ? 2 : 3, kHops = 3;
+    static_assert(kSegs + kHops * kChains <= 64, "a lane per segment");
+    extern __shared__ uint64_t s_dyn[];
+    Key *s_keys = reinterpret_cast<Key *>(s_dyn);
+    // per segment gathered: its place less the entries of those before it, and
+    // the entries up to its end
+    __shared__ uint32_t s_off[64], s_end[64];
+    __shared__ uint32_t s_vis, s_upd, s_more, s_job;
+    const BatchHdr H = *B.hdr;
+    const uint32_t tvox = 1u << (H.lt[0] + H.lt[1] + H.lt[2]);
+    const BatchCtl *ctl = B.ctl + H.once;
+    const uint32_t nheavy = ctl->n_nonempty, nne = nheavy + ctl->n_light;
+    if (blockIdx.x == 0) {
+        // the next batch's counters
+        uint32_t *other = reinterpret_cast<uint32_t *>(B.ctl + (3u - H.once));
+        for (uint32_t j = threadIdx.x; j < sizeof(BatchCtl) / 4; j += kTileBlock) other[j] = 0;
+    }
+    const int32_t shb[3] = {H.lt[1] + H.lt[2] + kKeyLog2, H.lt[2] + kKeyLog2, kKeyLog2};
+    const int32_t ext[3] = {1 << H.lt[0], 1 << H.lt[1], 1 << H.lt[2]};
+    const uint32_t wl = threadIdx.x < 64u ? threadIdx.x : 64u;  // lane of the first wave
+    uint32_t job = blockIdx.x;
+    if (job >= nne) return;
+    const uint32_t nq = gridDim.x < (uint32_t)kQueues ? gridDim.x : (uint32_t)kQueues;
+    const uint32_t queue = blockIdx.x % nq;
+    for (uint32_t v = threadIdx.x; v < tvox; v += kTileBlock) s_keys[v] = kNone;
+    while (job < nne) {
+        const bool from_heavy = job < nheavy;
+        uint32_t g, mb;
+        if (from_heavy) {
+            g = uniform(B.offsets[job]);
+            mb = uniform(B.cursor[job]);
+        } else {
+            const uint4 jb = B.jobs[job - nheavy];
+            g = uniform(jb.x);
+            mb = uniform(jb.y);
+        }
+        TileList *L = &B.lists[g];
+        const unsigned long long head = *reinterpret_cast<const unsigned long long *>(L);  // in one access
+        const uint32_t nseg = uniform((uint32_t)head), total = uniform((uint32_t)(head >> 32));
+        // (a heavy tile is listed twice: whoever took it from the heavy ones does
+        // it, before or after the other looked)
+        if (nseg && (total >= kHeavyTile) == from_heavy) {
+            const MapDev MD = uniform_map(B.maps[mb]);
+            const int4 sens = B.seq_sensor[mb];
+            const int32_t o[3] = {uniform(sens.x), uniform(sens.y), uniform(sens.z)};
+            const int32_t tau = uniform(sens.w);
+            uint32_t cur = 0;
+            uint2 mine = make_uint2(0u, 0u);
+            if (wl < kSegs && wl < nseg) mine = L->seg[wl];
+            if (wl >= 16u && wl < 16u + kChains && nseg > kSegs) cur = L->chain[wl - 16u];
+            if (kStats && threadIdx.x == 0) s_vis = s_upd = 0;
+            const uint32_t t = g - MD.tile_base;
+            const uint32_t tz = t % (uint32_t)MD.nt[2];
+            const uint32_t txy = t / (uint32_t)MD.nt[2];
+            const int32_t t0[3] = {(int32_t)(txy / (uint32_t)MD.nt[1]) << H.lt[0],
+                                   (int32_t)(txy % (uint32_t)MD.nt[1]) << H.lt[1], (int32_t)tz << H.lt[2]};
+            int32_t blo[3];
+            bool cut = false;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                blo[a] = MD.origin[a] + t0[a];
+                cut = cut || t0[a] + (1 << H.lt[a]) > MD.dims[a];
+            }
+            uint32_t visits = 0;
+            bool more = true;
+            while (more) {
+                if (wl < 64u) {
+                    // segment of lane s: s < kSegs of the list, then hop h of chain c
+                    // in lane kSegs + 16 h + c
+                    uint2 sg = mine;
+                    mine = make_uint2(0u, 0u);
+#pragma unroll
+                    for (int h = 0; h < kHops; ++h) {
+                        uint4 nd = make_uint4(0u, 0u, 0u, 0u);
+                        if (cur) nd = B.nodes[cur - 1u];
+                        cur = nd.x;
+                        const int from = (int)wl - (int)kSegs - (int)kChains * h + 16;  // the chain's lane
+                        const uint32_t x = (uint32_t)__shfl((int)nd.y, from & 63), y = (uint32_t)__shfl((int)nd.z, from & 63);
+                        if (from >= 16 && from < 16 + (int)kChains) sg = make_uint2(x, y);
+                    }
+                    uint32_t p = sg.y;
+#pragma unroll
+                    for (int off = 1; off < 64; off <<= 1) {
+                        const uint32_t v = (uint32_t)__shfl_up((int)p, off);
+                        if (wl >= (uint32_t)off) p += v;
+                    }
+                    s_off[wl] = sg.x - (p - sg.y);
+                    s_end[wl] = p;
+                    const bool left = __any(cur != 0u);
+                    if (wl == 0u) s_more = left ? 1u : 0u;
+                }
+                __syncthreads();
+                const uint32_t n = uniform(s_end[63]);
+                more = uniform(s_more) != 0u;
+                for (uint32_t e = threadIdx.x; e < n; e += kTileBlock) {
+                    uint32_t j = 0;
+#pragma unroll
+                    for (uint32_t step = 32; step > 0; step >>= 1) j += s_end[j + step - 1u] <= e ? step : 0u;
+                    const uint32_t at = s_off[j] + e;
+                    visits += walk_entry<kStats, Key>(B.entries[at], B.entries2[at], o, tau, lds_address(s_keys), H, MD,
+                                                      t0, blo, ext, shb, cut);
+                }
+                __syncthreads();
+            }
+            // the list is empty again for the next batch
+            if (wl == 0u) *reinterpret_cast<unsigned long long *>(L) = 0ull;
+            if (nseg > kSegs && wl >= 16u && wl < 16u + kChains) L->chain[wl - 16u] = 0u;
+            const uint32_t updated = merge_tile_direct<kTileBlock, Key>(s_keys, tvox, H, MD, t0, cut);
+            if (kStats) {
+                if (visits) atomicAdd(&s_vis, visits);
+                if (updated) atomicAdd(&s_upd, updated);
+                __syncthreads();
+                if (threadIdx.x == 0) {
+                    B.tile_vis[g] = s_vis;
+                    B.tile_upd[g] = s_upd;
+                }
+            }
+        } else {
+            __syncthreads();  // every wave has read s_job
+        }
+        if (threadIdx.x == 0)
+            s_job = gridDim.x + queue + nq * atomicAdd(&B.ctl[H.once].work[queue * kQueueStride], 1u);
         __syncthreads();
         job = uniform(s_job);
     }
@@ -741,7 +977,7 @@ __global__ __launch_bounds__(256) void k_stats(BatchArrays B)
         B.scan_stats[4 * s + 0] = s_sum[0][0];
         B.scan_stats[4 * s + 1] = s_sum[1][0];
         B.scan_stats[4 * s + 2] = s_sum[2][0];
-        B.scan_stats[4 * s + 3] = B.ctl->overflow;
+        B.scan_stats[4 * s + 3] = (B.ctl + H.once)->overflow;
     }
 }
 
@@ -759,25 +995,30 @@ int32_t max_tiles_per_ray(int32_t tau, const int32_t lt[3]) { return band_tiles_
 namespace {
 
 template <int kBB>
-void launch_bin(bool fill, uint32_t bins, const BatchArrays &B, const InlineDesc &I, hipStream_t stream)
+void launch_bin(int mode, uint32_t bins, const BatchArrays &B, const InlineDesc &I, hipStream_t stream)
 {
-    if (fill) hipLaunchKernelGGL((k_bin<true, kBB, false>), dim3(bins), dim3(kBB), 0, stream, B, I);
-    else if (I.on) hipLaunchKernelGGL((k_bin<false, kBB, true>), dim3(bins), dim3(kBB), 0, stream, B, I);
-    else hipLaunchKernelGGL((k_bin<false, kBB, false>), dim3(bins), dim3(kBB), 0, stream, B, I);
+    const dim3 grid(bins), block(kBB);
+    if (mode == kFillRuns) hipLaunchKernelGGL((k_bin<kFillRuns, kBB, false>), grid, block, 0, stream, B, I);
+    else if (mode == kCount && I.on) hipLaunchKernelGGL((k_bin<kCount, kBB, true>), grid, block, 0, stream, B, I);
+    else if (mode == kCount) hipLaunchKernelGGL((k_bin<kCount, kBB, false>), grid, block, 0, stream, B, I);
+    else if (I.on) hipLaunchKernelGGL((k_bin<kOnce, kBB, true>), grid, block, 0, stream, B, I);
+    else hipLaunchKernelGGL((k_bin<kOnce, kBB, false>), grid, block, 0, stream, B, I);
 }
 
-void launch_bin_any(bool fill, uint32_t bins, uint32_t block, const BatchArrays &B, const InlineDesc &I,
+void launch_bin_any(int mode, uint32_t bins, uint32_t block, const BatchArrays &B, const InlineDesc &I,
                     hipStream_t stream)
 {
-    if (block == 128) launch_bin<128>(fill, bins, B, I, stream);
-    else if (block == 512) launch_bin<512>(fill, bins, B, I, stream);
-    else launch_bin<256>(fill, bins, B, I, stream);
+    if (block == 128) launch_bin<128>(mode, bins, B, I, stream);
+    else if (block == 512) launch_bin<512>(mode, bins, B, I, stream);
+    else launch_bin<256>(mode, bins, B, I, stream);
 }
 
 template <int kTB, bool kStats, typename Key>
 void launch_tile_as(const LaunchCaps &caps, const BatchArrays &B, hipStream_t stream)
 {
-    hipLaunchKernelGGL((k_tile<kTB, kStats, Key>), dim3((uint32_t)caps.tile_grid), dim3(kTB), caps.tile_lds, stream, B);
+    const dim3 grid((uint32_t)caps.tile_grid), block(kTB);
+    if (caps.once) hipLaunchKernelGGL((k_tile_once<kTB, kStats, Key>), grid, block, caps.tile_lds, stream, B);
+    else hipLaunchKernelGGL((k_tile<kTB, kStats, Key>), grid, block, caps.tile_lds, stream, B);
 }
 
 template <int kTB>
@@ -826,10 +1067,14 @@ hipError_t launch_batch(const BatchArrays &B, const LaunchCaps &caps, hipStream_
     const uint32_t bins = caps.blocks > 0 ? caps.blocks : 1u;
     InlineDesc none;
     memset(&none, 0, sizeof(none));
-    launch_bin_any(false, bins, caps.bin_block, B, inl ? *inl : none, stream);
-    hipLaunchKernelGGL(k_alloc, dim3((caps.gtiles + kAllocTiles - 1) / kAllocTiles), dim3(kAllocBlock), 0, stream,
-                       B);
-    launch_bin_any(true, bins, caps.bin_block, B, none, stream);
+    if (caps.once) {
+        launch_bin_any(kOnce, bins, caps.bin_block, B, inl ? *inl : none, stream);
+    } else {
+        launch_bin_any(kCount, bins, caps.bin_block, B, inl ? *inl : none, stream);
+        hipLaunchKernelGGL(k_alloc, dim3((caps.gtiles + kAllocTiles - 1) / kAllocTiles), dim3(kAllocBlock), 0, stream,
+                           B);
+        launch_bin_any(kFillRuns, bins, caps.bin_block, B, none, stream);
+    }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (ev_binned && (e = hipEventRecord(ev_binned, stream)) != hipSuccess) return e;
     // the per-scan counts are a template switch: without them the walk and

@@ -100,8 +100,8 @@ Engine::Engine(hipStream_t stream, int device) : stream_(stream), device_(device
         if (hipEventCreateWithFlags(&pts_ev_[k], hipEventDisableTiming) != hipSuccess) poisoned_ = true;
     }
     if (hipEventCreateWithFlags(&order_ev_, hipEventDisableTiming) != hipSuccess) poisoned_ = true;
-    if (hipMalloc(&ctl_, sizeof(BatchCtl)) != hipSuccess) poisoned_ = true;
-    else if (launch_fill_u32((uint32_t *)ctl_, sizeof(BatchCtl) / 4, 0u, stream_) != hipSuccess) poisoned_ = true;
+    if (hipMalloc(&ctl_, 3 * sizeof(BatchCtl)) != hipSuccess) poisoned_ = true;
+    else if (launch_fill_u32((uint32_t *)ctl_, 3 * sizeof(BatchCtl) / 4, 0u, stream_) != hipSuccess) poisoned_ = true;
 }
 
 Engine::~Engine()
@@ -122,7 +122,7 @@ Engine::~Engine()
     }
     if (order_ev_) (void)hipEventDestroy(order_ev_);
     for (GraphEntry &g : graphs_) (void)hipGraphExecDestroy(g.exec);
-    for (void *p : {inline_dev_, entries_, valid_, stats_, ctl_, pts_dev_})
+    for (void *p : {inline_dev_, entries_, valid_, stats_, ctl_, lists_, pts_dev_})
         if (p) (void)hipFree(p);
     if (arr_ && !arr_external_) (void)hipFree(arr_);
     for (auto &t : prof_ev_)
@@ -314,19 +314,43 @@ tsdf_status Engine::run_chunk(const std::vector<MapRef> &maps, const std::vector
                 nc = std::max(need_c, c_cap_ + c_cap_ / 2);
                 ng = std::max(need_g, g_cap_ + g_cap_ / 2);
             }
-            const size_t bytes = up(5 * nc * sizeof(uint32_t)) + up(ng * sizeof(uint4));
+            size_t bytes = up(5 * nc * sizeof(uint32_t)) + up(ng * sizeof(uint4));
+            lists_in_arr_ = false;
             if (arr_external_) {
                 if (bytes > arr_bytes_) return TSDF_ERANGE;
+                // (the caller's memory fits the finest tiles: with coarser ones
+                // the lists of one binning pass need no memory of their own)
+                lists_in_arr_ = bytes + ng * sizeof(TileList) <= arr_bytes_;
+                lists_at_ = bytes;
+                bytes += lists_in_arr_ ? ng * sizeof(TileList) : 0;
                 ECHK(hipStreamSynchronize(stream_));
             } else if ((st = grow(&arr_, &arr_bytes_, bytes, false)) != TSDF_OK) {
                 return st;
             }
-            ECHK(launch_fill_u32((uint32_t *)arr_, (int64_t)(bytes / 4), 0u, stream_));
+            arr_clear_ = bytes;  // once all memory is there (growing waits for the stream)
             c_cap_ = nc;
             g_cap_ = ng;
         }
     }
-    if ((st = grow(&entries_, &entries_cap_, need_entries * 2 * sizeof(uint4), false)) != TSDF_OK) return st;
+    // One binning pass where each map has one scan: a ray is walked once on the
+    // grid of tiles, without counts and runs, and a call is two launches instead
+    // of four (scans of 16 and 128 rows of 1024 points 24.6 and 44 -> 17 and 33
+    // us, one of 3 M points 134 -> 102, 32 small ones into 32 maps 117 -> 102).
+    // A tile busy in several slots reads its entries slot by slot, in runs. The
+    // nodes are 2/3 more memory, so that the largest scans, and any where it is
+    // short, take the two passes.
+    const uint32_t emit = (uint32_t)max_tiles_per_ray(tau_max, lt);
+    bool once = S == 1 && nblocks > 0 && nblocks <= kOnceBlocks && nblocks * bb * emit < ((uint64_t)1 << 31);
+    if (once) {
+        // per block bb emit entries of two records, and its nodes
+        const size_t records = (size_t)nblocks * (2 * bb * emit + nodes_per_block(bb, emit));
+        st = grow(&entries_, &entries_cap_, records * sizeof(uint4), false);
+        if (st == TSDF_OK && !lists_in_arr_) st = grow(&lists_, &lists_cap_, gtiles * sizeof(TileList), true);
+        if (st != TSDF_OK && st != TSDF_ENOMEM) return st;
+        once = st == TSDF_OK;
+        if (!once) (void)hipGetLastError();  // the failed allocation's
+    }
+    if (!once && (st = grow(&entries_, &entries_cap_, need_entries * 2 * sizeof(uint4), false)) != TSDF_OK) return st;
     if ((st = grow(&valid_, &valid_cap_, cap_blocks * sizeof(uint32_t), false)) != TSDF_OK) return st;
     if ((st = grow(&stats_, &stats_cap_, cap_scans * 4 * sizeof(uint32_t), false)) != TSDF_OK) return st;
 
@@ -374,6 +398,8 @@ tsdf_status Engine::run_chunk(const std::vector<MapRef> &maps, const std::vector
     hdr->cap = (uint32_t)std::min<size_t>(entries_cap_ / (2 * sizeof(uint4)), 0xffffffffu);
     hdr->want_stats = stats ? 1u : 0u;
     hdr->bin_block = bb;
+    hdr->emit = emit;
+    hdr->once = once ? once_ : 0u;
     memcpy(h + L.maps, md.data(), nmaps * sizeof(MapDev));
     ScanDev *sd = (ScanDev *)(h + L.scans);
     uint32_t *bs = (uint32_t *)(h + L.block_scan);
@@ -408,6 +434,7 @@ tsdf_status Engine::run_chunk(const std::vector<MapRef> &maps, const std::vector
     hdr->G = plan.G;
     hdr->key_shift = plan.key_shift;
     caps.key32 = plan.key_shift ? 1u : 0u;
+    caps.once = once ? 1u : 0u;
     caps.tile_lds = plan.lds;
     caps.tile_grid = shape.tile_grid > 0 ? shape.tile_grid : plan.grid;
     InlineDesc I;
@@ -450,11 +477,20 @@ tsdf_status Engine::run_chunk(const std::vector<MapRef> &maps, const std::vector
     B.tile_vis = arr + 3 * c_cap_;
     B.tile_upd = arr + 4 * c_cap_;
     B.jobs = (uint4 *)((char *)arr_ + up(5 * c_cap_ * 4));
+    // (split by the capacity, not by this batch's need: captured launches are
+    // keyed by these addresses)
+    const size_t records = entries_cap_ / sizeof(uint4), half = once ? records / (3 * emit + 2) * emit : records / 2;
     B.entries = (uint4 *)entries_;
-    B.entries2 = B.entries + entries_cap_ / (2 * sizeof(uint4));
+    B.entries2 = B.entries + half;
+    B.nodes = once ? B.entries2 + half : nullptr;
     B.valid_part = (uint32_t *)valid_;
     B.scan_stats = (uint32_t *)stats_;
     B.ctl = (BatchCtl *)ctl_;
+    B.lists = (TileList *)(lists_in_arr_ ? (void *)((char *)arr_ + lists_at_) : lists_);
+    if (once) once_ = 3u - once_;
+
+    if (arr_clear_) ECHK(launch_fill_u32((uint32_t *)arr_, (int64_t)(arr_clear_ / 4), 0u, stream_));
+    arr_clear_ = 0;
 
     // order after earlier work on each map's own stream
     for (int32_t j = 0; j < nmaps; ++j) {

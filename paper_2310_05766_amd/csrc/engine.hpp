@@ -96,13 +96,19 @@ private:
     size_t arr_bytes_ = 0;
     bool arr_external_ = false;
     size_t c_cap_ = 0, g_cap_ = 0;
+    size_t arr_clear_ = 0;  // bytes still to be cleared
     void *entries_ = nullptr;
     size_t entries_cap_ = 0;  // bytes
     void *valid_ = nullptr;
     size_t valid_cap_ = 0;  // bytes
     void *stats_ = nullptr;
     size_t stats_cap_ = 0;  // bytes
-    void *ctl_ = nullptr;
+    void *ctl_ = nullptr;  // [3]: of two binning passes, and of one in turn
+    uint32_t once_ = 1;    // the latter's next
+    bool lists_in_arr_ = false;  // the lists of one binning pass: arr_ + lists_at_, or
+    size_t lists_at_ = 0;
+    void *lists_ = nullptr;
+    size_t lists_cap_ = 0;  // bytes
     // host points staging
     void *pts_dev_ = nullptr;
     size_t pts_dev_cap_ = 0;

@@ -61,6 +61,9 @@ struct BatchHdr {
     uint32_t want_stats;
     uint32_t bin_block;  // binning threads per block (one ray each)
     uint32_t key_shift;  // of the tile pass's 32-bit keys; 0: 64-bit keys
+    // one binning pass (TileList): its counters, ctl[1] or ctl[2] in turn (0:
+    // count, runs and fill, with ctl[0]); entries that a point can give
+    uint32_t once, emit;
 };
 
 // The descriptors of a batch of one scan, handed to the first binning
@@ -88,6 +91,23 @@ struct BatchCtl {
     uint32_t work[kQueues * kQueueStride];  // next job of queue q: work[q * kQueueStride]
 };
 
+// The entries of a tile where each map has one scan (one binning pass): every
+// binning block writes its entries, tile by tile, into a region of its own and
+// adds a segment of them to each tile it met. The first kSegs segments lie in
+// the list itself, the others in kChains chains of nodes in turn, which one wave
+// follows together. All zero between batches (segments may hold anything).
+constexpr uint32_t kSegs = 7, kChains = 16;
+struct TileList {
+    uint32_t nseg, total;   // segments, entries (one 64-bit counter)
+    uint2 seg[kSegs];       // first entry, entries
+    uint32_t chain[kChains];  // first node + 1, 0: none
+};
+static_assert(sizeof(TileList) == 128, "a line per tile");
+// Nodes (next + 1, first entry, entries, -) of a block: one per slot of its
+// table, one per entry that found the table full.
+__host__ __device__ inline uint32_t nodes_per_block(uint32_t bin_block, uint32_t emit) { return bin_block * (2u + emit); }
+constexpr uint64_t kOnceBlocks = 65536;  // binning blocks of a batch that is binned in one pass, at most
+
 // Device addresses of one engine (all inside buffers the engine owns).
 struct BatchArrays {
     BatchHdr *hdr;
@@ -106,6 +126,8 @@ struct BatchArrays {
     uint32_t *valid_part;  // [nblocks] points with a ray per binning block
     uint32_t *scan_stats;  // [nscans * 4] updated, valid, visits, overflow
     BatchCtl *ctl;
+    TileList *lists;       // [gtiles], one binning pass
+    uint4 *nodes;          // [nblocks * nodes_per_block], one binning pass
 };
 
 // The point of thread t of a scan's block b. A block takes a patch of the
@@ -146,6 +168,7 @@ struct LaunchCaps {
     uint32_t tile_block;  // tile workgroup size: 256 or 512
     uint32_t stats;       // per-scan counts wanted: k_stats runs only then
     uint32_t key32;       // 32-bit keys in the tile pass
+    uint32_t once;        // one binning pass
 };
 
 // The tile pass's LDS and grid for a tiling, S sequence slots, a truncation and

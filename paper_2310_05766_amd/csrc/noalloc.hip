@@ -101,6 +101,8 @@ size_t noalloc_layout(void *base, uint32_t nblocks, uint32_t gtiles, uint32_t ca
     A.scan_stats = (uint32_t *)take(4 * 4);
     A.entries = (uint4 *)take((size_t)cap * sizeof(uint4));
     A.entries2 = (uint4 *)take((size_t)cap * sizeof(uint4));
+    A.lists = nullptr;
+    A.nodes = nullptr;
     if (B) *B = A;
     return off;
 }
@@ -218,6 +220,7 @@ extern "C" tsdf_status tsdf_integrate_scan_noalloc(tsdf_map *m, const float *xyz
         const TilePlan plan = tile_plan(lt, 1, m->d.tau_q10, n_points, shape.tile_block, g_cu[m->device]);
         hdr.G = plan.G;
         hdr.key_shift = plan.key_shift;
+        hdr.once = hdr.emit = 0;
         LaunchCaps caps;
         caps.blocks = (uint32_t)nblocks;
         caps.gtiles = md.ntot;
@@ -226,6 +229,7 @@ extern "C" tsdf_status tsdf_integrate_scan_noalloc(tsdf_map *m, const float *xyz
         caps.tile_block = (uint32_t)shape.tile_block;
         caps.stats = stats ? 1u : 0u;
         caps.key32 = plan.key_shift ? 1u : 0u;
+        caps.once = 0;
         caps.tile_lds = plan.lds;
         caps.tile_grid = m->tile_grid > 0 ? m->tile_grid : plan.grid;
         if (launch_noalloc_setup(B, hdr, md, sd, m->stream) != hipSuccess ||

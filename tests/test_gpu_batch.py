@@ -411,3 +411,46 @@ def test_automatic_tilings(maps, per_map, n):
         assert same(g, o, dims)
         g.close()
         o.close()
+
+
+@pytest.mark.parametrize("case", ["one_tile", "small_tiles", "long_bands", "several_maps", "many_blocks", "wide_keys"])
+def test_one_binning_pass(case):
+    """Batches of one scan per map, binned in one pass: tiles with more
+    segments than their list and the first chains hold (every block meets the
+    same few tiles) and heavy ones, blocks that meet more tiles than their
+    table has slots, rays with more tiles than a block lists, several maps,
+    many blocks, 64-bit keys; counts and maps are the oracle's, twice in a row
+    (the lists are empty again)."""
+    from paper_2310_05766_amd.tsdf import integrate_batch
+    dims, origin, tau, extent, maps, n, tiling = (41, 39, 35), (-20, -19, -17), 5120, 2.0, 1, 20000, None
+    if case == "one_tile":
+        extent, n = 0.35, 70000
+    elif case == "small_tiles":
+        dims, origin, tau, extent, tiling, n = (120, 117, 64), (-60, -58, -32), 10240, 5.0, (3, 3, 3), 6000
+    elif case == "long_bands":
+        tau, tiling, n = 32767, (3, 3, 3), 3000
+    elif case == "several_maps":
+        maps, n = 5, 7001
+    elif case == "many_blocks":
+        n = (1 << 20) + 1
+    else:
+        tau, n = 32767, 40000
+    gms = [gpu_map(dims, origin, 0.1, tau, 64) for _ in range(maps)]
+    oms = [oracle.OracleMap(dims, origin, 0.1, tau, 64) for _ in range(maps)]
+    for k in range(2):
+        items, ost = [], []
+        for m in range(maps):
+            if tiling:
+                gms[m].set_tiling(tiling)
+            x = synth.fuzz_scan((101, k, m), n - 1000 * m, extent_m=extent, nan_frac=0.02)
+            p = synth.fuzz_pose((102, k, m), 0.3)
+            items.append((gms[m], x, p))
+            ost.append(oms[m].integrate(x, p))
+        if maps == 1:
+            assert gms[0].integrate(items[0][1], items[0][2], stats=True) == ost[0]
+        else:
+            assert integrate_batch(items, stats=True) == ost
+    for g, o in zip(gms, oms):
+        assert same(g, o, dims)
+        g.close()
+        o.close()
