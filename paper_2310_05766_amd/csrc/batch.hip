@@ -20,7 +20,8 @@
 //   k_tile        per busy tile, per sequence slot in order: every ray jumps
 //                 to its first voxel in the tile (exact crossing counts) and
 //                 walks the tile; candidates meet in LDS; then the merge
-//   k_stats       per-scan counts, when asked for
+//   k_stats       per-scan counts, when asked for (one binning pass: the tile
+//                 pass adds them up)
 //
 // Where each map has one scan, binning is one pass (the engine says when):
 //   k_bin<once>   the walk once; each block writes its entries, tile by tile,
@@ -135,6 +136,9 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
         for (int q = 0; q < kQueues; ++q) B.ctl->work[q * kQueueStride] = 0;
     }
     if (blockIdx.x >= H.nblocks) return;
+    if (kMode == kOnce && H.want_stats)
+        for (uint32_t j = blockIdx.x * kBinBlock + threadIdx.x; j < (uint32_t)H.nscans * kStatWords; j += H.nblocks * kBinBlock)
+            B.scan_stats[j] = 0;
     for (uint32_t j = threadIdx.x; j < kHashSlots; j += kBinBlock) {
         h_key[j] = 0;
         h_cnt[j] = 0;
@@ -833,6 +837,20 @@ __global__ __launch_bounds__(kTileBlock) __attribute__((amdgpu_waves_per_eu(kTil
         uint32_t *other = reinterpret_cast<uint32_t *>(B.ctl + (3u - H.once));
         for (uint32_t j = threadIdx.x; j < sizeof(BatchCtl) / 4; j += kTileBlock) other[j] = 0;
     }
+    if (kStats) {
+        // a scan's valid points, over its binning blocks
+        for (uint32_t s = blockIdx.x; s < (uint32_t)H.nscans; s += gridDim.x) {
+            const ScanDev &SD = B.scans[s];
+            const uint32_t nb = (uint32_t)((SD.n + H.bin_block - 1) / H.bin_block);
+            if (threadIdx.x == 0) s_vis = 0;
+            __syncthreads();
+            uint32_t val = 0;
+            for (uint32_t b = threadIdx.x; b < nb; b += kTileBlock) val += B.valid_part[SD.block0 + b];
+            if (val) atomicAdd(&s_vis, val);
+            __syncthreads();
+            if (threadIdx.x == 0) B.scan_stats[s * kStatWords + 2u] = s_vis;
+        }
+    }
     const int32_t shb[3] = {H.lt[1] + H.lt[2] + kKeyLog2, H.lt[2] + kKeyLog2, kKeyLog2};
     const int32_t ext[3] = {1 << H.lt[0], 1 << H.lt[1], 1 << H.lt[2]};
     const uint32_t wl = threadIdx.x < 64u ? threadIdx.x : 64u;  // lane of the first wave
@@ -928,10 +946,10 @@ __global__ __launch_bounds__(kTileBlock) __attribute__((amdgpu_waves_per_eu(kTil
                 if (visits) atomicAdd(&s_vis, visits);
                 if (updated) atomicAdd(&s_upd, updated);
                 __syncthreads();
-                if (threadIdx.x == 0) {
-                    B.tile_vis[g] = s_vis;
-                    B.tile_upd[g] = s_upd;
-                }
+                if (threadIdx.x == 0)
+                    atomicAdd(reinterpret_cast<unsigned long long *>(
+                                  &B.scan_stats[mb * kStatWords + g % kStatParts * 16u]),  // (scan k is map k's)
+                              (unsigned long long)s_vis << 32 | s_upd);
             }
         } else {
             __syncthreads();  // every wave has read s_job
@@ -977,7 +995,7 @@ __global__ __launch_bounds__(256) void k_stats(BatchArrays B)
         B.scan_stats[4 * s + 0] = s_sum[0][0];
         B.scan_stats[4 * s + 1] = s_sum[1][0];
         B.scan_stats[4 * s + 2] = s_sum[2][0];
-        B.scan_stats[4 * s + 3] = (B.ctl + H.once)->overflow;
+        B.scan_stats[4 * s + 3] = B.ctl->overflow;
     }
 }
 
@@ -1083,7 +1101,7 @@ hipError_t launch_batch(const BatchArrays &B, const LaunchCaps &caps, hipStream_
     else launch_tile<256>(caps, B, stream);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (ev_tiles && (e = hipEventRecord(ev_tiles, stream)) != hipSuccess) return e;
-    if (caps.stats) hipLaunchKernelGGL(k_stats, dim3(caps.scans > 0 ? caps.scans : 1u), dim3(256), 0, stream, B);
+    if (caps.stats && !caps.once) hipLaunchKernelGGL(k_stats, dim3(caps.scans > 0 ? caps.scans : 1u), dim3(256), 0, stream, B);
     return hipGetLastError();
 }
 

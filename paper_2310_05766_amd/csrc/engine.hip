@@ -114,6 +114,7 @@ Engine::~Engine()
     for (int k = 0; k < 2; ++k) {
         if (desc_host_[k]) (void)hipHostFree(desc_host_[k]);
         if (pts_host_[k]) (void)hipHostFree(pts_host_[k]);
+        if (k == 0 && stats_host_) (void)hipHostFree(stats_host_);
         if (desc_ev_[k]) (void)hipEventDestroy(desc_ev_[k]);
         if (desc_used_[k]) (void)hipEventDestroy(desc_used_[k]);
         if (desc_dev_[k]) (void)hipFree(desc_dev_[k]);
@@ -352,7 +353,9 @@ tsdf_status Engine::run_chunk(const std::vector<MapRef> &maps, const std::vector
     }
     if (!once && (st = grow(&entries_, &entries_cap_, need_entries * 2 * sizeof(uint4), false)) != TSDF_OK) return st;
     if ((st = grow(&valid_, &valid_cap_, cap_blocks * sizeof(uint32_t), false)) != TSDF_OK) return st;
-    if ((st = grow(&stats_, &stats_cap_, cap_scans * 4 * sizeof(uint32_t), false)) != TSDF_OK) return st;
+    const size_t stat_words = once ? kStatWords : 4, stat_bytes = cap_scans * stat_words * sizeof(uint32_t);
+    if ((st = grow(&stats_, &stats_cap_, stat_bytes, false)) != TSDF_OK) return st;
+    if (stats && (st = grow(&stats_host_, &stats_host_cap_, stat_bytes, false, true)) != TSDF_OK) return st;
 
     // host points: pinned staging, one copy to the device
     std::vector<const float *> xyz(nscans);
@@ -538,15 +541,26 @@ tsdf_status Engine::run_chunk(const std::vector<MapRef> &maps, const std::vector
         }
     }
     if (stats) {
-        std::vector<uint32_t> host(nscans * 4);
-        ECHK(hipMemcpyAsync(host.data(), stats_, nscans * 4 * sizeof(uint32_t), hipMemcpyDeviceToHost, stream_));
+        ECHK(hipMemcpyAsync(stats_host_, stats_, nscans * stat_words * sizeof(uint32_t), hipMemcpyDeviceToHost, stream_));
         ECHK(hipStreamSynchronize(stream_));
         for (size_t k = 0; k < nscans; ++k) {
-            if (host[4 * k + 3]) return fail();  // entry buffer overflow: cannot happen by its sizing
+            const uint32_t *host = (const uint32_t *)stats_host_ + k * stat_words;
             stats[k].points_in = scans[b + k].n;
-            stats[k].points_valid = host[4 * k + 1];
-            stats[k].visits = host[4 * k + 2];
-            stats[k].voxels_updated = host[4 * k + 0];
+            if (once) {
+                uint32_t updated = 0, visits = 0;
+                for (uint32_t j = 0; j < kStatParts; ++j) {
+                    updated += host[16 * j];
+                    visits += host[16 * j + 1];
+                }
+                stats[k].points_valid = host[2];
+                stats[k].visits = visits;
+                stats[k].voxels_updated = updated;
+                continue;
+            }
+            if (host[3]) return fail();  // entry buffer overflow: cannot happen by its sizing
+            stats[k].points_valid = host[1];
+            stats[k].visits = host[2];
+            stats[k].voxels_updated = host[0];
         }
     }
     return TSDF_OK;
