@@ -29,7 +29,7 @@
 //                 list of each tile it met; who adds a tile's first one lists
 //                 the tile as busy
 //   k_tile_once   k_tile for these lists
-// (128 x 1024 points: 12.6 us, where count, runs and fill took 6.4 + 5.7 + 11.2.)
+// (128 x 1024 points: 11.7 us, where count, runs and fill took 6.4 + 5.7 + 11.2.)
 #include <string.h>
 
 #include <algorithm>
@@ -74,25 +74,29 @@ enum { kCount = 0, kFillRuns = 1, kOnce = 2 };
 // pass then starts the longest tiles early instead of ending on one of them.
 constexpr uint32_t kHeavyTile = 2048;
 
-// Adds a block's segment of n entries to a tile's list. A tile is listed as
-// busy by its first segment (`first` is then set, and the caller does it), and
-// once more, among the heavy ones, by the segment that makes it heavy: the tile
-// pass takes it from there and skips it among the others.
-__device__ __forceinline__ void add_segment(const BatchArrays &B, BatchCtl *ctl, uint32_t tile, uint32_t map,
-                                            uint32_t pos, uint32_t n, uint32_t node, bool &first)
+// Adds a block's segment of n entries to a tile's list, in two steps, so that
+// other work can go between the atomic and its result: the segments and entries
+// listed before, and the segment's place. A tile is listed as busy by its first
+// segment (finish_segment is then true, and the caller does it), and once more,
+// among the heavy ones, by the segment that makes it heavy: the tile pass takes
+// it from there and skips it among the others.
+__device__ __forceinline__ unsigned long long begin_segment(const BatchArrays &B, uint32_t tile, uint32_t n)
+{
+    return atomicAdd(reinterpret_cast<unsigned long long *>(&B.lists[tile]), (unsigned long long)n << 32 | 1ull);
+}
+__device__ __forceinline__ bool finish_segment(const BatchArrays &B, BatchCtl *ctl, unsigned long long old, uint32_t tile,
+                                               uint32_t map, uint32_t pos, uint32_t n, uint32_t node)
 {
     TileList *L = &B.lists[tile];
-    const unsigned long long old =
-        atomicAdd(reinterpret_cast<unsigned long long *>(L), (unsigned long long)n << 32 | 1ull);
     const uint32_t k = (uint32_t)old, total = (uint32_t)(old >> 32);
     if (k < kSegs) L->seg[k] = make_uint2(pos, n);
     else B.nodes[node] = make_uint4(atomicExch(&L->chain[(k - kSegs) % kChains], node + 1u), pos, n, 0u);
-    first = k == 0u;
     if (total < kHeavyTile && total + n >= kHeavyTile) {
         const uint32_t h = atomicAdd(&ctl->n_nonempty, 1u);
         B.offsets[h] = tile;
         B.cursor[h] = map;
     }
+    return k == 0u;
 }
 
 // kInline (the first pass only): the batch is one scan whose descriptors are
@@ -218,9 +222,9 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
                 const uint32_t x = atomicAdd(&s_extra, 1u), pos = region + kBinBlock * H.emit - 1u - x;
                 B.entries[pos] = make_uint4((uint32_t)i, (uint32_t)q[0], (uint32_t)q[1], (uint32_t)q[2]);
                 B.entries2[pos] = entry_ray(R, cpack, seq);
-                bool first;
-                add_segment(B, ctl, key, (uint32_t)SD.map, pos, 1u, node0 + 2u * kBinBlock + x, first);
-                if (first) B.jobs[atomicAdd(&ctl->n_light, 1u)] = make_uint4(key, (uint32_t)SD.map, 0u, 0u);
+                if (finish_segment(B, ctl, begin_segment(B, key, 1u), key, (uint32_t)SD.map, pos, 1u,
+                                   node0 + 2u * kBinBlock + x))
+                    B.jobs[atomicAdd(&ctl->n_light, 1u)] = make_uint4(key, (uint32_t)SD.map, 0u, 0u);
             } else if (kFill) {  // table full or very long band: straight to the tile's run
                 const uint32_t pos = atomicAdd(&B.cursor[key], 1u);
                 if (pos < H.cap) {
@@ -236,6 +240,25 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
         }
         active = walk_next_event(W, t_in, typ_in);
     }
+    const auto write_records = [&]() {
+        // each record carries the point's fixed-point position, so the tile pass
+        // needs neither the point nor the pose again
+        const uint4 rec = make_uint4((uint32_t)i, (uint32_t)q[0], (uint32_t)q[1], (uint32_t)q[2]);
+        // the entries listed in LDS: an entry that found the table full went
+        // straight to its run and left its LDS place unwritten
+        const int nl = ne < kMaxEmit ? ne : kMaxEmit;
+        for (int k = 0; k < nl; ++k) {
+            if (!((listed >> k) & 1u)) continue;
+            const uint32_t sc = s_slot[k * kBinBlock + threadIdx.x];
+            const uint32_t pos = h_base[sc & 1023u] + s_rank[k * kBinBlock + threadIdx.x];
+            if (kMode == kOnce || pos < H.cap) {
+                B.entries[pos] = rec;
+                B.entries2[pos] = entry_ray(R, counts_7to8(sc >> 10), seq);
+            } else {
+                atomicOr(&B.ctl->overflow, 1u);
+            }
+        }
+    };
     if (kFirst && valid) atomicAdd(&s_valid, 1u);
     __syncthreads();
     if (kMode == kOnce) {
@@ -253,9 +276,15 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
         const uint32_t at = region + p - c0 - c1;
         h_base[j0] = at;
         h_base[j0 + 1u] = at + c0;
-        bool f0 = false, f1 = false;
-        if (c0) add_segment(B, ctl, h_key[j0] - 1u, (uint32_t)SD.map, at, c0, node0 + j0, f0);
-        if (c1) add_segment(B, ctl, h_key[j0 + 1u] - 1u, (uint32_t)SD.map, at + c0, c1, node0 + j0 + 1u, f1);
+        const uint32_t k0 = h_key[j0] - 1u, k1 = h_key[j0 + 1u] - 1u;
+        unsigned long long old0 = 0, old1 = 0;
+        if (c0) old0 = begin_segment(B, k0, c0);
+        if (c1) old1 = begin_segment(B, k1, c1);
+        __syncthreads();
+        // the records go out while the atomics are under way
+        write_records();
+        const bool f0 = c0 && finish_segment(B, ctl, old0, k0, (uint32_t)SD.map, at, c0, node0 + j0);
+        const bool f1 = c1 && finish_segment(B, ctl, old1, k1, (uint32_t)SD.map, at + c0, c1, node0 + j0 + 1u);
         // one atomic for all tiles that this block lists
         uint32_t r = 0;
         if (f0 || f1) r = atomicAdd(&s_new, (f0 ? 1u : 0u) + (f1 ? 1u : 0u));
@@ -265,9 +294,10 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
             B.valid_part[blockIdx.x] = s_valid;
         }
         __syncthreads();
-        if (f0) B.jobs[s_job + r++] = make_uint4(h_key[j0] - 1u, (uint32_t)SD.map, 0u, 0u);
-        if (f1) B.jobs[s_job + r] = make_uint4(h_key[j0 + 1u] - 1u, (uint32_t)SD.map, 0u, 0u);
-    } else {
+        if (f0) B.jobs[s_job + r++] = make_uint4(k0, (uint32_t)SD.map, 0u, 0u);
+        if (f1) B.jobs[s_job + r] = make_uint4(k1, (uint32_t)SD.map, 0u, 0u);
+        return;
+    }
     // one global atomic per distinct key of this block
     for (uint32_t j = threadIdx.x; j < kHashSlots; j += kBinBlock) {
         const uint32_t k1 = h_key[j];
@@ -276,29 +306,12 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
         if (kFill) h_base[j] = atomicAdd(&B.cursor[k1 - 1u], c);
         else atomicAdd(&B.counts[k1 - 1u], c);
     }
-    }
     if (!kFill) {
         if (threadIdx.x == 0) B.valid_part[blockIdx.x] = s_valid;
         return;
     }
     __syncthreads();
-    // each record carries the point's fixed-point position, so the tile pass
-    // needs neither the point nor the pose again
-    const uint4 rec = make_uint4((uint32_t)i, (uint32_t)q[0], (uint32_t)q[1], (uint32_t)q[2]);
-    // the entries listed in LDS: an entry that found the table full went
-    // straight to its run and left its LDS place unwritten
-    const int nl = ne < kMaxEmit ? ne : kMaxEmit;
-    for (int k = 0; k < nl; ++k) {
-        if (!((listed >> k) & 1u)) continue;
-        const uint32_t sc = s_slot[k * kBinBlock + threadIdx.x];
-        const uint32_t pos = h_base[sc & 1023u] + s_rank[k * kBinBlock + threadIdx.x];
-        if (pos < H.cap) {
-            B.entries[pos] = rec;
-            B.entries2[pos] = entry_ray(R, counts_7to8(sc >> 10), seq);
-        } else {
-            atomicOr(&B.ctl->overflow, 1u);
-        }
-    }
+    write_records();
 }
 
 // Map slot of a global tile: the last map whose first tile is <= g.
