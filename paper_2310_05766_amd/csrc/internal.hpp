@@ -344,14 +344,25 @@ struct LinesXfer {
     uint32_t ny, nz;  // the box
 };
 hipError_t launch_pack_lines(const LinesXfer &A, uint32_t line0, uint32_t lines, int16_t *out, hipStream_t stream);
-// Whole chunks of a window whose dims are multiples of 64 (chunks_dev[j].lo:
-// the chunk's global origin), staged chunk by chunk in the store's layout
+// Whole chunks of a window whose dims are multiples of 64 (lo[j]: the chunk's
+// global origin), staged chunk by chunk in the store's layout
 // (stage + j * 2 * kChunkVox: sdf, then w). pack clears the window voxels and
-// sets flags[j] (zero beforehand) when chunk j holds a non-zero voxel.
-hipError_t launch_pack_chunks(const BoxXfer *chunks_dev, int32_t nchunks, int16_t *sdf, int16_t *w,
-                              const int32_t dims[3], int16_t *stage, uint32_t *flags, hipStream_t stream);
-hipError_t launch_unpack_chunks(const BoxXfer *chunks_dev, int32_t nchunks, int16_t *sdf, int16_t *w,
-                                const int32_t dims[3], const int16_t *stage, hipStream_t stream);
+// sets flags[j] (pinned host memory, zero beforehand) when chunk j holds a
+// non-zero voxel. move copies staged chunks at[j] to (out) or from their pinned
+// host buffers host[j].
+constexpr int kShiftChunks = 16;  // one chunk layer of a 512 x 512 x 128 window
+struct ChunkList {
+    int32_t lo[kShiftChunks][3];
+};
+struct ChunkPtrs {
+    int16_t *host[kShiftChunks];
+    int32_t at[kShiftChunks];
+};
+hipError_t launch_pack_chunks(const ChunkList &C, int32_t nchunks, int16_t *sdf, int16_t *w, const int32_t dims[3],
+                              int16_t *stage, uint32_t *flags, hipStream_t stream);
+hipError_t launch_move_chunks(const ChunkPtrs &P, int32_t nchunks, int16_t *stage, bool out, hipStream_t stream);
+hipError_t launch_unpack_chunks(const ChunkList &C, int32_t nchunks, int16_t *sdf, int16_t *w, const int32_t dims[3],
+                                const int16_t *stage, hipStream_t stream);
 hipError_t launch_unpack_boxes(const BoxXfer *boxes_dev, int32_t nboxes, int64_t max_box_vox, int16_t *sdf,
                                int16_t *w, const int32_t dims[3], const int16_t *stage_sdf,
                                const int16_t *stage_w, hipStream_t stream);

@@ -186,8 +186,7 @@ constexpr uint64_t kCrewBytes = (uint64_t)4 << 20;
 constexpr int kCrewHelpers = 7;
 
 // Staging of whole-chunk shifts: kShiftChunks chunks out and kShiftChunks in
-// per round trip (one chunk layer of a 512 x 512 x 128 window).
-constexpr int kShiftChunks = 16;
+// per round trip.
 
 // The stream whose copies run beside the map's own kernels.
 tsdf_status ensure_copy_stream(tsdf_map *m)
@@ -202,21 +201,14 @@ tsdf_status ensure_copy_stream(tsdf_map *m)
 
 tsdf_status ensure_chunk_stage(tsdf_map *m)
 {
-    if (m->cstage_dev && m->cflags_dev && m->cflags_host && m->clist_dev && m->clist_host && m->copy_stream &&
-        m->copy_done)
-        return TSDF_OK;
+    if (m->cstage_dev && m->cflags_host && m->copy_stream && m->copy_done) return TSDF_OK;
     if (m->cstage_dev) return TSDF_ENOMEM;  // an earlier attempt failed part way
     const size_t bytes = (size_t)2 * kShiftChunks * 2 * kChunkVox * sizeof(int16_t);
     if (hipMalloc(&m->cstage_dev, bytes) != hipSuccess) {
         m->cstage_dev = nullptr;
         return TSDF_ENOMEM;
     }
-    bool ok = hipMalloc(&m->cflags_dev, kShiftChunks * sizeof(uint32_t)) == hipSuccess;
-    ok = ok && hipHostMalloc((void **)&m->cflags_host, kShiftChunks * sizeof(uint32_t), hipHostMallocDefault) ==
-                   hipSuccess;
-    ok = ok && hipMalloc(&m->clist_dev, 2 * kShiftChunks * sizeof(BoxXfer)) == hipSuccess;
-    ok = ok && hipHostMalloc((void **)&m->clist_host, 2 * kShiftChunks * sizeof(BoxXfer), hipHostMallocDefault) ==
-                   hipSuccess;
+    bool ok = hipHostMalloc((void **)&m->cflags_host, kShiftChunks * sizeof(uint32_t), hipHostMallocDefault) == hipSuccess;
     ok = ok && ensure_copy_stream(m) == TSDF_OK;
     ok = ok && hipEventCreateWithFlags(&m->copy_done, hipEventDisableTiming) == hipSuccess;
     return ok ? TSDF_OK : TSDF_ENOMEM;
@@ -247,10 +239,7 @@ void release(tsdf_map *m)
     if (m->reg_result) (void)hipHostFree(m->reg_result);
     if (m->copy_stream) (void)hipStreamSynchronize(m->copy_stream);
     if (m->cstage_dev) (void)hipFree(m->cstage_dev);
-    if (m->cflags_dev) (void)hipFree(m->cflags_dev);
     if (m->cflags_host) (void)hipHostFree(m->cflags_host);
-    if (m->clist_dev) (void)hipFree(m->clist_dev);
-    if (m->clist_host) (void)hipHostFree(m->clist_host);
     if (m->copy_done) (void)hipEventDestroy(m->copy_done);
     if (m->copy_stream) (void)hipStreamDestroy(m->copy_stream);
     m->store.clear();
@@ -1191,16 +1180,16 @@ tsdf_status tsdf_shift(tsdf_map *m, const int32_t new_origin[3])
         if (st != TSDF_OK) return st;
     }
     int16_t *cs_out = m->cstage_dev, *cs_in = m->cstage_dev + (size_t)kShiftChunks * 2 * kChunkVox;
-    const size_t chunk_bytes = (size_t)2 * kChunkVox * sizeof(int16_t);
     // the first round of entering chunks goes to the device on the copy
     // stream right away, while the leaving chunks are packed and copied out
     auto copy_in = [&](size_t e0) -> tsdf_status {
         const size_t n = std::min<size_t>(kShiftChunks, efull.size() - e0);
+        ChunkPtrs P;
         for (size_t j = 0; j < n; ++j) {
-            const Chunk &c = m->store.find(key_of(efull[e0 + j].lo))->second;
-            HIPCHK(m, hipMemcpyAsync(cs_in + j * 2 * kChunkVox, c.buf, chunk_bytes, hipMemcpyHostToDevice,
-                                     m->copy_stream));
+            P.host[j] = m->store.find(key_of(efull[e0 + j].lo))->second.buf;
+            P.at[j] = (int32_t)j;
         }
+        HIPCHK(m, launch_move_chunks(P, (int32_t)n, cs_in, false, m->copy_stream));
         HIPCHK(m, hipEventRecord(m->copy_done, m->copy_stream));
         return TSDF_OK;
     };
@@ -1210,23 +1199,17 @@ tsdf_status tsdf_shift(tsdf_map *m, const int32_t new_origin[3])
     //    chunks that hold an observed voxel, one copy out per such chunk
     for (size_t l0 = 0; l0 < lfull.size(); l0 += kShiftChunks) {
         const int32_t n = (int32_t)std::min<size_t>(kShiftChunks, lfull.size() - l0);
+        ChunkList list;
         for (int32_t j = 0; j < n; ++j) {
-            BoxXfer &x = m->clist_host[j];
-            for (int a = 0; a < 3; ++a) {
-                x.lo[a] = lfull[l0 + j].lo[a];
-                x.ext[a] = kChunk;
-            }
-            x.off = 0;
+            for (int a = 0; a < 3; ++a) list.lo[j][a] = lfull[l0 + j].lo[a];
+            m->cflags_host[j] = 0;
         }
-        HIPCHK(m, hipMemcpyAsync(m->clist_dev, m->clist_host, (size_t)n * sizeof(BoxXfer), hipMemcpyHostToDevice,
-                                 m->stream));
-        HIPCHK(m, launch_fill_u32(m->cflags_dev, n, 0u, m->stream));
         HIPCHK(m, prof_start(m, TSDF_KERNEL_PACK));
-        HIPCHK(m, launch_pack_chunks(m->clist_dev, n, m->sdf, m->w, m->d.dims, cs_out, m->cflags_dev, m->stream));
+        HIPCHK(m, launch_pack_chunks(list, n, m->sdf, m->w, m->d.dims, cs_out, m->cflags_host, m->stream));
         HIPCHK(m, prof_stop(m, TSDF_KERNEL_PACK));
-        HIPCHK(m, hipMemcpyAsync(m->cflags_host, m->cflags_dev, (size_t)n * sizeof(uint32_t), hipMemcpyDeviceToHost,
-                                 m->stream));
         HIPCHK(m, hipStreamSynchronize(m->stream));
+        ChunkPtrs P;
+        int32_t kept = 0;
         for (int32_t j = 0; j < n; ++j) {
             const ChunkKey ck = key_of(lfull[l0 + j].lo);
             auto it = m->store.find(ck);
@@ -1242,13 +1225,18 @@ tsdf_status tsdf_shift(tsdf_map *m, const int32_t new_origin[3])
             if (it == m->store.end()) {
                 Chunk c;
                 c.buf = chunk_take(m);
-                if (!c.buf) return TSDF_ENOMEM;
+                if (!c.buf) {  // those before it are kept
+                    HIPCHK(m, launch_move_chunks(P, kept, cs_out, true, m->stream));
+                    HIPCHK(m, hipStreamSynchronize(m->stream));
+                    return TSDF_ENOMEM;
+                }
                 it = m->store.emplace(ck, c).first;
             }
-            HIPCHK(m, hipMemcpyAsync(it->second.buf, cs_out + (size_t)j * 2 * kChunkVox, chunk_bytes,
-                                     hipMemcpyDeviceToHost, m->stream));
+            P.host[kept] = it->second.buf;
+            P.at[kept++] = j;
         }
-        HIPCHK(m, hipStreamSynchronize(m->stream));
+        HIPCHK(m, launch_move_chunks(P, kept, cs_out, true, m->stream));
+        if (kept) HIPCHK(m, hipStreamSynchronize(m->stream));
     }
 
     // 2. other leaving pieces: pack (and clear) -> host staging -> store
@@ -1289,19 +1277,12 @@ tsdf_status tsdf_shift(tsdf_map *m, const int32_t new_origin[3])
     for (size_t e0 = 0; e0 < efull.size(); e0 += kShiftChunks) {
         const int32_t n = (int32_t)std::min<size_t>(kShiftChunks, efull.size() - e0);
         if (e0 > 0 && (st = copy_in(e0)) != TSDF_OK) return st;
-        BoxXfer *list = m->clist_host + kShiftChunks;
-        for (int32_t j = 0; j < n; ++j) {
-            for (int a = 0; a < 3; ++a) {
-                list[j].lo[a] = efull[e0 + j].lo[a];
-                list[j].ext[a] = kChunk;
-            }
-            list[j].off = 0;
-        }
-        HIPCHK(m, hipMemcpyAsync(m->clist_dev + kShiftChunks, list, (size_t)n * sizeof(BoxXfer),
-                                 hipMemcpyHostToDevice, m->stream));
+        ChunkList list;
+        for (int32_t j = 0; j < n; ++j)
+            for (int a = 0; a < 3; ++a) list.lo[j][a] = efull[e0 + j].lo[a];
         HIPCHK(m, hipStreamWaitEvent(m->stream, m->copy_done, 0));
         HIPCHK(m, prof_start(m, TSDF_KERNEL_UNPACK));
-        HIPCHK(m, launch_unpack_chunks(m->clist_dev + kShiftChunks, n, m->sdf, m->w, m->d.dims, cs_in, m->stream));
+        HIPCHK(m, launch_unpack_chunks(list, n, m->sdf, m->w, m->d.dims, cs_in, m->stream));
         HIPCHK(m, prof_stop(m, TSDF_KERNEL_UNPACK));
         HIPCHK(m, hipStreamSynchronize(m->stream));
         for (int32_t j = 0; j < n; ++j) {

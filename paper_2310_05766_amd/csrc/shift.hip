@@ -68,28 +68,35 @@ __global__ __launch_bounds__(kBlock) void k_unpack(const BoxXfer *__restrict__ b
 // both [x][y][z] in chunk order: the host store's own layout, so a chunk
 // crosses the host link as one contiguous copy. Each thread moves 8 voxels
 // (16 bytes) of each array per step. k_pack_chunks also clears the window
-// voxels and sets flag[j] when any voxel of chunk j is non-zero.
+// voxels and sets flag[j], in host memory, when any voxel of chunk j is non-zero.
+//
+// k_move_chunks copies chunks between staging and their buffers in pinned host
+// memory, all of a round in one launch, bound by the link: six chunks of 1 MiB
+// take 114 us out (55 GB/s) and 128 in (49). A copy command per chunk took 19 us
+// out and 24 in and left the link idle for 10 us and more after each; flags and
+// lists that went by copies of their own took 30 us more per shift. One chunk
+// layer out of a 512 x 512 x 128 window and back: 480 -> 373 us.
 constexpr int kChunkUnits = kChunk * kChunk * kChunk / 8;  // 16-byte units per array
 
-__device__ __forceinline__ int64_t chunk_row_slot(const BoxXfer &b, int32_t u, int32_t nx, int32_t ny, int32_t nz)
+__device__ __forceinline__ int64_t chunk_row_slot(const int32_t lo[3], int32_t u, int32_t nx, int32_t ny, int32_t nz)
 {
     const int32_t x = u >> 9, y = (u >> 3) & 63, zq = u & 7;
     // slots of the chunk's rows: floor_mod(c0 + i, n) = floor_mod(c0, n) + i (n a multiple of 64)
-    const int32_t sx = fmod_pos(b.lo[0], nx) + x, sy = fmod_pos(b.lo[1], ny) + y;
-    const int32_t sz = fmod_pos(b.lo[2], nz) + 8 * zq;
+    const int32_t sx = fmod_pos(lo[0], nx) + x, sy = fmod_pos(lo[1], ny) + y;
+    const int32_t sz = fmod_pos(lo[2], nz) + 8 * zq;
     return ((int64_t)sx * ny + sy) * nz + sz;
 }
 
-__global__ __launch_bounds__(kBlock) void k_pack_chunks(const BoxXfer *__restrict__ boxes, int16_t *__restrict__ sdf,
+__global__ __launch_bounds__(kBlock) void k_pack_chunks(ChunkList C, int16_t *__restrict__ sdf,
                                                         int16_t *__restrict__ w, int32_t nx, int32_t ny, int32_t nz,
                                                         int16_t *__restrict__ stage, uint32_t *__restrict__ flags)
 {
-    const BoxXfer b = boxes[blockIdx.y];
+    const int32_t lo[3] = {C.lo[blockIdx.y][0], C.lo[blockIdx.y][1], C.lo[blockIdx.y][2]};
     int4 *dst_s = reinterpret_cast<int4 *>(stage + (int64_t)blockIdx.y * 2 * kChunkVox);
     int4 *dst_w = dst_s + kChunkUnits;
     bool any = false;
     for (int32_t u = blockIdx.x * kBlock + threadIdx.x; u < kChunkUnits; u += gridDim.x * kBlock) {
-        const int64_t slot = chunk_row_slot(b, u, nx, ny, nz);
+        const int64_t slot = chunk_row_slot(lo, u, nx, ny, nz);
         int4 *ps = reinterpret_cast<int4 *>(sdf + slot);
         int4 *pw = reinterpret_cast<int4 *>(w + slot);
         const int4 vs = *ps, vw = *pw;
@@ -99,21 +106,39 @@ __global__ __launch_bounds__(kBlock) void k_pack_chunks(const BoxXfer *__restric
         *pw = make_int4(0, 0, 0, 0);
         any |= (vs.x | vs.y | vs.z | vs.w | vw.x | vw.y | vw.z | vw.w) != 0;
     }
-    if (__any(any) && (threadIdx.x & 63u) == 0) atomicOr(&flags[blockIdx.y], 1u);
+    if (__syncthreads_or(any) && threadIdx.x == 0) flags[blockIdx.y] = 1u;
 }
 
-__global__ __launch_bounds__(kBlock) void k_unpack_chunks(const BoxXfer *__restrict__ boxes, int16_t *__restrict__ sdf,
+__global__ __launch_bounds__(kBlock) void k_unpack_chunks(ChunkList C, int16_t *__restrict__ sdf,
                                                           int16_t *__restrict__ w, int32_t nx, int32_t ny, int32_t nz,
                                                           const int16_t *__restrict__ stage)
 {
-    const BoxXfer b = boxes[blockIdx.y];
+    const int32_t lo[3] = {C.lo[blockIdx.y][0], C.lo[blockIdx.y][1], C.lo[blockIdx.y][2]};
     const int4 *src_s = reinterpret_cast<const int4 *>(stage + (int64_t)blockIdx.y * 2 * kChunkVox);
     const int4 *src_w = src_s + kChunkUnits;
     for (int32_t u = blockIdx.x * kBlock + threadIdx.x; u < kChunkUnits; u += gridDim.x * kBlock) {
-        const int64_t slot = chunk_row_slot(b, u, nx, ny, nz);
+        const int64_t slot = chunk_row_slot(lo, u, nx, ny, nz);
         *reinterpret_cast<int4 *>(sdf + slot) = src_s[u];
         *reinterpret_cast<int4 *>(w + slot) = src_w[u];
     }
+}
+
+// 16-byte units of a thread, all requested before any is stored (1, 4, 8, 16, 32:
+// 148, 143, 146, 128, 123 us in, 114, 114, 114, 114, 130 out).
+constexpr int kMoveUnits = 16;
+
+__global__ __launch_bounds__(kBlock) void k_move_chunks(ChunkPtrs P, int16_t *__restrict__ stage, bool out)
+{
+    const uint32_t u0 = blockIdx.x * kBlock * kMoveUnits + threadIdx.x;
+    int4 *host = reinterpret_cast<int4 *>(P.host[blockIdx.y]);
+    int4 *dev = reinterpret_cast<int4 *>(stage + (int64_t)P.at[blockIdx.y] * 2 * kChunkVox);
+    const int4 *from = out ? dev : host;
+    int4 *to = out ? host : dev;
+    int4 v[kMoveUnits];
+#pragma unroll
+    for (int k = 0; k < kMoveUnits; ++k) v[k] = from[u0 + k * kBlock];
+#pragma unroll
+    for (int k = 0; k < kMoveUnits; ++k) to[u0 + k * kBlock] = v[k];
 }
 
 // A thread per voxel (neighbouring lanes along z, across the ends of lines):
@@ -159,21 +184,30 @@ hipError_t launch_pack_lines(const LinesXfer &A, uint32_t line0, uint32_t lines,
     return hipGetLastError();
 }
 
-hipError_t launch_pack_chunks(const BoxXfer *chunks_dev, int32_t nchunks, int16_t *sdf, int16_t *w,
-                              const int32_t dims[3], int16_t *stage, uint32_t *flags, hipStream_t stream)
+hipError_t launch_pack_chunks(const ChunkList &C, int32_t nchunks, int16_t *sdf, int16_t *w, const int32_t dims[3],
+                              int16_t *stage, uint32_t *flags, hipStream_t stream)
 {
     if (nchunks <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_pack_chunks, dim3(32, (uint32_t)nchunks), dim3(kBlock), 0, stream, chunks_dev, sdf, w,
-                       dims[0], dims[1], dims[2], stage, flags);
+    hipLaunchKernelGGL(k_pack_chunks, dim3(32, (uint32_t)nchunks), dim3(kBlock), 0, stream, C, sdf, w, dims[0], dims[1],
+                       dims[2], stage, flags);
     return hipGetLastError();
 }
 
-hipError_t launch_unpack_chunks(const BoxXfer *chunks_dev, int32_t nchunks, int16_t *sdf, int16_t *w,
-                                const int32_t dims[3], const int16_t *stage, hipStream_t stream)
+hipError_t launch_move_chunks(const ChunkPtrs &P, int32_t nchunks, int16_t *stage, bool out, hipStream_t stream)
 {
     if (nchunks <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_unpack_chunks, dim3(32, (uint32_t)nchunks), dim3(kBlock), 0, stream, chunks_dev, sdf, w,
-                       dims[0], dims[1], dims[2], stage);
+    constexpr uint32_t kBlocks = 2 * kChunkUnits / (kBlock * kMoveUnits);
+    static_assert(kBlocks * kBlock * kMoveUnits == 2 * kChunkUnits, "whole blocks to a chunk");
+    hipLaunchKernelGGL(k_move_chunks, dim3(kBlocks, (uint32_t)nchunks), dim3(kBlock), 0, stream, P, stage, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_unpack_chunks(const ChunkList &C, int32_t nchunks, int16_t *sdf, int16_t *w, const int32_t dims[3],
+                                const int16_t *stage, hipStream_t stream)
+{
+    if (nchunks <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_unpack_chunks, dim3(32, (uint32_t)nchunks), dim3(kBlock), 0, stream, C, sdf, w, dims[0], dims[1],
+                       dims[2], stage);
     return hipGetLastError();
 }
 

@@ -378,3 +378,29 @@ def test_fused_transform_chain_crafted_rounding():
     assert not np.array_equal(off.readback(*o)[0], om.readback(*o)[0])
     for m in (gm, om, off):
         m.close()
+
+
+@pytest.mark.parametrize("nc,by", [((1, 1, 1), (64, 0, 0)), ((3, 3, 2), (192, 0, 0)), ((3, 3, 2), (-64, 64, 0)),
+                                   ((4, 2, 2), (0, 0, 128)), ((2, 2, 2), (64, -64, 64))])
+def test_chunk_layers_out_and_back(nc, by):
+    """Shifts of whole chunks: one chunk, exactly a round of them, more than a
+    round, chunks without an observed voxel among them, and shifts where chunks
+    leave and enter together; map and store are the oracle's at every stage."""
+    dims = tuple(64 * c for c in nc)
+    origin = tuple(-64 * (c // 2) for c in nc)
+    away = tuple(origin[a] + by[a] for a in range(3))
+    om = oracle.OracleMap(dims, origin, 0.1, 3072, 64)
+    gm = gpu_map(dims, origin, 0.1, 3072, 64)
+    for step, to in enumerate((away, origin, away, origin)):
+        xyz = synth.fuzz_scan((121, step), 3000, extent_m=2.0, nan_frac=0.02)
+        pose = synth.fuzz_pose((122, step), 0.5)
+        gm.integrate(xyz, pose)
+        om.integrate(xyz, pose)
+        gm.shift(to)
+        om.shift(to)
+        lo = tuple(min(origin[a], away[a]) for a in range(3))
+        hi = tuple(max(origin[a], away[a]) + dims[a] for a in range(3))
+        g, r = gm.readback(lo, hi), om.readback(lo, hi)
+        assert np.array_equal(g[0], r[0]) and np.array_equal(g[1], r[1]), step
+    gm.close()
+    om.close()
