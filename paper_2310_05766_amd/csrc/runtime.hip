@@ -1180,20 +1180,27 @@ tsdf_status tsdf_shift(tsdf_map *m, const int32_t new_origin[3])
         if (st != TSDF_OK) return st;
     }
     int16_t *cs_out = m->cstage_dev, *cs_in = m->cstage_dev + (size_t)kShiftChunks * 2 * kChunkVox;
-    // the first round of entering chunks goes to the device on the copy
-    // stream right away, while the leaving chunks are packed and copied out
-    auto copy_in = [&](size_t e0) -> tsdf_status {
+    // the first round of entering chunks goes to the device on the copy stream
+    // right away, while the leaving chunks are packed and copied out: by a copy
+    // command each, which the copy engine carries out beside the kernel that
+    // writes to the host (16 chunks out and 16 in: 0.54 ms, 0.71 with kernels both
+    // ways); where no whole chunk leaves, by one kernel (6 chunks: 128 us, 144 and
+    // the gaps by commands)
+    auto copy_in = [&](size_t e0, bool commands) -> tsdf_status {
         const size_t n = std::min<size_t>(kShiftChunks, efull.size() - e0);
         ChunkPtrs P;
         for (size_t j = 0; j < n; ++j) {
             P.host[j] = m->store.find(key_of(efull[e0 + j].lo))->second.buf;
             P.at[j] = (int32_t)j;
+            if (commands)
+                HIPCHK(m, hipMemcpyAsync(cs_in + j * 2 * kChunkVox, P.host[j], (size_t)2 * kChunkVox * sizeof(int16_t),
+                                         hipMemcpyHostToDevice, m->copy_stream));
         }
-        HIPCHK(m, launch_move_chunks(P, (int32_t)n, cs_in, false, m->copy_stream));
+        if (!commands) HIPCHK(m, launch_move_chunks(P, (int32_t)n, cs_in, false, m->copy_stream));
         HIPCHK(m, hipEventRecord(m->copy_done, m->copy_stream));
         return TSDF_OK;
     };
-    if (!efull.empty() && (st = copy_in(0)) != TSDF_OK) return st;
+    if (!efull.empty() && (st = copy_in(0, !lfull.empty())) != TSDF_OK) return st;
 
     // 1. whole leaving chunks: pack (and clear) on the device, flags of the
     //    chunks that hold an observed voxel, one copy out per such chunk
@@ -1276,7 +1283,7 @@ tsdf_status tsdf_shift(tsdf_map *m, const int32_t new_origin[3])
     //    device (copy stream); unpacked once there, then dropped from the store
     for (size_t e0 = 0; e0 < efull.size(); e0 += kShiftChunks) {
         const int32_t n = (int32_t)std::min<size_t>(kShiftChunks, efull.size() - e0);
-        if (e0 > 0 && (st = copy_in(e0)) != TSDF_OK) return st;
+        if (e0 > 0 && (st = copy_in(e0, false)) != TSDF_OK) return st;
         ChunkList list;
         for (int32_t j = 0; j < n; ++j)
             for (int a = 0; a < 3; ++a) list.lo[j][a] = efull[e0 + j].lo[a];

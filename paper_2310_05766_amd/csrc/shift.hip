@@ -75,7 +75,8 @@ __global__ __launch_bounds__(kBlock) void k_unpack(const BoxXfer *__restrict__ b
 // take 114 us out (55 GB/s) and 128 in (49). A copy command per chunk took 19 us
 // out and 24 in and left the link idle for 10 us and more after each; flags and
 // lists that went by copies of their own took 30 us more per shift. One chunk
-// layer out of a 512 x 512 x 128 window and back: 480 -> 373 us.
+// layer out of a 512 x 512 x 128 window and back: 384 -> 340 us; 16 chunks out
+// and 16 in 0.60 -> 0.54 ms.
 constexpr int kChunkUnits = kChunk * kChunk * kChunk / 8;  // 16-byte units per array
 
 __device__ __forceinline__ int64_t chunk_row_slot(const int32_t lo[3], int32_t u, int32_t nx, int32_t ny, int32_t nz)
