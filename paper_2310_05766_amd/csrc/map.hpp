@@ -39,6 +39,7 @@ struct tsdf_map {
     // device triangles on their way out (two pieces at most)
     void *mesh_dev = nullptr, *mesh_host = nullptr, *mesh_tris = nullptr;
     size_t mesh_dev_cap = 0, mesh_host_cap = 0, mesh_tris_cap = 0;
+    bool meshed = false;  // a mesh has left without staging
     // shift / readback / mesh staging
     int16_t *stage_dev = nullptr;  // [2][stage_cap]
     int16_t *stage_host = nullptr;

@@ -124,7 +124,9 @@ MapRef map_ref(const tsdf_map *m)
     return r;
 }
 
-tsdf_status ensure_stage(tsdf_map *m, int64_t vox, int32_t boxes)
+// Staging for vox voxels, in pinned host memory and, where `device`, as much on
+// the device (results that leave a kernel's own buffer need only the former).
+tsdf_status ensure_stage(tsdf_map *m, int64_t vox, int32_t boxes, bool device = true)
 {
     if (vox > m->stage_cap) {
         HIPCHK(m, hipStreamSynchronize(m->stream));
@@ -133,11 +135,16 @@ tsdf_status ensure_stage(tsdf_map *m, int64_t vox, int32_t boxes)
         m->stage_dev = nullptr;
         m->stage_host = nullptr;
         m->stage_cap = 0;
-        if (hipMalloc(&m->stage_dev, (size_t)vox * 2 * sizeof(int16_t)) != hipSuccess) return TSDF_ENOMEM;
         if (hipHostMalloc((void **)&m->stage_host, (size_t)vox * 2 * sizeof(int16_t), hipHostMallocDefault) !=
-            hipSuccess)
+            hipSuccess) {
+            m->stage_host = nullptr;
             return TSDF_ENOMEM;
+        }
         m->stage_cap = vox;
+    }
+    if (device && !m->stage_dev && hipMalloc(&m->stage_dev, (size_t)m->stage_cap * 2 * sizeof(int16_t)) != hipSuccess) {
+        m->stage_dev = nullptr;
+        return TSDF_ENOMEM;
     }
     if (boxes > m->boxes_cap) {
         HIPCHK(m, hipStreamSynchronize(m->stream));
@@ -184,6 +191,8 @@ void chunk_give(tsdf_map *m, Chunk &c)
 // bytes of a call on: below, the threads' start costs as much as they save.
 constexpr uint64_t kCrewBytes = (uint64_t)4 << 20;
 constexpr int kCrewHelpers = 7;
+// Below this a map's first mesh takes no staging.
+constexpr uint64_t kFirstBytes = (uint64_t)32 << 20;
 
 // Staging of whole-chunk shifts: kShiftChunks chunks out and kShiftChunks in
 // per round trip.
@@ -894,8 +903,27 @@ tsdf_status tsdf_mesh(tsdf_map *m, const int32_t lo[3], const int32_t hi[3], flo
     // slots on the copy stream.
     constexpr size_t kPieceSlots = 16;
     constexpr uint64_t kTri = 9 * sizeof(float);
-    tsdf_status st =
-        ensure_stage(m, std::max<int64_t>({m->stage_cap, 16 * kChunkVox, (int64_t)(most * kTri + 16) * kSlots / 4}), 0);
+    const int64_t stage = std::max<int64_t>(16 * kChunkVox, (int64_t)(most * kTri + 16) * kSlots / 4);
+    if (m->stage_cap < stage && (total * kTri < kCrewBytes || (total * kTri < kFirstBytes && !m->meshed))) {
+        // no staging yet, whose 16 MiB of pinned memory cost more than a
+        // millisecond: few triangles, and a map's first ones up to kFirstBytes,
+        // take one launch and one copy (0.5 MB: first 381 -> 256 us, later 126 ->
+        // 106; 5 MB: first 0.95 -> 0.58 ms, later, with staging, 0.37)
+        m->meshed = true;
+        if (total * kTri > m->mesh_tris_cap) {
+            if (m->mesh_tris) HIPCHK(m, hipFree(m->mesh_tris));
+            m->mesh_tris = nullptr;
+            m->mesh_tris_cap = 0;
+            if (hipMalloc(&m->mesh_tris, total * kTri) != hipSuccess) return TSDF_ENOMEM;
+            m->mesh_tris_cap = total * kTri;
+        }
+        HIPCHK(m, hipMemcpyAsync(unit_base, base, ((size_t)units + 1) * 8, hipMemcpyHostToDevice, m->stream));
+        HIPCHK(m, launch_mesh_emit(A, row_tris, unit_base, 0, units, 0, (float *)m->mesh_tris, m->stream));
+        HIPCHK(m, hipMemcpyAsync(tris, m->mesh_tris, total * kTri, hipMemcpyDeviceToHost, m->stream));
+        HIPCHK(m, hipStreamSynchronize(m->stream));
+        return TSDF_OK;
+    }
+    tsdf_status st = ensure_stage(m, std::max<int64_t>(m->stage_cap, stage), 0, false);
     if (st == TSDF_OK) st = ensure_copy_stream(m);
     if (st != TSDF_OK) return st;
     const uint64_t slot = slot_bytes(m), slot_tris = slot / kTri, piece_bytes = kPieceSlots * slot;

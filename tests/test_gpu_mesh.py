@@ -117,3 +117,21 @@ def test_mesh_through_staging_slots(dims):
     assert g.shape == o.shape and np.array_equal(g, o)
     gm.close()
     om.close()
+
+
+@pytest.mark.parametrize("dims", [(12, 14, 63), (40, 44, 63)])
+def test_mesh_with_and_without_staging(dims):
+    """A map's first mesh leaves without staging, a later one of more than 4 MB
+    through it, and a small one after that through what is there."""
+    origin = (-11, 5, -40)
+    gm, om = _random_pair(dims, origin, 0.92, 7)
+    hi = tuple(origin[a] + dims[a] for a in range(3))
+    o, part = om.mesh(origin, hi), om.mesh(origin, (origin[0] + 5, origin[1] + 6, hi[2]))
+    for k in range(3):
+        g = gm.mesh(origin, hi)
+        say(dims, k, g.shape, g.nbytes)
+        assert g.shape == o.shape and np.array_equal(g, o)
+    g = gm.mesh(origin, (origin[0] + 5, origin[1] + 6, hi[2]))
+    assert g.shape == part.shape and np.array_equal(g, part)
+    gm.close()
+    om.close()
