@@ -146,7 +146,7 @@ tsdf_status tsdf_integrate_scan_noalloc(tsdf_map *m, const float *xyz_dev, int64
 tsdf_status tsdf_batch_release(void *hip_stream);
 
 /* Launch mode of every integration (process wide). on = 1 (the default):
- * each launch shape is captured once in a hipGraph (its five kernels, grid
+ * each launch shape is captured once in a hipGraph (its kernels, grid
  * sizes rounded up to powers of two) and replayed; the kernels read the
  * batch's real sizes from device memory. on = 0: direct kernel launches.
  * Results are identical in both modes. */

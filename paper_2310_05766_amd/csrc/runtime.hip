@@ -1225,7 +1225,6 @@ tsdf_status tsdf_shift(tsdf_map *m, const int32_t new_origin[3])
                                          hipMemcpyHostToDevice, m->copy_stream));
         }
         if (!commands) HIPCHK(m, launch_move_chunks(P, (int32_t)n, cs_in, false, m->copy_stream));
-        HIPCHK(m, hipEventRecord(m->copy_done, m->copy_stream));
         return TSDF_OK;
     };
     if (!efull.empty() && (st = copy_in(0, !lfull.empty())) != TSDF_OK) return st;
@@ -1315,6 +1314,9 @@ tsdf_status tsdf_shift(tsdf_map *m, const int32_t new_origin[3])
         ChunkList list;
         for (int32_t j = 0; j < n; ++j)
             for (int a = 0; a < 3; ++a) list.lo[j][a] = efull[e0 + j].lo[a];
+        // (recorded only now: where the two streams share a hardware queue, its
+        // wait for the copies would hold up the leaving chunks' kernels)
+        HIPCHK(m, hipEventRecord(m->copy_done, m->copy_stream));
         HIPCHK(m, hipStreamWaitEvent(m->stream, m->copy_done, 0));
         HIPCHK(m, prof_start(m, TSDF_KERNEL_UNPACK));
         HIPCHK(m, launch_unpack_chunks(list, n, m->sdf, m->w, m->d.dims, cs_in, m->stream));
