@@ -311,7 +311,7 @@ def interp_leg(torch, synth, TsdfMap, n_scans: int = 10, reps: int = 5):
             "atomic_roofline": {"bound": ATOMIC_BOUND, "probe_atomics_per_s": probe,
                                 "issued_atomics_per_s": aps, "visits_per_s": vps,
                                 "frac": aps / probe["window_key_volume"],
-                                "note": "issued atomics counted on the device (one per visit on this path)"}}
+                                "note": "issued atomics counted on the device (a block merges its candidates before it issues any; 32-bit where keys fit)"}}
 
 
 def carve_leg(torch, synth, TsdfMap, n_scans: int = 50, reps: int = 3):
@@ -356,8 +356,8 @@ def carve_leg(torch, synth, TsdfMap, n_scans: int = 50, reps: int = 3):
             "atomic_roofline": {"bound": ATOMIC_BOUND, "probe_atomics_per_s": probe,
                                 "issued_atomics_per_s": aps, "visits_per_s": vps,
                                 "frac": aps / probe["window_key_volume"],
-                                "note": "issued atomics counted on the device; the lockstep check and the read "
-                                        "before the atomic leave many visits without one"}}
+                                "note": "issued atomics counted on the device; free-space visits mark voxels "
+                                        "without one, and a block merges its band's candidates"}}
 
 
 def uneven_batch_leg(torch, synth, reps: int = 3):
