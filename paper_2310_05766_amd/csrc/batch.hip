@@ -1,10 +1,10 @@
 // Batched integration (FeatSense, arXiv 2310.05766, Sec. VI): any number of
-// registered scans, into any number of maps, in one pass of five kernels.
+// registered scans, into any number of maps, in one pass of two to five kernels.
 //
 // Each map window is cut into tiles of 2^lt voxels per axis (window-relative
 // coordinates). The per-scan volume V of the min-tsdf step never reaches HBM:
 // a workgroup owns one tile, keeps its candidate keys (|s|, point index, s)
-// in LDS and resolves them with ds_min_u64 (order independent, one winner per
+// in LDS and resolves them with ds_min (order independent, one winner per
 // voxel), then applies the averaging step, Eq. (1) and Eq. (2), to the tile.
 // When several scans of one map share a batch, the tile's SDF and weights
 // stay in LDS while its workgroup applies those scans one after another, in

@@ -92,10 +92,10 @@ struct Guard {
 // the call. A larger tile has fewer fixed costs per scan, a smaller one holds
 // more scans' keys at once; the tile pass's time, us (tiles of 8x8x8, 16x8x8,
 // 16x16x8, 16x16x16 voxels):
-//   1 scan    32 maps, 16 x 1024 points each     184 148 129 106
-//             4 maps, 64 x 1024                   69  61  59  55
-//             1 map, 128 x 1024                   52  47  44  45
-//             1 map, 16 x 1024                    26  25  24  26
+//   1 scan    32 maps, 16 x 1024 points each     153 122 110  96
+//             4 maps, 64 x 1024                   61  62  60  61
+//             1 map, 128 x 1024                   41  36  33  37
+//             1 map, 16 x 1024                    17  17  16  19
 //   2 scans   1 map, 128 x 1024                   76  69  68  75
 //   4 scans   16 maps, uneven                    665 605 567 608
 //             4 maps, 64 x 1024                  128 120 129 145
