@@ -9,8 +9,7 @@ g++ compiles csrc/ray.hpp with its one inline-asm minimum replaced.
   rounding, with perturbed reciprocal estimates;
 * free_walk_check: carving's free-space walk, clipped to random boxes and to
   the carving scan's slabs, against the oracle's segment voxels and keys
-  (the oracle is compiled with gcc and linked in);
-* free_run_check: the near free walk of carving against the free-space walk."""
+  (the oracle is compiled with gcc and linked in)."""
 import os
 import shutil
 import subprocess
