@@ -278,8 +278,13 @@ __global__ __launch_bounds__(kKeyRays * kFillLanes) void k_interp_scan(InterpSca
             tt = (double)(dd - rr * rr);  // |D|^2 - r^2, in [0, 2r]
         }
         // (a fill reaches 64 voxels at most, and less the nearer the ray: its
-        // height grows with the voxel's distance, at most |D| + tau along)
-        const double top = fills ? fmin((double)P.dq * (R.r + (double)P.rp.tau + 2048.0) * 0x1p-30 + 3.0, 66.0) : 0.0;
+        // height grows with the voxel's distance along the ray, len = rdiv((c - o)
+        // . D, r). The band ends (1 + tau / r) |D| from the sensor, a centre lies
+        // within 888 units of it, and |D|^2 <= r^2 + 2r, so len is at most
+        // (r + tau)(1 + 2 / r) + 888 sqrt(3): a few units from the sensor much
+        // more than r + tau)
+        const double reach = (R.r + (double)P.rp.tau) * (1.0 + 4.0 * R.inv_r2) + 2048.0;
+        const double top = fills ? fmin((double)P.dq * reach * 0x1p-30 + 3.0, 66.0) : 0.0;
         Walk W;
         walk_init(R, W);
         bool more = !band_outside(P, R, (int32_t)top);

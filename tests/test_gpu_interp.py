@@ -155,3 +155,29 @@ def test_interpolation_with_far_sensors():
     assert same(gm, om, dims)
     gm.close()
     om.close()
+
+
+@pytest.mark.parametrize("D", [(1, 1, 1), (1, 0, 1), (1, 1, -1), (2, 1, 2), (3, 3, 2), (20, 20, 20), (700, 400, 650)])
+def test_fills_of_points_at_the_sensor(D):
+    """Points a few units (1/1024 voxel) from the sensor under a large tau: the
+    band reaches sqrt(3) tau, a voxel's length along the ray 3 tau, and its fill
+    64 voxels beyond the band. Windows that lie past the band, 40 and more
+    voxels from it, on the side of the fill."""
+    spec = (1.024, 32767, 64)  # a unit is a millimetre
+    up = 1 if D[2] > 0 else -1
+    hit = 0
+    for z in (40, 56, 72, 80):
+        dims, origin = (80, 80, 16), (-8, -8, z if up > 0 else -z - 16)
+        om = oracle.OracleMap(dims, origin, *spec)
+        gm = gpu_map(dims, origin, *spec)
+        om.set_interpolation(44.9, 1)
+        gm.set_interpolation(44.9, 1)
+        xyz = (np.array([D]) * 0.001).astype(np.float32)
+        say("a point", D, "units from the sensor, window from z", origin[2])
+        ost = om.integrate(xyz, np.eye(4))
+        assert gm.integrate(xyz, np.eye(4), stats=True) == ost, z
+        assert same(gm, om, dims)
+        hit += ost["visits"]
+        gm.close()
+        om.close()
+    assert hit > 0
