@@ -139,6 +139,8 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
         B.ctl->overflow = 0;
         for (int q = 0; q < kQueues; ++q) B.ctl->work[q * kQueueStride] = 0;
     }
+    const uint32_t turn = kMode == kOnce ? B.ctl->next_turn : 0u;
+    if (kMode == kOnce && blockIdx.x == 0 && threadIdx.x == 0) B.ctl->turn = turn;
     if (blockIdx.x >= H.nblocks) return;
     if (kMode == kOnce && H.want_stats)
         for (uint32_t j = blockIdx.x * kBinBlock + threadIdx.x; j < (uint32_t)H.nscans * kStatWords; j += H.nblocks * kBinBlock)
@@ -184,7 +186,7 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
     // one pass: this block's region of the entries, its nodes, the counters
     const uint32_t region = kMode == kOnce ? blockIdx.x * kBinBlock * H.emit : 0u;
     const uint32_t node0 = kMode == kOnce ? blockIdx.x * nodes_per_block(kBinBlock, H.emit) : 0u;
-    BatchCtl *ctl = kMode == kOnce ? B.ctl + H.once : B.ctl;
+    BatchCtl *ctl = kMode == kOnce ? B.ctl + 1u + turn : B.ctl;
     int ne = 0;
     uint32_t listed = 0;  // fill: bit k set when entry k was listed in LDS (not sent straight to its run)
     double t_in = -1.0;  // event that entered the current tile (none for the first)
@@ -843,11 +845,13 @@ __global__ __launch_bounds__(kTileBlock) __attribute__((amdgpu_waves_per_eu(kTil
     __shared__ uint32_t s_vis, s_upd, s_more, s_job;
     const BatchHdr H = *B.hdr;
     const uint32_t tvox = 1u << (H.lt[0] + H.lt[1] + H.lt[2]);
-    const BatchCtl *ctl = B.ctl + H.once;
+    const uint32_t turn = B.ctl->turn;
+    BatchCtl *ctl = B.ctl + 1u + turn;
     const uint32_t nheavy = ctl->n_nonempty, nne = nheavy + ctl->n_light;
     if (blockIdx.x == 0) {
         // the next batch's counters
-        uint32_t *other = reinterpret_cast<uint32_t *>(B.ctl + (3u - H.once));
+        uint32_t *other = reinterpret_cast<uint32_t *>(B.ctl + (2u - turn));
+        if (threadIdx.x == 0) B.ctl->next_turn = 1u - turn;
         for (uint32_t j = threadIdx.x; j < sizeof(BatchCtl) / 4; j += kTileBlock) other[j] = 0;
     }
     if (kStats) {
@@ -968,7 +972,7 @@ __global__ __launch_bounds__(kTileBlock) __attribute__((amdgpu_waves_per_eu(kTil
             __syncthreads();  // every wave has read s_job
         }
         if (threadIdx.x == 0)
-            s_job = gridDim.x + queue + nq * atomicAdd(&B.ctl[H.once].work[queue * kQueueStride], 1u);
+            s_job = gridDim.x + queue + nq * atomicAdd(&ctl->work[queue * kQueueStride], 1u);
         __syncthreads();
         job = uniform(s_job);
     }

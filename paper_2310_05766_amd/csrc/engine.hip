@@ -402,7 +402,7 @@ tsdf_status Engine::run_chunk(const std::vector<MapRef> &maps, const std::vector
     hdr->want_stats = stats ? 1u : 0u;
     hdr->bin_block = bb;
     hdr->emit = emit;
-    hdr->once = once ? once_ : 0u;
+    hdr->once = once ? 1u : 0u;
     memcpy(h + L.maps, md.data(), nmaps * sizeof(MapDev));
     ScanDev *sd = (ScanDev *)(h + L.scans);
     uint32_t *bs = (uint32_t *)(h + L.block_scan);
@@ -490,7 +490,6 @@ tsdf_status Engine::run_chunk(const std::vector<MapRef> &maps, const std::vector
     B.scan_stats = (uint32_t *)stats_;
     B.ctl = (BatchCtl *)ctl_;
     B.lists = (TileList *)(lists_in_arr_ ? (void *)((char *)arr_ + lists_at_) : lists_);
-    if (once) once_ = 3u - once_;
 
     if (arr_clear_) ECHK(launch_fill_u32((uint32_t *)arr_, (int64_t)(arr_clear_ / 4), 0u, stream_));
     arr_clear_ = 0;

@@ -106,7 +106,6 @@ private:
     void *stats_host_ = nullptr;  // pinned
     size_t stats_host_cap_ = 0;   // bytes
     void *ctl_ = nullptr;  // [3]: of two binning passes, and of one in turn
-    uint32_t once_ = 1;    // the latter's next
     bool lists_in_arr_ = false;  // the lists of one binning pass: arr_ + lists_at_, or
     size_t lists_at_ = 0;
     void *lists_ = nullptr;

@@ -61,9 +61,7 @@ struct BatchHdr {
     uint32_t want_stats;
     uint32_t bin_block;  // binning threads per block (one ray each)
     uint32_t key_shift;  // of the tile pass's 32-bit keys; 0: 64-bit keys
-    // one binning pass (TileList): its counters, ctl[1] or ctl[2] in turn (0:
-    // count, runs and fill, with ctl[0]); entries that a point can give
-    uint32_t once, emit;
+    uint32_t once, emit; // one binning pass (TileList); entries that a point can give
 };
 
 // The descriptors of a batch of one scan, handed to the first binning
@@ -87,7 +85,8 @@ struct BatchCtl {
     uint32_t n_nonempty;  // busy tiles with heavy work, listed from the list's start
     uint32_t entries, overflow;
     uint32_t n_light;     // the other busy tiles, listed from the list's end
-    uint32_t pad[28];
+    uint32_t turn, next_turn;  // of ctl[0] (once_ctl)
+    uint32_t pad[26];
     uint32_t work[kQueues * kQueueStride];  // next job of queue q: work[q * kQueueStride]
 };
 
@@ -96,6 +95,11 @@ struct BatchCtl {
 // adds a segment of them to each tile it met. The first kSegs segments lie in
 // the list itself, the others in kChains chains of nodes in turn, which one wave
 // follows together. All zero between batches (segments may hold anything).
+// (Their counters are ctl[1] and ctl[2] in turn, ctl[0] being those of two
+// binning passes: a tile pass clears the next batch's. The turn is kept on the
+// device, so that a launch that a caller captured finds cleared counters at every
+// replay: binning goes by ctl[0].next_turn and leaves it in ctl[0].turn, which the
+// tile pass goes by; it then sets next_turn.)
 constexpr uint32_t kSegs = 7, kChains = 16;
 struct TileList {
     uint32_t nseg, total;   // segments, entries (one 64-bit counter)

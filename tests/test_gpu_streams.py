@@ -82,3 +82,60 @@ def test_batch_waits_for_points_written_on_torch_stream():
     m.close()
     assert (ww > 0).sum() > 10000
     assert np.array_equal(sdf, want_sdf) and np.array_equal(ww, want_w)
+
+
+@pytest.mark.parametrize("option", ["none", "interpolation", "carving"])
+@pytest.mark.parametrize("calls", [1, 2, 3])
+def test_calls_in_a_captured_graph_replay(calls, option):
+    """One-scan calls of device points, captured by the caller once the map has
+    its memory, give at every replay what eager calls give: replays follow one
+    another and other calls (a scan, a batch of two) come between."""
+    torch = pytest.importorskip("torch")
+    import oracle
+    from paper_2310_05766_amd.tsdf import TsdfMap, integrate_batch
+
+    spec = ((48, 40, 32), (-24, -20, -16), 0.1, 3072, 64)
+    st = torch.cuda.Stream()
+    gm, om = TsdfMap(*spec, stream=st), oracle.OracleMap(*spec)
+    for m in (gm, om):
+        if option == "interpolation":
+            m.set_interpolation(30.0, 16)
+        elif option == "carving":
+            m.set_carving(True)
+    scans = [(synth.fuzz_scan((71, k), 3000, extent_m=1.6, nan_frac=0.05), synth.fuzz_pose((72, k), 0.4)) for k in range(5)]
+    dev = [torch.from_numpy(x).to("cuda") for x, _ in scans]
+    torch.cuda.synchronize()
+
+    def eager(k):
+        with torch.cuda.stream(st):
+            gm.integrate(dev[k], scans[k][1])
+        om.integrate(*scans[k])
+
+    def same():
+        lo, hi = spec[1], tuple(spec[1][a] + spec[0][a] for a in range(3))
+        return all(np.array_equal(a, b) for a, b in zip(gm.readback(lo, hi), om.readback(lo, hi)))
+
+    for k in range(len(scans)):
+        eager(k)
+    torch.cuda.synchronize()
+    say("capture of", calls, "calls,", option)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        for k in range(calls):
+            gm.integrate(dev[k], scans[k][1])
+    for step in range(6):
+        for _ in range(1 + step % 3):
+            with torch.cuda.stream(st):
+                graph.replay()
+            for k in range(calls):
+                om.integrate(*scans[k])
+        if step % 2:
+            eager(step % len(scans))
+        if step == 3:
+            integrate_batch([(gm, dev[k], scans[k][1]) for k in (3, 4)], stream=st)
+            for k in (3, 4):
+                om.integrate(*scans[k])
+        torch.cuda.synchronize()
+        assert same(), step
+    gm.close()
+    om.close()
