@@ -18,6 +18,8 @@
 // beside the copies to the host, which take 3.5 ms (60 GB/s) and bound the
 // call (24.1 -> 6.0 ms with those copies and their page faults shared by
 // several host threads).
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace tsdf {
@@ -30,6 +32,9 @@ constexpr int kMeshWaves = kMeshBlock / 64;
 // hold thousands of triangles each.
 constexpr int kEmitWaves = (int)kMeshUnit, kEmitBlock = 64 * kEmitWaves;
 constexpr int kMostTris = 12;  // six tetrahedra, two triangles each
+// Units per launch: 2^31 work-items, half of what a grid may hold (a thin, wide
+// window has up to 2^30 rows of cubes).
+constexpr uint32_t kCountUnits = 0x80000000u / kMeshBlock, kEmitUnits = 0x80000000u / kEmitBlock;
 
 // What a cube holds, by its signs (bit k: corner k = (k & 1, k >> 1 & 1,
 // k >> 2 & 1) is negative): the number of triangles, and for each, 6 bits per
@@ -143,14 +148,16 @@ __device__ __forceinline__ MeshSpan mesh_span(const MeshArgs &A, const int32_t r
     return P;
 }
 
-__global__ __launch_bounds__(kMeshBlock) void k_mesh_count(MeshArgs A, uint32_t *row_tris, uint32_t *unit_tris)
+__global__ __launch_bounds__(kMeshBlock) void k_mesh_count(MeshArgs A, uint32_t *row_tris, uint32_t *unit_tris,
+                                                           uint32_t unit0)
 {
+    const uint32_t u = unit0 + blockIdx.x;
     __shared__ uint32_t s_sum;
     if (threadIdx.x == 0) s_sum = 0;
     __syncthreads();
     const int lane = (int)(threadIdx.x & 63u);
     for (uint32_t j = threadIdx.x / 64; j < kMeshUnit; j += kMeshWaves) {
-        const uint32_t r = blockIdx.x * kMeshUnit + j;
+        const uint32_t r = u * kMeshUnit + j;
         if (r >= A.nrows) break;
         int32_t row[4];
         mesh_rows(A, r, row);
@@ -169,7 +176,7 @@ __global__ __launch_bounds__(kMeshBlock) void k_mesh_count(MeshArgs A, uint32_t 
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0) unit_tris[blockIdx.x] = s_sum;
+    if (threadIdx.x == 0) unit_tris[u] = s_sum;
 }
 
 __device__ __forceinline__ void mesh_wave_sync()
@@ -250,16 +257,26 @@ __global__ __launch_bounds__(kEmitBlock) void k_mesh_emit(MeshArgs A, const uint
 
 hipError_t launch_mesh_count(const MeshArgs &A, uint32_t *row_tris, uint32_t *unit_tris, hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_mesh_count, dim3(mesh_units(A.nrows)), dim3(kMeshBlock), 0, stream, A, row_tris, unit_tris);
-    return hipGetLastError();
+    const uint32_t units = mesh_units(A.nrows);
+    for (uint32_t u = 0; u < units; u += kCountUnits) {
+        hipLaunchKernelGGL(k_mesh_count, dim3(std::min(kCountUnits, units - u)), dim3(kMeshBlock), 0, stream, A, row_tris,
+                           unit_tris, u);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_mesh_emit(const MeshArgs &A, const uint32_t *row_tris, const uint64_t *unit_base, uint32_t unit0,
                             uint32_t units, uint64_t base, float *out, hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_mesh_emit, dim3(units), dim3(kEmitBlock), 0, stream, A, row_tris, unit_base, unit0, base,
-                       out);
-    return hipGetLastError();
+    for (uint32_t u = 0; u < units; u += kEmitUnits) {
+        hipLaunchKernelGGL(k_mesh_emit, dim3(std::min(kEmitUnits, units - u)), dim3(kEmitBlock), 0, stream, A, row_tris,
+                           unit_base, unit0 + u, base, out);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace tsdf

@@ -135,3 +135,31 @@ def test_mesh_with_and_without_staging(dims):
     assert g.shape == part.shape and np.array_equal(g, part)
     gm.close()
     om.close()
+
+
+def test_mesh_of_a_thin_wide_window():
+    """More rows of cubes than one launch holds work-items for (2^28 rows in
+    units of 16 under 256 threads to count, 2^26 under 1024 to emit): the scans
+    of a corner and of the far corner, in the order of a small window's meshes."""
+    from paper_2310_05766_amd.tsdf import TsdfMap
+    dims, origin = (16384, 16400, 4), (-8192, -8200, -2)
+    assert (dims[0] - 1) * (dims[1] - 1) > 1 << 28
+    gm = TsdfMap(dims, origin, 0.1, 3072, 64)
+    parts = []
+    for corner in (0, 1):
+        at = [origin[a] + corner * (dims[a] - 48) for a in range(2)]
+        small = TsdfMap((48, 48, 4), (at[0], at[1], -2), 0.1, 3072, 64)
+        pose = np.eye(4)
+        pose[:3, 3] = ((at[0] + 24) * 0.1, (at[1] + 24) * 0.1, 0.6)
+        g = np.random.default_rng((74, corner))
+        xyz = np.concatenate([g.uniform(-1.5, 1.5, (20000, 2)), g.uniform(-0.65, -0.55, (20000, 1))], 1).astype(np.float32)
+        for m in (gm, small):
+            m.integrate(xyz, pose)
+        parts.append(small.mesh((at[0], at[1], -2), (at[0] + 48, at[1] + 48, 2)))
+        small.close()
+    say("mesh of", dims, "triangles", [p.shape[0] for p in parts])
+    assert min(p.shape[0] for p in parts) > 1000
+    g = gm.mesh(origin, tuple(origin[a] + dims[a] for a in range(3)))
+    want = np.concatenate(parts)
+    assert g.shape == want.shape and np.array_equal(g, want)
+    gm.close()
