@@ -238,11 +238,11 @@ __device__ __forceinline__ bool band_outside(const InterpScan &P, const Ray &R, 
 }
 
 template <typename Key>
-__global__ __launch_bounds__(kKeyRays * kFillLanes) void k_interp_scan(InterpScan P)
+__global__ __launch_bounds__(kKeyRays * kFillLanes) void k_interp_scan(InterpScan P, uint32_t block0)
 {
     __shared__ KeyTable<Key, kKeyRays * kFillLanes, sizeof(Key) == 4 ? 12 : 11> T;
     T.clear();
-    const int64_t i = patch_point<kKeyRays, kKeyRows>(blockIdx.x, threadIdx.x / kFillLanes, P.n);
+    const int64_t i = patch_point<kKeyRays, kKeyRows>(block0 + blockIdx.x, threadIdx.x / kFillLanes, P.n);
     const int sub = (int)(threadIdx.x % kFillLanes);
     uint64_t valid = 0, visits = 0, atomics = 0;
     int32_t q[3];
@@ -798,10 +798,16 @@ __global__ __launch_bounds__(256) void k_carve_merge(InterpScan P, int64_t nvox)
     block_add(updated, P, kCtrUpdated);
 }
 
+// (in launches of at most 2^31 work-items, like the free walks: a ray takes kFillLanes)
 void launch_interp_scan(const InterpScan &P, uint32_t blocks, hipStream_t stream)
 {
-    if (P.key_shift) hipLaunchKernelGGL((k_interp_scan<uint32_t>), dim3(blocks), dim3(kKeyRays * kFillLanes), 0, stream, P);
-    else hipLaunchKernelGGL((k_interp_scan<uint64_t>), dim3(blocks), dim3(kKeyRays * kFillLanes), 0, stream, P);
+    const uint32_t per = (uint32_t)1 << 23;
+    static_assert(((uint64_t)kKeyRays * kFillLanes << 23) <= (uint64_t)1 << 31, "work-items of a launch");
+    for (uint32_t b0 = 0; b0 < blocks; b0 += per) {
+        const dim3 grid(blocks - b0 < per ? blocks - b0 : per), block(kKeyRays * kFillLanes);
+        if (P.key_shift) hipLaunchKernelGGL((k_interp_scan<uint32_t>), grid, block, 0, stream, P, b0);
+        else hipLaunchKernelGGL((k_interp_scan<uint64_t>), grid, block, 0, stream, P, b0);
+    }
 }
 
 }  // namespace

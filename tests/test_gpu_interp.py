@@ -181,3 +181,26 @@ def test_fills_of_points_at_the_sensor(D):
         gm.close()
         om.close()
     assert hit > 0
+
+
+def test_interpolation_of_more_points_than_a_launch_holds():
+    """2^30 points and some: four work-items a point pass what one launch
+    holds. Returns at both ends of the scan, none between."""
+    import torch
+    spec = ((24, 24, 24), (-12, -12, -12), 0.1, 3072, 64)
+    n, k = (1 << 30) + 4000, 3000
+    xyz = torch.full((n, 3), float("nan"), dtype=torch.float32, device="cuda")
+    ends = synth.fuzz_scan((66, 0), 2 * k, extent_m=1.2, nan_frac=0.05)
+    xyz[:k] = torch.from_numpy(ends[:k]).cuda()
+    xyz[n - k:] = torch.from_numpy(ends[k:]).cuda()
+    gm, om = gpu_map(*spec), oracle.OracleMap(*spec)
+    gm.set_interpolation(40.0, 8)
+    om.set_interpolation(40.0, 8)
+    pose = synth.fuzz_pose((67, 0), 0.4)
+    say("interpolation of", n, "points")
+    want = om.integrate(ends, pose)
+    got = gm.integrate(xyz, pose, stats=True)
+    assert got == dict(want, points_in=n)
+    assert same(gm, om, spec[0])
+    gm.close()
+    om.close()
