@@ -339,29 +339,39 @@ tsdf_status Engine::run_chunk(const std::vector<MapRef> &maps, const std::vector
     // us, one of 3 M points 134 -> 102, 32 small ones into 32 maps 117 -> 102).
     // A tile busy in several slots reads its entries slot by slot, in runs. The
     // nodes are 2/3 more memory, so that the largest scans, and any where it is
-    // short, take the two passes.
+    // short, take the two passes: what both need is grown first, and a size that
+    // did not fit is not tried again (each try waits for the stream, frees the
+    // buffer and takes a smaller one).
+    if ((st = grow(&valid_, &valid_cap_, cap_blocks * sizeof(uint32_t), false)) != TSDF_OK) return st;
+    if ((st = grow(&stats_, &stats_cap_, cap_scans * kStatWords * sizeof(uint32_t), false)) != TSDF_OK) return st;
+    if (nhost > 0 && (st = grow(&pts_dev_, &pts_dev_cap_, nhost * 3 * sizeof(float), false)) != TSDF_OK) return st;
     const uint32_t emit = (uint32_t)max_tiles_per_ray(tau_max, lt);
     bool once = S == 1 && nblocks > 0 && nblocks <= kOnceBlocks && nblocks * bb * emit < ((uint64_t)1 << 31);
     if (once) {
         // per block bb emit entries of two records, and its nodes
-        const size_t records = (size_t)nblocks * (2 * bb * emit + nodes_per_block(bb, emit));
-        st = grow(&entries_, &entries_cap_, records * sizeof(uint4), false);
-        if (st == TSDF_OK && !lists_in_arr_) st = grow(&lists_, &lists_cap_, gtiles * sizeof(TileList), true);
-        if (st != TSDF_OK && st != TSDF_ENOMEM) return st;
-        once = st == TSDF_OK;
-        if (!once) (void)hipGetLastError();  // the failed allocation's
+        const size_t records = (size_t)nblocks * (2 * bb * emit + nodes_per_block(bb, emit)) * sizeof(uint4);
+        const size_t lists = lists_in_arr_ ? 0 : gtiles * sizeof(TileList);
+        const bool grows = records > entries_cap_ || lists > lists_cap_;
+        once = !grows || records + lists < once_failed_;
+        if (once && grows) {
+            st = grow(&entries_, &entries_cap_, records, false);
+            if (st == TSDF_OK) st = grow(&lists_, &lists_cap_, lists, true);
+            if (st != TSDF_OK && st != TSDF_ENOMEM) return st;
+            once = st == TSDF_OK;
+            if (!once) {
+                (void)hipGetLastError();  // the failed allocation's
+                once_failed_ = records + lists;
+            }
+        }
     }
     if (!once && (st = grow(&entries_, &entries_cap_, need_entries * 2 * sizeof(uint4), false)) != TSDF_OK) return st;
-    if ((st = grow(&valid_, &valid_cap_, cap_blocks * sizeof(uint32_t), false)) != TSDF_OK) return st;
     const size_t stat_words = once ? kStatWords : 4, stat_bytes = cap_scans * stat_words * sizeof(uint32_t);
-    if ((st = grow(&stats_, &stats_cap_, stat_bytes, false)) != TSDF_OK) return st;
     if (stats && (st = grow(&stats_host_, &stats_host_cap_, stat_bytes, false, true)) != TSDF_OK) return st;
 
     // host points: pinned staging, one copy to the device
     std::vector<const float *> xyz(nscans);
     if (nhost > 0) {
         const size_t bytes = nhost * 3 * sizeof(float);
-        if ((st = grow(&pts_dev_, &pts_dev_cap_, bytes, false)) != TSDF_OK) return st;
         const int k = pts_cur_;
         if (pts_ev_live_[k]) ECHK(hipEventSynchronize(pts_ev_[k]));
         pts_ev_live_[k] = false;

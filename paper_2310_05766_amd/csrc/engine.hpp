@@ -110,6 +110,7 @@ private:
     size_t lists_at_ = 0;
     void *lists_ = nullptr;
     size_t lists_cap_ = 0;  // bytes
+    size_t once_failed_ = SIZE_MAX;  // bytes of entries and lists that one binning pass could not get
     // host points staging
     void *pts_dev_ = nullptr;
     size_t pts_dev_cap_ = 0;

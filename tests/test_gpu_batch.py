@@ -454,3 +454,48 @@ def test_one_binning_pass(case):
         assert same(g, o, dims)
         g.close()
         o.close()
+
+
+def test_one_binning_pass_where_memory_is_short():
+    """A scan whose one-pass buffers (about 14 GB) do not fit the memory that
+    is left, while those of two passes (about 9) do: the same map and counts as
+    with all memory, and the size that failed is not tried again."""
+    import torch
+    from paper_2310_05766_amd.tsdf import TsdfMap
+    spec, n = ((64, 60, 56), (-32, -30, -28), 0.1, 10240, 64), 65536 * 512
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    xyz = torch.randn(n, 3, generator=g, device="cuda")
+    xyz *= (3.0 / xyz.norm(dim=1, keepdim=True)) * (0.8 + 0.4 * torch.rand(n, 1, generator=g, device="cuda"))
+    torch.cuda.synchronize()
+
+    def made():
+        m = TsdfMap(*spec)
+        m.set_tiling((3, 3, 3))
+        m.set_blocks(512, 256)
+        return m
+
+    ref = made()
+    want = [ref.integrate(xyz, synth.fuzz_pose((103, k), 0.3), stats=True) for k in range(3)]
+    arrays = ref.readback_window()
+    ref.close()
+    gm = made()
+    gm.integrate(xyz[:1000], np.eye(4))
+    gm.close()  # (what the first use of a path loads is loaded)
+    gm = made()
+    torch.cuda.empty_cache()
+    GB = 1 << 30
+    held = []
+    while torch.cuda.mem_get_info()[0] > 12.5 * GB:
+        held.append(torch.empty(int(min(16 * GB, torch.cuda.mem_get_info()[0] - 12 * GB)), dtype=torch.uint8, device="cuda"))
+    say("free", torch.cuda.mem_get_info()[0] / GB)
+    got = [gm.integrate(xyz, synth.fuzz_pose((103, k), 0.3), stats=True) for k in range(2)]
+    say("free", torch.cuda.mem_get_info()[0] / GB)
+    del held
+    torch.cuda.empty_cache()
+    free = torch.cuda.mem_get_info()[0]
+    got.append(gm.integrate(xyz, synth.fuzz_pose((103, 2), 0.3), stats=True))
+    assert free - torch.cuda.mem_get_info()[0] < GB
+    assert got == want
+    assert all(np.array_equal(a, b) for a, b in zip(gm.readback_window(), arrays))
+    gm.close()
