@@ -96,3 +96,13 @@ def test_near_free_walk_matches_the_general_one(build, seed):
     out = subprocess.run([build("free_run_check"), str(seed), "60000"], capture_output=True, text=True)
     assert out.returncode == 0, out.stdout + out.stderr
     assert "mismatches 0" in out.stdout
+
+
+@pytest.mark.parametrize("seed", [1, 2])
+def test_tile_resume_in_whole_tiles(build, seed):
+    """The tile pass's own call: entry records resumed in whole tiles of every
+    tiling lie in their tile, visit the plain walk's voxels one tile after
+    another, and address nothing outside their slot of the key buffer."""
+    out = subprocess.run([build("tile_resume_check"), str(seed), "60000"], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout + out.stderr
+    assert "mismatches 0" in out.stdout
