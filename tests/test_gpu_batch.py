@@ -499,3 +499,39 @@ def test_one_binning_pass_where_memory_is_short():
     assert got == want
     assert all(np.array_equal(a, b) for a, b in zip(gm.readback_window(), arrays))
     gm.close()
+
+
+@pytest.mark.parametrize("dims", [(41, 39, 35), (64, 48, 40), (130, 9, 70)])
+def test_one_binning_pass_on_caller_owned_memory(dims):
+    """A map in the caller's arrays and in scratch of exactly the stated size:
+    the tile lists lie in the scratch behind the tables for coarse tiles and in
+    memory of their own for the finest, and the scratch is cut anew when tiles
+    get finer. Automatic, fine and automatic tiling again, with and without
+    counts, a batch of two scans between; nothing behind the scratch is
+    written."""
+    import torch
+    from paper_2310_05766_amd.tsdf import TsdfMap, integrate_batch
+    args = (dims, tuple(-(n // 2) for n in dims), 0.1, 3072, 64)
+    nv, sb, guard = dims[0] * dims[1] * dims[2], TsdfMap.scratch_bytes(*args), 4096
+    sdf, w = (torch.zeros(nv + guard, dtype=torch.int16, device="cuda") for _ in range(2))
+    scratch = torch.full((sb + guard,), 0xA5, dtype=torch.uint8, device="cuda")
+    sdf[nv:] = w[nv:] = 0x5A5A
+    torch.cuda.synchronize()
+    gm, om = TsdfMap(*args, arrays=(sdf[:nv], w[:nv], scratch[:sb])), oracle.OracleMap(*args)
+    say("scratch of", sb, "bytes for", dims)
+    k = 0
+    for tiling in (None, (3, 3, 3), (2, 2, 5), None, (4, 4, 4)):
+        gm.set_tiling(tiling or (0, 0, 0))
+        for stats in (True, False, True):
+            x, p = synth.fuzz_scan((104, k), 9000, extent_m=2.5, nan_frac=0.03), synth.fuzz_pose((105, k), 0.3)
+            got, want = gm.integrate(x, p, stats=stats), om.integrate(x, p)
+            assert got == (want if stats else None), (tiling, k)
+            k += 1
+        assert same(gm, om, dims), tiling
+        x, p = synth.fuzz_scan((106, k), 5000, extent_m=2.5), synth.fuzz_pose((107, k), 0.3)
+        assert integrate_batch([(gm, x, p), (gm, x[:3000], p)], stats=True) == [om.integrate(x, p), om.integrate(x[:3000], p)]
+    assert same(gm, om, dims)
+    torch.cuda.synchronize()
+    assert bool((scratch[sb:] == 0xA5).all()) and bool((sdf[nv:] == 0x5A5A).all()) and bool((w[nv:] == 0x5A5A).all())
+    gm.close()
+    om.close()
