@@ -1,5 +1,5 @@
 // Batched integration (FeatSense, arXiv 2310.05766, Sec. VI): any number of
-// registered scans, into any number of maps, in one pass of two to five kernels.
+// registered scans, into any number of maps, in one pass of two to six kernels.
 //
 // Each map window is cut into tiles of 2^lt voxels per axis (window-relative
 // coordinates). The per-scan volume V of the min-tsdf step never reaches HBM:
@@ -10,6 +10,7 @@
 // stay in LDS while its workgroup applies those scans one after another, in
 // submission order, and go back to HBM once.
 //
+//   k_rows        where scans may have rows of points, their lengths (patch.hpp)
 //   k_bin<count>  every ray walks its band on the grid of tiles (the exact
 //                 walk with tile-sized cells) and counts one entry per tile;
 //                 keys are (sequence slot, tile), merged per block in an LDS
@@ -23,7 +24,8 @@
 //   k_stats       per-scan counts, when asked for (one binning pass: the tile
 //                 pass adds them up)
 //
-// Where each map has one scan, binning is one pass (the engine says when):
+// Where each map has one scan, binning is one pass (the engine says when), after
+// k_rows where there are several:
 //   k_bin<once>   the walk once; each block writes its entries, tile by tile,
 //                 into a region of its own and adds a segment of them to the
 //                 list of each tile it met; who adds a tile's first one lists
@@ -99,6 +101,19 @@ __device__ __forceinline__ bool finish_segment(const BatchArrays &B, BatchCtl *c
     return k == 0u;
 }
 
+// The rows of a batch's scans, a wave each: 6 us. (By every block of the counting
+// pass for itself, 10 us on 50 scans of 128 x 1024 points. The one scan of a plain
+// call does that: 0.8 us of 34 where a kernel of its own would take 5.)
+__global__ __launch_bounds__(256) void k_rows(BatchArrays B)
+{
+    const uint32_t s = blockIdx.x * 4u + threadIdx.x / 64u;
+    if (s >= (uint32_t)B.hdr->nscans) return;
+    ScanDev &SD = B.scans[s];
+    if (SD.lengths[0].length == 0) return;
+    const uint32_t k = find_row(SD.xyz, SD.n, SD.lengths, kBinPatch.step);
+    if (threadIdx.x % 64u == 0) SD.row = row_at(SD.lengths, k);
+}
+
 // kInline (the first pass only): the batch is one scan whose descriptors are
 // I, not yet in memory.
 template <int kMode, int kBinBlock, bool kInline>
@@ -119,7 +134,7 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
     // per emitted entry: hash slot | crossing counts (7 bits per axis) << 10, and rank
     __shared__ uint32_t s_slot[kFill ? kMaxEmit * kBinBlock : 1];
     __shared__ uint16_t s_rank[kFill ? kMaxEmit * kBinBlock : 1];
-    __shared__ uint32_t s_valid, s_extra, s_new, s_job, s_sum[kBinBlock / 64];
+    __shared__ uint32_t s_valid, s_extra, s_new, s_job, s_row, s_sum[kBinBlock / 64];
     // a one-scan batch's descriptors come with the counting launch, which
     // stores them for the kernels after it
     constexpr bool inl = kFirst && kInline;
@@ -150,22 +165,43 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
         h_cnt[j] = 0;
     }
     if (threadIdx.x == 0) s_valid = s_extra = s_new = 0;
-    __syncthreads();
-
     // (a one-scan batch's block table is written here, for the fill)
     if (inl && kMode == kCount && threadIdx.x == 0) B.block_scan[blockIdx.x] = 0u;
     const uint32_t s = inl ? 0u : B.block_scan[blockIdx.x];
     const ScanDev &SD = inl ? I.scan : B.scans[s];
+    // one scan: the points of the likely patch are requested beside the samples
+    // that tell the row length (every block finds the same); several: k_rows has it
+    const int64_t n = SD.n;
+    const float *xyz = SD.xyz;
+    const uint32_t block = blockIdx.x - SD.block0;
+    int64_t i;
+    float px = 0.f, py = 0.f, pz = 0.f;
+    const auto request = [&](const Row &row) {
+        i = patch_point<kBinBlock, kBinPatch.rows>(block, threadIdx.x, row);
+        if (i < n) {
+            px = xyz[3 * i];
+            py = xyz[3 * i + 1];
+            pz = xyz[3 * i + 2];
+        }
+    };
+    const Row likely = uniform_row(SD.row);
+    request(likely);
+    const bool tries = inl && SD.lengths[0].length != 0;
+    if (tries && threadIdx.x < 64u) s_row = find_row(xyz, n, SD.lengths, kBinPatch.step);
+    __syncthreads();
+    if (tries) {
+        const Row row = uniform_row(row_at(SD.lengths, s_row));
+        if (row.length != likely.length) request(row);
+        if (kMode == kCount && block == 0 && threadIdx.x == 0) B.scans[0].row = row;
+    }
     const MapDev &MD = inl ? I.map : B.maps[SD.map];
-    const int64_t i = patch_point<kBinBlock>(blockIdx.x - SD.block0, threadIdx.x, SD.n);
     const RayParams rp = SD.rp;
     Ray R;
     Walk W, Wv;  // the walk on the tile grid; the voxel walk's start (fill)
     bool active = false;
     int32_t q[3] = {0, 0, 0};
-    if (i < SD.n) {
-        const float *p = SD.xyz + 3 * i;
-        if (quantise(p[0], p[1], p[2], rp, q) && make_ray(q, rp, R)) {
+    if (i < n) {
+        if (quantise(px, py, pz, rp, q) && make_ray(q, rp, R)) {
             active = true;
             // the tiles of the band's voxels are the cells of the same exact
             // walk on the grid of tiles (floor of a floor division)
@@ -1102,6 +1138,7 @@ hipError_t launch_batch(const BatchArrays &B, const LaunchCaps &caps, hipStream_
     const uint32_t bins = caps.blocks > 0 ? caps.blocks : 1u;
     InlineDesc none;
     memset(&none, 0, sizeof(none));
+    if (caps.rows) hipLaunchKernelGGL(k_rows, dim3((caps.scans + 3) / 4), dim3(256), 0, stream, B);
     if (caps.once) {
         launch_bin_any(kOnce, bins, caps.bin_block, B, inl ? *inl : none, stream);
     } else {

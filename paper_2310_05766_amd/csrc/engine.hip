@@ -418,6 +418,7 @@ tsdf_status Engine::run_chunk(const std::vector<MapRef> &maps, const std::vector
     uint32_t *bs = (uint32_t *)(h + L.block_scan);
     int4 *ss = (int4 *)(h + L.seq_sensor);
     for (size_t j = 0; j < (size_t)nmaps * S; ++j) ss[j] = make_int4(0, 0, 0, 0);
+    bool rows = false;
     for (size_t k = 0; k < nscans; ++k) {
         const ScanRef &s = scans[b + k];
         const MapRef &m = maps[s.map];
@@ -431,12 +432,15 @@ tsdf_status Engine::run_chunk(const std::vector<MapRef> &maps, const std::vector
         d.map = slot_of[s.map];
         d.seq = seq[k];
         d.block0 = block0[k];
+        d.row = row_lengths(s.n, kBinPatch, d.lengths);
+        rows = rows || (!one && d.lengths[0].length);
         d.pad = 0;
         const uint32_t nb = (uint32_t)((s.n + bb - 1) / bb);
         for (uint32_t q = 0; q < nb; ++q) bs[block0[k] + q] = (uint32_t)k;
         ss[d.map * S + d.seq] = make_int4(d.rp.o[0], d.rp.o[1], d.rp.o[2], d.rp.tau);
     }
     LaunchCaps caps;
+    caps.rows = rows ? 1u : 0u;
     caps.blocks = (uint32_t)nblocks;
     caps.gtiles = (uint32_t)gtiles;
     caps.scans = (uint32_t)nscans;

@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "../../include/tsdf.h"
+#include "patch.hpp"
 #include "ray.hpp"
 
 namespace tsdf {
@@ -47,8 +48,11 @@ struct ScanDev {
     int32_t map;         // map slot in the batch
     int32_t seq;         // position among this map's scans in the batch
     uint32_t block0;     // first binning block of this scan
+    Row row;             // final, or likely until the lengths have been tried
+    Row lengths[kRowLengths];
     uint32_t pad;
 };
+constexpr PatchKind kBinPatch = {32, 32768, 3.5f};
 
 struct BatchHdr {
     int32_t lt[3];
@@ -140,27 +144,38 @@ struct BatchArrays {
     uint4 *nodes;          // [nblocks * nodes_per_block], one binning pass
 };
 
-// The point of thread t of a scan's block b. A block takes a patch of the
-// scan, kPatchRows runs of points kPatchStride apart, instead of one run: in
-// an organised scan (ring by ring, about a thousand columns to a ring) those
-// are neighbouring rings, whose points share tiles, so that a block meets
-// fewer tiles, sends fewer atomics and writes longer stretches of a run. Runs
-// of 1, 4, 8, 16 and 32 rows on 50 scans of 128 x 1024 points: count 123, 103,
-// 106, 103, 103 us, fill 153, 156, 157, 138, 131 us; on 64 uneven room scans
-// count + fill 378, -, 377, 359, 343 us. (In a scan of another width the runs
-// of a block lie apart: what the binning loses there the tile pass's other
-// changes outweigh, 28 scans of 104 x 554 points 205 -> 202 us in all.)
-constexpr uint32_t kPatchStride = 1024;
-
-template <int kBinBlock, uint32_t kPatchRows = 32>
-__device__ __forceinline__ int64_t patch_point(uint32_t b, uint32_t t, int64_t n)
+// A row of a scan among the lengths to try (patch.hpp). A whole wave calls; its
+// index, or kRowLengths.
+__device__ __forceinline__ uint32_t find_row(const float *xyz, int64_t n, const Row lengths[kRowLengths], float step)
 {
-    constexpr uint32_t kPatch = kPatchRows * kPatchStride;  // points that a group of blocks shares out
-    constexpr uint32_t kRun = kBinBlock / kPatchRows, kGroup = kPatch / kBinBlock;
-    static_assert(kRun * kPatchRows == kBinBlock && kGroup * kRun == kPatchStride, "a group covers its points once");
-    const int64_t g0 = (int64_t)(b / kGroup) * kPatch;
-    if (g0 + kPatch > n) return (int64_t)b * kBinBlock + t;  // the last points: in order
-    return g0 + t / kRun * kPatchStride + b % kGroup * kRun + t % kRun;
+    const uint32_t lane = __lane_id(), j = lane / kRowSamples;
+    uint32_t row = 0;
+#pragma unroll
+    for (int k = 0; k < kRowLengths; ++k) row = j == (uint32_t)k ? lengths[k].length : row;
+    bool counts = false, fits = false;
+    if (row) {
+        const float *a = xyz + 3 * row_sample(n, lane % kRowSamples), *b = a + 3 * (int64_t)row, *c = a + 3 * kRowSpan;
+        const float pa[3] = {a[0], a[1], a[2]}, pb[3] = {b[0], b[1], b[2]}, pc[3] = {c[0], c[1], c[2]};
+        row_vote(pa, pb, pc, step, counts, fits);
+    }
+    const uint64_t mine = ((1ull << kRowSamples) - 1) << (j * kRowSamples);
+    const int nc = __popcll(__ballot(counts) & mine), nf = __popcll(__ballot(fits) & mine);
+    const uint64_t ok = __ballot(row_fits(nc, nf));
+    return ok ? (uint32_t)__builtin_ctzll(ok) / kRowSamples : kRowLengths;
+}
+__device__ __forceinline__ Row row_at(const Row lengths[kRowLengths], uint32_t k)
+{
+    Row row{0, 0, 0};
+#pragma unroll
+    for (uint32_t j = 0; j < kRowLengths; ++j)
+        if (k == j) row = lengths[j];
+    return row;
+}
+// The same, held alike by all lanes, in scalar registers.
+__device__ __forceinline__ Row uniform_row(const Row &row)
+{
+    return Row{(uint32_t)__builtin_amdgcn_readfirstlane((int)row.length), (uint32_t)__builtin_amdgcn_readfirstlane((int)row.end),
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)row.inverse)};
 }
 
 // Upper bound of the tiles one ray's band can fall in.
@@ -180,6 +195,7 @@ struct LaunchCaps {
     uint32_t stats;       // per-scan counts wanted: k_stats runs only then
     uint32_t key32;       // 32-bit keys in the tile pass
     uint32_t once;        // one binning pass
+    uint32_t rows;        // scans that may have rows: k_rows runs only then
 };
 
 // The tile pass's LDS and grid for a tiling, S sequence slots, a truncation and
@@ -230,12 +246,15 @@ struct InterpScan {
     uint32_t key_shift;
     uint32_t *keys32;
     uint8_t *marks;
+    Row row, lengths[kRowLengths];  // as in ScanDev
+    Row *found;                    // from the band's kernel to the free space's
     int32_t want_stats;            // count valid points, visits and voxels updated
     unsigned long long *counters;  // [kinds][kCtrLines * kCtrStride], added to
 };
 enum { kCtrValid = 0, kCtrVisits = 1, kCtrUpdated = 2, kCtrAtomics = 3, kCtrKinds = 4 };
 constexpr uint32_t kCtrLines = 64, kCtrStride = 16;  // counters of a kind, and words from one to the next
 constexpr size_t kCtrWords = (size_t)kCtrLines * kCtrStride;
+constexpr PatchKind kKeyPatch = {8, 8192, 6.0f};
 // Bytes of a key volume: 64-bit keys, or 32-bit keys and marks.
 inline size_t key_marks_offset(int64_t nvox) { return ((size_t)nvox * 4 + 255) / 256 * 256; }
 inline size_t key_marks_bytes(int64_t nvox) { return ((size_t)nvox + 4095) / 4096 * 4096; }

@@ -68,7 +68,6 @@ constexpr int kInterpBlock = 256;
 // table twice as large; 2 and 8 lanes 147 and 139. (Carving's bands, without
 // fills: 58, 62, 62; 54 with 2 lanes. Its atomics alone take 43 us.)
 constexpr int kKeyRays = 64, kFillLanes = 4, kBandLanes = 2;
-constexpr uint32_t kKeyRows = 8;
 constexpr int kCarveChunkLog2 = 3;
 constexpr int kCarvePieces = 16;  // of a ray's free segment, one wave each per 64 rays
 constexpr int kCarveAhead = 2;    // voxels whose marks are requested together
@@ -241,8 +240,12 @@ template <typename Key>
 __global__ __launch_bounds__(kKeyRays * kFillLanes) void k_interp_scan(InterpScan P, uint32_t block0)
 {
     __shared__ KeyTable<Key, kKeyRays * kFillLanes, sizeof(Key) == 4 ? 12 : 11> T;
+    __shared__ uint32_t s_row;
+    const bool tries = P.lengths[0].length != 0;
+    if (tries && threadIdx.x < 64u) s_row = find_row(P.xyz, P.n, P.lengths, kKeyPatch.step);
     T.clear();
-    const int64_t i = patch_point<kKeyRays, kKeyRows>(block0 + blockIdx.x, threadIdx.x / kFillLanes, P.n);
+    const Row row = tries ? uniform_row(row_at(P.lengths, s_row)) : P.row;
+    const int64_t i = patch_point<kKeyRays, kKeyPatch.rows>(block0 + blockIdx.x, threadIdx.x / kFillLanes, row);
     const int sub = (int)(threadIdx.x % kFillLanes);
     uint64_t valid = 0, visits = 0, atomics = 0;
     int32_t q[3];
@@ -554,8 +557,13 @@ __device__ __forceinline__ int free_axis(const Ray &R, const RayParams &P)
 __global__ __launch_bounds__(kKeyRays * kBandLanes) void k_carve_band(InterpScan P)
 {
     __shared__ KeyTable<uint32_t, kKeyRays * kBandLanes, 11> T;
+    __shared__ uint32_t s_row;
+    const bool tries = P.lengths[0].length != 0;
+    if (tries && threadIdx.x < 64u) s_row = find_row(P.xyz, P.n, P.lengths, kKeyPatch.step);
     T.clear();
-    const int64_t i = patch_point<kKeyRays, kKeyRows>(blockIdx.x, threadIdx.x / kBandLanes, P.n);
+    const Row row = tries ? uniform_row(row_at(P.lengths, s_row)) : P.row;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *P.found = row;
+    const int64_t i = patch_point<kKeyRays, kKeyPatch.rows>(blockIdx.x, threadIdx.x / kBandLanes, row);
     const int sub = (int)(threadIdx.x % kBandLanes);
     const auto offer = [&](const int32_t g[3], uint32_t key) -> uint32_t {
         const uint32_t idx = rel_index(P, g);
@@ -636,7 +644,7 @@ __device__ __forceinline__ uint32_t mark_free(const InterpScan &P, uint32_t idx,
 __global__ __launch_bounds__(kInterpBlock) void k_carve_free(InterpScan P, int64_t block0)
 {
     const int64_t w = ((block0 + (int64_t)blockIdx.x) * kInterpBlock + threadIdx.x) >> 6;
-    const int64_t i = patch_point<64, kKeyRows>((uint32_t)(w / kCarvePieces), threadIdx.x & 63u, P.n);
+    const int64_t i = patch_point<64, kKeyPatch.rows>((uint32_t)(w / kCarvePieces), threadIdx.x & 63u, *P.found);
     const int32_t piece = (int32_t)(w % kCarvePieces);
     uint64_t visits = 0, atomics = 0;
     int32_t q[3];

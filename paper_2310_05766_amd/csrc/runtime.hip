@@ -620,6 +620,8 @@ static tsdf_status integrate_interp(tsdf_map *m, const float *xyz, int64_t n, bo
     P.touched = m->interp_touched;
     P.counters = m->interp_ctr;
     P.want_stats = stats ? 1 : 0;
+    P.row = row_lengths(n, kKeyPatch, P.lengths);
+    P.found = (Row *)(m->interp_ctr + kCtrKinds * kCtrWords);
     P.key_shift = key32_shift(P.rp.tau, n);
     P.keys32 = (uint32_t *)m->interp_keys;
     P.marks = (uint8_t *)m->interp_keys + key_marks_offset(m->nvox);
@@ -664,7 +666,8 @@ static tsdf_status ensure_key_volume(tsdf_map *m)
     }
     const int64_t runs = (m->nvox + 63) / 64;
     const size_t touched_bytes = (size_t)((runs + 3) / 4 * 4);
-    if (hipMalloc(&m->interp_ctr, kCtrKinds * kCtrWords * sizeof(unsigned long long)) != hipSuccess) m->interp_ctr = nullptr;
+    // (behind the counters: the row length that a carving scan's first kernel found)
+    if (hipMalloc(&m->interp_ctr, kCtrKinds * kCtrWords * sizeof(unsigned long long) + sizeof(Row)) != hipSuccess) m->interp_ctr = nullptr;
     if (hipHostMalloc(&m->interp_ctr_host, kCtrKinds * kCtrWords * sizeof(unsigned long long), hipHostMallocDefault) !=
         hipSuccess)
         m->interp_ctr_host = nullptr;

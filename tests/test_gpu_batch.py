@@ -535,3 +535,56 @@ def test_one_binning_pass_on_caller_owned_memory(dims):
     assert bool((scratch[sb:] == 0xA5).all()) and bool((sdf[nv:] == 0x5A5A).all()) and bool((w[nv:] == 0x5A5A).all())
     gm.close()
     om.close()
+
+
+def _rings(rings, cols, seed, missing=0.02):
+    """An organised scan of a small room, in the sensor frame."""
+    g = np.random.default_rng(seed)
+    el = np.deg2rad(np.linspace(-22.5, 22.5, rings))[:, None]
+    az = 2 * np.pi * np.arange(cols)[None] / cols
+    d = np.stack([np.cos(el) * np.cos(az), np.cos(el) * np.sin(az), np.sin(el) * np.ones_like(az)], -1).reshape(-1, 3)
+    half, pos = np.array([3.0, 2.4, 1.3]), np.array([0.4, -0.3, 0.1])
+    with np.errstate(divide="ignore"):
+        t = (np.where(d > 0, half - pos, half + pos) / np.abs(d)).min(1) + 0.01 * g.standard_normal(len(d))
+    xyz = (d * t[:, None]).astype(np.float32)
+    xyz[g.random(len(d)) < missing] = np.nan
+    return xyz
+
+
+@pytest.mark.parametrize("rings,cols", [(104, 554), (64, 1021), (128, 900), (128, 333), (40, 1800), (32, 1025), (64, 512), (33, 1024)])
+def test_patches_of_rows_of_any_length(rings, cols):
+    """Scans whose rows the binning finds (or not) take their points in patches:
+    every point once. One scan, a batch of several scans of a map, one per map,
+    interpolating and carving maps, and the allocation-free call, against the
+    oracle; the same points shuffled, which have no rows."""
+    import ctypes as C
+
+    import torch
+    from paper_2310_05766_amd import _abi
+    from paper_2310_05766_amd.tsdf import integrate_batch
+    spec = ((72, 64, 40), (-36, -32, -20), 0.1, 3072, 64)
+    scans = [(_rings(rings, cols, (108, k)), synth.fuzz_pose((109, k), 0.2)) for k in range(3)]
+    scans.append((np.random.default_rng(110).permutation(scans[0][0]), scans[0][1]))
+    dev = [(torch.from_numpy(x).to("cuda"), p) for x, p in scans]
+    gms, oms = [gpu_map(*spec) for _ in range(5)], [oracle.OracleMap(*spec) for _ in range(5)]
+    for m in (gms[2], oms[2]):
+        m.set_interpolation(45.0, 64)
+    for m in (gms[3], oms[3]):
+        m.set_carving(True)
+    say(rings, "x", cols)
+    for k in range(4):
+        for m in (0, 2, 3):
+            assert gms[m].integrate(*dev[k], stats=True) == oms[m].integrate(*scans[k]), (k, m)
+        M, st = np.ascontiguousarray(scans[k][1], dtype=np.float64), _abi.ScanStats()
+        torch.cuda.synchronize()
+        assert _abi.lib().tsdf_integrate_scan_noalloc(gms[4].handle, dev[k][0].data_ptr(), dev[k][0].shape[0],
+                                                      M.ctypes.data_as(C.POINTER(C.c_double)), C.byref(st)) == 0
+        assert dict((f, getattr(st, f)) for f, _ in st._fields_) == oms[4].integrate(*scans[k]), k
+    items = [(0, 0), (1, 1), (0, 2), (0, 3), (1, 0)]
+    assert integrate_batch([(gms[m], *dev[k]) for m, k in items], stats=True) == [oms[m].integrate(*scans[k]) for m, k in items]
+    items = [(0, 1), (1, 2)]
+    assert integrate_batch([(gms[m], *dev[k]) for m, k in items], stats=True) == [oms[m].integrate(*scans[k]) for m, k in items]
+    for g, o in zip(gms, oms):
+        assert same(g, o, spec[0])
+        g.close()
+        o.close()
