@@ -301,7 +301,7 @@ struct RegArgs {
 hipError_t launch_reg_step(const RegArgs &A, hipStream_t stream);
 
 // Surface extraction of a box of the window (mesh.hip).
-constexpr uint32_t kMeshUnit = 16;  // rows of cubes per workgroup
+constexpr uint32_t kMeshUnit = 16;  // groups of rows of cubes per workgroup
 struct MeshArgs {
     const int16_t *sdf, *w;
     int32_t dims[3];  // the window (slot = floor_mod(g, dims))
@@ -309,14 +309,19 @@ struct MeshArgs {
     int32_t s0[3];    // its slot per axis
     int32_t n[3];     // cubes per axis
     uint32_t nrows;   // n[0] * n[1]
+    // a wave takes a group of 64 >> lseg rows of up to 2^lseg voxels side by side,
+    // where they are that short, else (lseg 6) one row
+    int32_t lseg;
+    uint32_t groups;
     double vs;        // voxel size, metres
 };
-inline uint32_t mesh_units(uint32_t nrows) { return (nrows + kMeshUnit - 1) / kMeshUnit; }
-// Triangles per row of cubes and per unit of kMeshUnit rows.
-hipError_t launch_mesh_count(const MeshArgs &A, uint32_t *row_tris, uint32_t *unit_tris, hipStream_t stream);
+void mesh_groups(MeshArgs &A);  // lseg and groups, from the rest
+inline uint32_t mesh_units(const MeshArgs &A) { return (A.groups + kMeshUnit - 1) / kMeshUnit; }
+// Triangles per group of rows and per unit of kMeshUnit groups.
+hipError_t launch_mesh_count(const MeshArgs &A, uint32_t *group_tris, uint32_t *unit_tris, hipStream_t stream);
 // Triangles of `units` units from unit0 on; unit_base: exclusive prefix of
 // unit_tris, with the total behind it; base: the first unit's.
-hipError_t launch_mesh_emit(const MeshArgs &A, const uint32_t *row_tris, const uint64_t *unit_base, uint32_t unit0,
+hipError_t launch_mesh_emit(const MeshArgs &A, const uint32_t *group_tris, const uint64_t *unit_base, uint32_t unit0,
                             uint32_t units, uint64_t base, float *out, hipStream_t stream);
 
 // ---------------------------------------------------------------------------

@@ -3,8 +3,9 @@
 // centres cut into the 6 tetrahedra around its 0-7 diagonal; one or two
 // triangles per tetrahedron with a sign change; edge points at
 // t = s_a / (s_a - s_b) in float64). Two passes give a deterministic order,
-// cube by cube (x, then y, then z): a count per row of cubes, and, after an
-// exclusive scan over units of 16 rows on the host, an emit pass.
+// cube by cube (x, then y, then z): a count per row of cubes (per group of short
+// rows, which share a wave), and, after an exclusive scan over units of 16 rows
+// (groups) on the host, an emit pass.
 //
 // Almost all cubes hold no surface (1 in 45 of a window around a room), so
 // both passes look at 63 cubes of a row at once: a wave reads 64 voxels of the
@@ -13,7 +14,10 @@
 // cube is complete, the distances are not read at all. Only then do lanes look
 // up what their cube holds in a table over its eight signs. The emit pass
 // spreads a wave's triangles over its lanes, one triangle per lane, however
-// many each cube gives. A 512 x 512 x 256 window with 5.8 M triangles: count
+// many each cube gives. Rows of at most 31 cubes (a slice of the ground) share
+// a wave, or most of its lanes would idle: 512 x 512 voxels, 2 layers, count 41 ->
+// 25 us and emit 29 -> 20 (a thread per cube: 16 and 43), 9 layers 41 -> 20 and 31 ->
+// 20 (27 and 61). A 512 x 512 x 256 window with 5.8 M triangles: count
 // 770 -> 160 us (bound by instruction issue, 1.3 M spans), emit 2.7 -> 1.5 ms,
 // beside the copies to the host, which take 3.5 ms (60 GB/s) and bound the
 // call (24.1 -> 6.0 ms with those copies and their page faults shared by
@@ -28,7 +32,7 @@ namespace {
 
 constexpr int kMeshBlock = 256;
 constexpr int kMeshWaves = kMeshBlock / 64;
-// The emit pass has a wave per row: where a wall lies along y, its few rows
+// The emit pass has a wave per row (group): where a wall lies along y, its few rows
 // hold thousands of triangles each.
 constexpr int kEmitWaves = (int)kMeshUnit, kEmitBlock = 64 * kEmitWaves;
 constexpr int kMostTris = 12;  // six tetrahedra, two triangles each
@@ -88,7 +92,8 @@ constexpr MeshTable make_table()
 
 __constant__ MeshTable kTable = make_table();
 
-// 63 cubes (64 voxels) of a row from voxel z0 on. q = (x | y << 1) numbers
+// The cubes of a wave: 63 (64 voxels) of one row from voxel z0 on, or, in thin
+// boxes, a group of rows side by side, 2^lseg lanes each. q = (x | y << 1) numbers
 // the four voxel rows.
 struct MeshSpan {
     uint64_t act;    // complete cubes whose signs differ
@@ -110,23 +115,27 @@ __device__ __forceinline__ void mesh_rows(const MeshArgs &A, uint32_t r, int32_t
     }
 }
 
-__device__ __forceinline__ MeshSpan mesh_span(const MeshArgs &A, const int32_t row[4], int32_t z0, int lane)
+// Slot of a row's voxel z of the box, 0 past the box.
+__device__ __forceinline__ int32_t mesh_z(const MeshArgs &A, int32_t z, bool valid)
+{
+    int32_t sz = A.s0[2] + z;
+    sz -= sz >= A.dims[2] ? A.dims[2] : 0;
+    return valid ? sz : 0;
+}
+
+// valid: this lane has a voxel of the box; ends: lanes that end a row of a group.
+__device__ __forceinline__ MeshSpan mesh_span(const MeshArgs &A, const int32_t row[4], int32_t sz, bool valid, uint64_t ends)
 {
     MeshSpan P;
     P.act = 0;
     P.signs = 0;
-    const int32_t z = z0 + lane;
-    const bool valid = z <= A.n[2];  // n cubes are n + 1 voxels
-    int32_t sz = A.s0[2] + z;
-    sz -= sz >= A.dims[2] ? A.dims[2] : 0;
-    sz = valid ? sz : 0;
     int32_t w[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) w[q] = A.w[row[q] + sz];
     uint64_t seen = __ballot(valid);
 #pragma unroll
     for (int q = 0; q < 4; ++q) seen &= __ballot(w[q] > 0);
-    const uint64_t cubes = seen & (seen >> 1);  // (the last voxel of a span starts no cube)
+    const uint64_t cubes = seen & (seen >> 1) & ~ends;  // (the last voxel of a span or row starts no cube)
     if (!cubes) return P;
 #pragma unroll
     for (int q = 0; q < 4; ++q) P.s[q] = A.sdf[row[q] + sz];
@@ -148,31 +157,71 @@ __device__ __forceinline__ MeshSpan mesh_span(const MeshArgs &A, const int32_t r
     return P;
 }
 
-__global__ __launch_bounds__(kMeshBlock) void k_mesh_count(MeshArgs A, uint32_t *row_tris, uint32_t *unit_tris,
+__device__ __forceinline__ uint32_t wave_sum(uint32_t n)
+{
+    if (__any(n != 0)) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) n += (uint32_t)__shfl_xor((int)n, off);
+    }
+    return n;
+}
+
+// A workgroup per unit, its waves take the unit's groups in turn.
+template <bool kThin>
+__global__ __launch_bounds__(kMeshBlock) void k_mesh_count(MeshArgs A, uint32_t *group_tris, uint32_t *unit_tris,
                                                            uint32_t unit0)
 {
+    constexpr uint32_t kPasses = kMeshUnit / kMeshWaves;
     const uint32_t u = unit0 + blockIdx.x;
     __shared__ uint32_t s_sum;
     if (threadIdx.x == 0) s_sum = 0;
     __syncthreads();
     const int lane = (int)(threadIdx.x & 63u);
-    for (uint32_t j = threadIdx.x / 64; j < kMeshUnit; j += kMeshWaves) {
-        const uint32_t r = u * kMeshUnit + j;
-        if (r >= A.nrows) break;
-        int32_t row[4];
-        mesh_rows(A, r, row);
-        uint32_t n = 0;
-        for (int32_t z0 = 0; z0 < A.n[2]; z0 += 63) {
-            const MeshSpan P = mesh_span(A, row, z0, lane);
-            if ((P.act >> lane) & 1ull) n += kTable.count[P.signs];
-        }
-        if (__any(n != 0)) {
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) n += (uint32_t)__shfl_xor((int)n, off);
-        }
+    const uint32_t group0 = u * kMeshUnit + threadIdx.x / 64;
+    const auto store = [&](uint32_t group, uint32_t n) {
+        n = wave_sum(n);
         if (lane == 0) {
-            row_tris[r] = n;
+            group_tris[group] = n;
             if (n) atomicAdd(&s_sum, n);
+        }
+    };
+    if (kThin) {
+        // the first of each row's four voxel rows, of all passes together: in most
+        // groups it holds nothing observed
+        const int32_t z = lane & ((1 << A.lseg) - 1);
+        const uint64_t ends = __ballot(z == (1 << A.lseg) - 1);
+        const int32_t sz = mesh_z(A, z, z <= A.n[2]);
+        int32_t row[kPasses][4], first[kPasses];
+#pragma unroll
+        for (uint32_t k = 0; k < kPasses; ++k) {
+            const uint32_t r = (group0 + k * kMeshWaves) * (64u >> A.lseg) + (uint32_t)(lane >> A.lseg);
+            const bool in = r < A.nrows && z <= A.n[2];
+            mesh_rows(A, in ? r : 0u, row[k]);
+            first[k] = in ? A.w[row[k][0] + sz] : 0;
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < kPasses; ++k) {
+            if (group0 + k * kMeshWaves >= A.groups) break;
+            uint32_t n = 0;
+            if (__any(first[k] > 0)) {
+                const MeshSpan P = mesh_span(A, row[k], sz, first[k] > 0, ends);
+                if ((P.act >> lane) & 1ull) n = kTable.count[P.signs];
+            }
+            store(group0 + k * kMeshWaves, n);
+        }
+    } else {
+        for (uint32_t k = 0; k < kPasses; ++k) {
+            const uint32_t r = group0 + k * kMeshWaves;
+            if (r >= A.groups) break;
+            int32_t row[4];
+            mesh_rows(A, r, row);
+            uint32_t n = 0;
+            for (int32_t z0 = 0; z0 < A.n[2]; z0 += 63) {
+                const bool valid = z0 + lane <= A.n[2];  // n cubes are n + 1 voxels
+                const MeshSpan P = mesh_span(A, row, mesh_z(A, z0 + lane, valid), valid, 0);
+                if ((P.act >> lane) & 1ull) n += kTable.count[P.signs];
+            }
+            store(r, n);
         }
     }
     __syncthreads();
@@ -188,32 +237,38 @@ __device__ __forceinline__ void mesh_wave_sync()
 
 // Units unit0 + blockIdx.x; unit u's triangles go to out at unit_base[u] -
 // base.
-__global__ __launch_bounds__(kEmitBlock) void k_mesh_emit(MeshArgs A, const uint32_t *row_tris,
+template <bool kThin>
+__global__ __launch_bounds__(kEmitBlock) void k_mesh_emit(MeshArgs A, const uint32_t *group_tris,
                                                           const uint64_t *unit_base, uint32_t unit0, uint64_t base,
                                                           float *out)
 {
-    __shared__ uint32_t s_row[kMeshUnit];
+    __shared__ uint32_t s_group[kMeshUnit];
     __shared__ int16_t s_val[kEmitWaves][4][64];
     __shared__ uint8_t s_signs[kEmitWaves][64], s_owner[kEmitWaves][64 * kMostTris];
     __shared__ uint16_t s_off[kEmitWaves][64];
     const uint32_t u = unit0 + blockIdx.x;
     if (unit_base[u + 1] == unit_base[u]) return;
     if (threadIdx.x < kMeshUnit) {
-        const uint32_t r = u * kMeshUnit + threadIdx.x;
-        s_row[threadIdx.x] = r < A.nrows ? row_tris[r] : 0u;
+        const uint32_t g = u * kMeshUnit + threadIdx.x;
+        s_group[threadIdx.x] = g < A.groups ? group_tris[g] : 0u;
     }
     __syncthreads();
     const int lane = (int)(threadIdx.x & 63u), wave = (int)(threadIdx.x / 64u);
-    const uint32_t j = (uint32_t)wave;  // this wave's row
-    if (s_row[j] != 0) {
+    const uint32_t j = (uint32_t)wave;  // this wave's group
+    if (s_group[j] != 0) {
         uint64_t at = unit_base[u] - base;
-        for (uint32_t k = 0; k < j; ++k) at += s_row[k];
-        const uint32_t r = u * kMeshUnit + j;
+        for (uint32_t k = 0; k < j; ++k) at += s_group[k];
+        const int lseg = kThin ? A.lseg : 6;
+        const uint32_t r0 = (u * kMeshUnit + j) << (6 - lseg), r = r0 + (uint32_t)(lane >> lseg);
+        const int32_t zl = lane & ((1 << lseg) - 1);
+        const uint64_t ends = kThin ? __ballot(zl == (1 << lseg) - 1) : 0ull;
+        const bool in = r < A.nrows;
         int32_t row[4];
-        mesh_rows(A, r, row);
-        const int32_t gx = A.lo[0] + (int32_t)(r / (uint32_t)A.n[1]), gy = A.lo[1] + (int32_t)(r % (uint32_t)A.n[1]);
-        for (int32_t z0 = 0; z0 < A.n[2]; z0 += 63) {
-            const MeshSpan P = mesh_span(A, row, z0, lane);
+        mesh_rows(A, in ? r : 0u, row);
+        const int32_t gx = A.lo[0] + (int32_t)(r0 / (uint32_t)A.n[1]), gy = A.lo[1] + (int32_t)(r0 % (uint32_t)A.n[1]);
+        for (int32_t z0 = 0; z0 < A.n[2]; z0 += 63) {  // (once in thin boxes)
+            const bool valid = in && z0 + zl <= A.n[2];
+            const MeshSpan P = mesh_span(A, row, mesh_z(A, z0 + zl, valid), valid, ends);
             if (!P.act) continue;
             const uint32_t n = (P.act >> lane) & 1ull ? kTable.count[P.signs] : 0u;
             uint32_t pre = n;  // inclusive prefix over the wave
@@ -232,7 +287,12 @@ __global__ __launch_bounds__(kEmitBlock) void k_mesh_emit(MeshArgs A, const uint
             for (uint32_t t = (uint32_t)lane; t < total; t += 64) {
                 const int o = s_owner[wave][t];
                 const uint32_t tri = kTable.tri[s_signs[wave][o]][t - s_off[wave][o]];
-                const int32_t g[3] = {gx, gy, A.lo[2] + z0 + o};
+                int32_t g[3] = {gx, gy, A.lo[2] + z0 + (o & ((1 << lseg) - 1))};
+                if (kThin) {
+                    const uint32_t ro = r0 + (uint32_t)(o >> lseg);
+                    g[0] = A.lo[0] + (int32_t)(ro / (uint32_t)A.n[1]);
+                    g[1] = A.lo[1] + (int32_t)(ro % (uint32_t)A.n[1]);
+                }
                 float *p = out + 9 * (at + t);
 #pragma unroll
                 for (int e = 0; e < 3; ++e) {
@@ -255,24 +315,34 @@ __global__ __launch_bounds__(kEmitBlock) void k_mesh_emit(MeshArgs A, const uint
 
 }  // namespace
 
-hipError_t launch_mesh_count(const MeshArgs &A, uint32_t *row_tris, uint32_t *unit_tris, hipStream_t stream)
+void mesh_groups(MeshArgs &A)
 {
-    const uint32_t units = mesh_units(A.nrows);
+    A.lseg = 1;
+    while (A.lseg < 6 && A.n[2] >= 1 << A.lseg) ++A.lseg;
+    const uint32_t per = 64u >> A.lseg;
+    A.groups = (A.nrows + per - 1) / per;
+}
+
+hipError_t launch_mesh_count(const MeshArgs &A, uint32_t *group_tris, uint32_t *unit_tris, hipStream_t stream)
+{
+    const uint32_t units = mesh_units(A);
     for (uint32_t u = 0; u < units; u += kCountUnits) {
-        hipLaunchKernelGGL(k_mesh_count, dim3(std::min(kCountUnits, units - u)), dim3(kMeshBlock), 0, stream, A, row_tris,
-                           unit_tris, u);
+        const dim3 grid(std::min(kCountUnits, units - u)), block(kMeshBlock);
+        if (A.lseg < 6) hipLaunchKernelGGL(k_mesh_count<true>, grid, block, 0, stream, A, group_tris, unit_tris, u);
+        else hipLaunchKernelGGL(k_mesh_count<false>, grid, block, 0, stream, A, group_tris, unit_tris, u);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
-hipError_t launch_mesh_emit(const MeshArgs &A, const uint32_t *row_tris, const uint64_t *unit_base, uint32_t unit0,
+hipError_t launch_mesh_emit(const MeshArgs &A, const uint32_t *group_tris, const uint64_t *unit_base, uint32_t unit0,
                             uint32_t units, uint64_t base, float *out, hipStream_t stream)
 {
     for (uint32_t u = 0; u < units; u += kEmitUnits) {
-        hipLaunchKernelGGL(k_mesh_emit, dim3(std::min(kEmitUnits, units - u)), dim3(kEmitBlock), 0, stream, A, row_tris,
-                           unit_base, unit0 + u, base, out);
+        const dim3 grid(std::min(kEmitUnits, units - u)), block(kEmitBlock);
+        if (A.lseg < 6) hipLaunchKernelGGL(k_mesh_emit<true>, grid, block, 0, stream, A, group_tris, unit_base, unit0 + u, base, out);
+        else hipLaunchKernelGGL(k_mesh_emit<false>, grid, block, 0, stream, A, group_tris, unit_base, unit0 + u, base, out);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

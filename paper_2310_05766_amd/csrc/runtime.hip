@@ -865,9 +865,10 @@ tsdf_status tsdf_mesh(tsdf_map *m, const int32_t lo[3], const int32_t hi[3], flo
     A.vs = m->d.voxel_size_m;
     *n_tris = 0;
     if (nrows == 0 || A.n[2] == 0) return TSDF_OK;
-    // counts per row of cubes and per unit of rows; the units' places
-    const uint32_t units = mesh_units(A.nrows);
-    const size_t off_units = (size_t)A.nrows * 4, off_base = (off_units + (size_t)units * 4 + 7) / 8 * 8;
+    // counts per group of rows and per unit of groups; the units' places
+    mesh_groups(A);
+    const uint32_t units = mesh_units(A);
+    const size_t off_units = (size_t)A.groups * 4, off_base = (off_units + (size_t)units * 4 + 7) / 8 * 8;
     const size_t dev_bytes = off_base + ((size_t)units + 1) * 8, host_bytes = ((size_t)units + 1) * 16;
     if (dev_bytes > m->mesh_dev_cap) {
         if (m->mesh_dev) HIPCHK(m, hipFree(m->mesh_dev));
@@ -883,11 +884,11 @@ tsdf_status tsdf_mesh(tsdf_map *m, const int32_t lo[3], const int32_t hi[3], flo
         if (hipHostMalloc(&m->mesh_host, host_bytes, hipHostMallocDefault) != hipSuccess) return TSDF_ENOMEM;
         m->mesh_host_cap = host_bytes;
     }
-    uint32_t *row_tris = (uint32_t *)m->mesh_dev, *unit_tris = (uint32_t *)((char *)m->mesh_dev + off_units);
+    uint32_t *group_tris = (uint32_t *)m->mesh_dev, *unit_tris = (uint32_t *)((char *)m->mesh_dev + off_units);
     uint64_t *unit_base = (uint64_t *)((char *)m->mesh_dev + off_base);
     uint64_t *base = (uint64_t *)m->mesh_host;
     const uint32_t *counts = (const uint32_t *)(base + units + 1);
-    HIPCHK(m, launch_mesh_count(A, row_tris, unit_tris, m->stream));
+    HIPCHK(m, launch_mesh_count(A, group_tris, unit_tris, m->stream));
     HIPCHK(m, hipMemcpyAsync((void *)counts, unit_tris, (size_t)units * 4, hipMemcpyDeviceToHost, m->stream));
     HIPCHK(m, hipStreamSynchronize(m->stream));
     uint64_t most = 0;
@@ -921,7 +922,7 @@ tsdf_status tsdf_mesh(tsdf_map *m, const int32_t lo[3], const int32_t hi[3], flo
             m->mesh_tris_cap = total * kTri;
         }
         HIPCHK(m, hipMemcpyAsync(unit_base, base, ((size_t)units + 1) * 8, hipMemcpyHostToDevice, m->stream));
-        HIPCHK(m, launch_mesh_emit(A, row_tris, unit_base, 0, units, 0, (float *)m->mesh_tris, m->stream));
+        HIPCHK(m, launch_mesh_emit(A, group_tris, unit_base, 0, units, 0, (float *)m->mesh_tris, m->stream));
         HIPCHK(m, hipMemcpyAsync(tris, m->mesh_tris, total * kTri, hipMemcpyDeviceToHost, m->stream));
         HIPCHK(m, hipStreamSynchronize(m->stream));
         return TSDF_OK;
@@ -959,7 +960,7 @@ tsdf_status tsdf_mesh(tsdf_map *m, const int32_t lo[3], const int32_t hi[3], flo
         const uint32_t u0 = parts[k0].u0, u1 = parts[k1 - 1].u1;
         hipError_t e = hipSuccess;
         if (base[u1] > base[u0])
-            e = launch_mesh_emit(A, row_tris, unit_base, u0, u1 - u0, base[u0],
+            e = launch_mesh_emit(A, group_tris, unit_base, u0, u1 - u0, base[u0],
                                  (float *)((char *)m->mesh_tris + (q & 1) * piece_bytes), m->stream);
         return e == hipSuccess ? hipEventRecord(emitted[q & 1], m->stream) : e;
     };

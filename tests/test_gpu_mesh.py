@@ -163,3 +163,20 @@ def test_mesh_of_a_thin_wide_window():
     want = np.concatenate(parts)
     assert g.shape == want.shape and np.array_equal(g, want)
     gm.close()
+
+
+@pytest.mark.parametrize("layers", [1, 2, 3, 4, 7, 8, 15, 16, 30, 31, 32])
+@pytest.mark.parametrize("rows", [(1, 1), (7, 9), (40, 37)])
+def test_mesh_of_thin_boxes(rows, layers):
+    """Short rows of cubes that share a wave, around every number of lanes that
+    a row may take: groups and units that are cut, the ring buffer's wrap inside
+    the box; bit-identical."""
+    dims, origin = (43, 41, 37), (-20, -13, -15)
+    gm, om = _random_pair(dims, origin, 0.95, 8)
+    lo = tuple(origin[a] + (dims[a] - c) // 2 for a, c in enumerate((*rows, layers)))
+    hi = tuple(lo[a] + c + 1 for a, c in enumerate((*rows, layers)))
+    g, o = gm.mesh(lo, hi), om.mesh(lo, hi)
+    say(rows, layers, g.shape)
+    assert g.shape == o.shape and np.array_equal(g, o)
+    gm.close()
+    om.close()
