@@ -191,6 +191,11 @@ void chunk_give(tsdf_map *m, Chunk &c)
 // bytes of a call on: below, the threads' start costs as much as they save.
 constexpr uint64_t kCrewBytes = (uint64_t)4 << 20;
 constexpr int kCrewHelpers = 7;
+// A readback of at most this many resident bytes leaves without slots, events and
+// copy commands, packed into pinned host memory by the kernel: 16^3 voxels 28 -> 18
+// us, 32^3 48 -> 22, 64^3 87 -> 60, 80^3 (2 MB) 126 -> 101. (Larger ones by the slots:
+// the host's copies then take longer than the link's.)
+constexpr uint64_t kDirectBytes = (uint64_t)1 << 21;
 // Below this a map's first mesh takes no staging.
 constexpr uint64_t kFirstBytes = (uint64_t)32 << 20;
 
@@ -1481,11 +1486,6 @@ tsdf_status tsdf_readback(tsdf_map *m, const int32_t lo[3], const int32_t hi[3],
     }
     A.ny = (uint32_t)std::max<int64_t>(rn[1], 1);
     A.nz = (uint32_t)std::max<int64_t>(rn[2], 1);
-    hipEvent_t copied[kSlots];
-    for (hipEvent_t &ev : copied) ev = take_event(m);
-    hipError_t e = hipSuccess;
-    for (hipEvent_t ev : copied)
-        if (!ev) e = hipErrorOutOfMemory;
     struct Copy {
         const int16_t *src;        // the part's first array, then its second
         int64_t l0, n;             // its lines
@@ -1509,6 +1509,30 @@ tsdf_status tsdf_readback(tsdf_map *m, const int32_t lo[3], const int32_t hi[3],
         for (int64_t l = a0; l < a1; ++l)
             memcpy(dst_of(which, C.l0 + l), C.src + (which ? C.n * rn[2] : 0) + l * rn[2], (size_t)rn[2] * sizeof(int16_t));
     };
+    auto bind_lines = [&](Copy &C, const void *src, int64_t l0, int64_t n) -> int64_t {  // the parts of the job
+        C.src = (const int16_t *)src;
+        C.l0 = l0;
+        C.n = n;
+        if (!whole) return (n + 511) / 512 * 2;
+        for (int w = 0; w < 2; ++w) C.pages[w] = PageParts(dst_of(w, l0), (uint64_t)(n * rn[2]) * sizeof(int16_t));
+        return C.pages[0].count() + C.pages[1].count();
+    };
+    if (lines > 0 && (uint64_t)(lines * rn[2]) * 4 <= kDirectBytes) {
+        // a small result is packed into pinned host memory by the kernel itself
+        HIPCHK(m, prof_start(m, TSDF_KERNEL_PACK));
+        HIPCHK(m, launch_pack_lines(A, 0, (uint32_t)lines, m->stage_host, m->stream));
+        HIPCHK(m, prof_stop(m, TSDF_KERNEL_PACK));
+        for (int64_t p = 0; p < fill.parts; ++p) fill_part(p);
+        HIPCHK(m, hipStreamSynchronize(m->stream));
+        const int64_t n = bind_lines(copy[0], m->stage_host, 0, lines);
+        for (int64_t p = 0; p < n; ++p) copy_part(copy[0], p);
+        return TSDF_OK;
+    }
+    hipEvent_t copied[kSlots];
+    for (hipEvent_t &ev : copied) ev = take_event(m);
+    hipError_t e = hipSuccess;
+    for (hipEvent_t ev : copied)
+        if (!ev) e = hipErrorOutOfMemory;
     struct Bound {
         decltype(copy_part) *fn;
         const Copy *c;
@@ -1536,16 +1560,8 @@ tsdf_status tsdf_readback(tsdf_map *m, const int32_t lo[3], const int32_t hi[3],
             },
             [&](size_t k, Crew::Job *job) {
                 Copy &C = copy[k % kSlots];
-                C.src = (const int16_t *)((const char *)m->stage_host + (k % kSlots) * slot);
-                C.l0 = (int64_t)k * per_slot;
-                C.n = std::min<int64_t>(per_slot, lines - C.l0);
-                if (whole) {
-                    for (int w = 0; w < 2; ++w)
-                        C.pages[w] = PageParts(dst_of(w, C.l0), (uint64_t)(C.n * rn[2]) * sizeof(int16_t));
-                    job->parts = C.pages[0].count() + C.pages[1].count();
-                } else {
-                    job->parts = (C.n + 511) / 512 * 2;
-                }
+                const int64_t l0 = (int64_t)k * per_slot;
+                job->parts = bind_lines(C, (const char *)m->stage_host + (k % kSlots) * slot, l0, std::min<int64_t>(per_slot, lines - l0));
                 bound[k % kSlots] = Bound{&copy_part, &C};
                 job->call = [](void *b, int64_t p) { (*((Bound *)b)->fn)(*((Bound *)b)->c, p); };
                 job->arg = &bound[k % kSlots];

@@ -68,3 +68,17 @@ def test_readback_of_nothing_and_errors(pair):
         lo, hi = (C.c_int32 * 3)(0, 0, 0), (C.c_int32 * 3)(1, -1, 1)
         one = np.zeros(1, np.int16).ctypes.data_as(C.POINTER(C.c_int16))
         _abi.check(_abi.lib().tsdf_readback(gm.handle, lo, hi, one, one), "tsdf_readback")
+
+
+@pytest.mark.parametrize("size", [(16, 16, 16), (64, 64, 64), (128, 64, 64), (129, 64, 64), (128, 64, 65), (1, 190, 122), (210, 1, 122),
+                                  (23, 190, 120), (22, 190, 122), (128, 128, 31), (600, 700, 1)])
+@pytest.mark.parametrize("at", [(0, 0, 0), (-9, 5, -3), (-90, 30, 2)])
+def test_readback_around_the_size_that_leaves_without_copies(pair, size, at):
+    """Boxes with up to 2 MiB resident (524,288 voxels) leave by the kernel's own
+    writes, larger ones through slots; in the window, across its edges, half in
+    the store."""
+    gm, om = pair
+    lo = tuple(MOVED[a] + at[a] for a in range(3))
+    lo, hi = _box(lo, size)
+    for g, o in zip(gm.readback(lo, hi), om.readback(lo, hi)):
+        assert g.shape == o.shape and np.array_equal(g, o)
