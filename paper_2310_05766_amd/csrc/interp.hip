@@ -52,6 +52,8 @@
 // applies to rays of r < 2^30 (|D|^2 < 2^62); h is capped at 65535 (64
 // voxels), so a fill segment spans |2 e_a| < 2^17 per axis, the range the
 // exact walk is built for.
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace tsdf {
@@ -520,15 +522,35 @@ __global__ __launch_bounds__(256) void k_interp_merge(InterpScan P, int64_t nvox
 // --- carving with 32-bit keys ----------------------------------------------
 
 constexpr uint8_t kNoMark = 0xff, kMarkFree = 1, kMarkTau = 2, kMarkKey = 4;
+constexpr int kMarkQuads = 2, kMarkGroup = kMarkQuads * 1024;  // marks of a wave of the merge
+
+// Where the window is large and the scan small for it, a byte per group of marks
+// (in P.touched, which these scans have no other use for) tells the merge whether
+// it holds any, or it would read the whole window for every scan; read first, as
+// its few lines are hot. A look per newly marked voxel costs the band and the free
+// space of 128 x 1024 points 18 us of 145, so the line lies where the merge of all
+// marks costs more: at 2^27 voxels, and at a third of them for each step that the
+// scan can take (points times the longest side). us a call, all marks / groups: 16
+// x 1024 points in 512 x 512 x 256 113 / 126, in 1024 x 1024 x 512 259 / 191, in
+// 1024^3 356 / 205; 2 x 256 points in 1024^3 248 / 80; 128 x 1024 points in 512 x 512
+// x 256 219 / 237, in 1024 x 1024 x 512 380 / 335, in 2048 x 2048 x 128 1099 / 1170.
+constexpr int64_t kGroupedWindow = (int64_t)1 << 27;
+__device__ __forceinline__ void touch_group(const InterpScan &P, uint32_t idx)
+{
+    uint8_t *t = &P.touched[idx / (uint32_t)kMarkGroup];
+    if (*t == 0) *t = 1;
+}
 
 // A candidate of the band to the volume, its voxel marked: 2 where |s| is tau,
 // else 4; 1 (an atomic). Marks 2 and 4 may overwrite each other: both are
 // stored only where some |s| below tau was offered, and there 2 costs the free
 // space an atomic and decides nothing.
+template <bool kGrouped>
 __device__ __forceinline__ uint32_t send_marked(const InterpScan &P, uint32_t idx, uint32_t key)
 {
     atomicMin(&P.keys32[slot_of_index(P, idx)], key);
     P.marks[idx] = (int32_t)(key >> P.key_shift) == P.rp.tau ? kMarkTau : kMarkKey;
+    if (kGrouped) touch_group(P, idx);
     return 1;
 }
 
@@ -554,6 +576,7 @@ __device__ __forceinline__ int free_axis(const Ray &R, const RayParams &P)
 // a free voxel whose distance rounds below tau is met less than a voxel's
 // length before S: in the last two voxels along the longest axis (three are
 // walked).
+template <bool kGrouped>
 __global__ __launch_bounds__(kKeyRays * kBandLanes) void k_carve_band(InterpScan P)
 {
     __shared__ KeyTable<uint32_t, kKeyRays * kBandLanes, 11> T;
@@ -567,7 +590,7 @@ __global__ __launch_bounds__(kKeyRays * kBandLanes) void k_carve_band(InterpScan
     const int sub = (int)(threadIdx.x % kBandLanes);
     const auto offer = [&](const int32_t g[3], uint32_t key) -> uint32_t {
         const uint32_t idx = rel_index(P, g);
-        return T.offer(idx, key) ? 0u : send_marked(P, idx, key);
+        return T.offer(idx, key) ? 0u : send_marked<kGrouped>(P, idx, key);
     };
     uint64_t valid = 0, visits = 0, atomics = 0;
     int32_t q[3];
@@ -615,16 +638,20 @@ __global__ __launch_bounds__(kKeyRays * kBandLanes) void k_carve_band(InterpScan
             for (int k = 0; k < kBandLanes; ++k) more = more && walk_next(W);
         }
     }
-    atomics += T.flush([&](uint32_t idx, uint32_t key) { return send_marked(P, idx, key); });
+    atomics += T.flush([&](uint32_t idx, uint32_t key) { return send_marked<kGrouped>(P, idx, key); });
     block_add(valid, P, kCtrValid);
     block_add(visits, P, kCtrVisits);
     block_add(atomics, P, kCtrAtomics);
 }
 
 // A visit of the free space whose voxel held mark m: 1 when it took an atomic.
+template <bool kGrouped>
 __device__ __forceinline__ uint32_t mark_free(const InterpScan &P, uint32_t idx, uint8_t m, uint32_t key)
 {
-    if (m == kNoMark) P.marks[idx] = kMarkFree;
+    if (m == kNoMark) {
+        P.marks[idx] = kMarkFree;
+        if (kGrouped) touch_group(P, idx);
+    }
     if (m != kMarkTau) return 0;
     uint32_t *k = &P.keys32[slot_of_index(P, idx)];
     if (*k <= key) return 0;
@@ -641,6 +668,7 @@ __device__ __forceinline__ uint32_t mark_free(const InterpScan &P, uint32_t idx,
 // 32 x 2 and 64 x 1 points: 139, 79, 79, 88 us. 8, 16, 32 pieces: 88 (64 x 1),
 // 79, 109 us (fewer leave the launch waiting for its longest, more set down more
 // walks); 2, 4, 8 marks at a time 139, 142, 149 us (one ring).
+template <bool kGrouped>
 __global__ __launch_bounds__(kInterpBlock) void k_carve_free(InterpScan P, int64_t block0)
 {
     const int64_t w = ((block0 + (int64_t)blockIdx.x) * kInterpBlock + threadIdx.x) >> 6;
@@ -689,7 +717,7 @@ __global__ __launch_bounds__(kInterpBlock) void k_carve_free(InterpScan P, int64
                 for (int k = 0; k < kCarveAhead; ++k) m[k] = on[k] ? P.marks[at[k]] : kMarkKey;
 #pragma unroll
                 for (int k = 0; k < kCarveAhead; ++k) {
-                    atomics += mark_free(P, at[k], m[k], key);
+                    atomics += mark_free<kGrouped>(P, at[k], m[k], key);
                     visits += on[k] ? 1u : 0u;
                 }
             }
@@ -698,7 +726,7 @@ __global__ __launch_bounds__(kInterpBlock) void k_carve_free(InterpScan P, int64
             if (free_walk_init(R, P.rp, lo, hi, F)) do {
                     if (F.u < kFreeBias) break;  // from here on k_carve_band's
                     const uint32_t idx = rel_index(P, F.W.g);
-                    atomics += mark_free(P, idx, P.marks[idx], key);
+                    atomics += mark_free<kGrouped>(P, idx, P.marks[idx], key);
                     ++visits;
                 } while (free_walk_next(F));
         }
@@ -713,8 +741,7 @@ __global__ __launch_bounds__(kInterpBlock) void k_carve_free(InterpScan P, int64
 // carved points, 330 thousand runs of 64 voxels read and written, about 280 MB
 // in 76 us. 1, 2, 4 K marks a wave: 78, 76, 82 us. (Whole runs stored, changed or
 // not: 82 us.)
-constexpr int kMarkQuads = 2, kMarkGroup = kMarkQuads * 1024;
-
+template <bool kGrouped>
 __global__ __launch_bounds__(256) void k_carve_merge(InterpScan P, int64_t nvox)
 {
     __shared__ uint4 s_mark[4][kMarkQuads * 64];
@@ -726,82 +753,91 @@ __global__ __launch_bounds__(256) void k_carve_merge(InterpScan P, int64_t nvox)
     uint4 *mine = s_mark[threadIdx.x / 64];
     const uint8_t *bytes = reinterpret_cast<const uint8_t *>(mine);
     const bool rows = P.dims[2] % 64 == 0;
-    for (int64_t gi = wave; gi < ngroups; gi += waves) {
-        // (the marks are padded to whole groups)
-        uint4 *m = reinterpret_cast<uint4 *>(P.marks + gi * kMarkGroup);
-        uint64_t mask = 0;
+    // the wave's groups, wave + k waves, 64 at a time: a lane looks at one
+    for (int64_t g0 = wave; g0 < ngroups; g0 += 64 * waves) {
+        const int64_t own = g0 + lane * waves;
+        const bool hold = own < ngroups && (!kGrouped || P.touched[own] != 0);
+        if (hold && kGrouped) P.touched[own] = 0;
+        uint64_t held = __ballot(hold);
+        while (held) {
+            const int64_t gi = g0 + __builtin_ctzll(held) * waves;
+            held &= held - 1;
+            // (the marks are padded to whole groups)
+            uint4 *m = reinterpret_cast<uint4 *>(P.marks + gi * kMarkGroup);
+            uint64_t mask = 0;
 #pragma unroll
-        for (int k = 0; k < kMarkQuads; ++k) {
-            // 16 runs of four lanes each: run r of them in bit 4 r, then in bit r
-            const uint4 v = m[64 * k + lane];
-            mine[64 * k + lane] = v;
-            const bool any = (v.x & v.y & v.z & v.w) != 0xffffffffu;
-            if (any) m[64 * k + lane] = make_uint4(0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu);
-            uint64_t some = __ballot(any);
-            some |= some >> 1;
-            some |= some >> 2;
-            some &= 0x1111111111111111ull;
-            some = (some | some >> 3) & 0x0303030303030303ull;
-            some = (some | some >> 6) & 0x000f000f000f000full;
-            some = (some | some >> 12) & 0x000000ff000000ffull;
-            some = (some | some >> 24) & 0xffffull;
-            mask |= some << (16 * k);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        while (mask) {
-            uint32_t j[kMergeBatch];
-            uint8_t f[kMergeBatch];
-#pragma unroll
-            for (int b = 0; b < kMergeBatch; ++b) {
-                f[b] = kNoMark;
-                j[b] = 0;
-                if (mask) {
-                    const uint32_t run = (uint32_t)__builtin_ctzll(mask);
-                    j[b] = (uint32_t)(gi * kMarkGroup) + run * 64u + (uint32_t)lane;
-                    mask &= mask - 1;
-                    f[b] = bytes[run * 64u + (uint32_t)lane];
-                }
+            for (int k = 0; k < kMarkQuads; ++k) {
+                // 16 runs of four lanes each: run r of them in bit 4 r, then in bit r
+                const uint4 v = m[64 * k + lane];
+                mine[64 * k + lane] = v;
+                const bool any = (v.x & v.y & v.z & v.w) != 0xffffffffu;
+                if (any) m[64 * k + lane] = make_uint4(0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu);
+                uint64_t some = __ballot(any);
+                some |= some >> 1;
+                some |= some >> 2;
+                some &= 0x1111111111111111ull;
+                some = (some | some >> 3) & 0x0303030303030303ull;
+                some = (some | some >> 6) & 0x000f000f000f000full;
+                some = (some | some >> 12) & 0x000000ff000000ffull;
+                some = (some | some >> 24) & 0xffffull;
+                mask |= some << (16 * k);
             }
-            uint32_t sl[kMergeBatch], key[kMergeBatch];
-            int16_t sv[kMergeBatch], wv[kMergeBatch];
-            // (where a row is whole runs, a run's row is the wave's: its
-            // divisions are scalar)
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            while (mask) {
+                uint32_t j[kMergeBatch];
+                uint8_t f[kMergeBatch];
 #pragma unroll
-            for (int b = 0; b < kMergeBatch; ++b) {
-                sl[b] = 0;
-                key[b] = (uint32_t)P.rp.tau << P.key_shift;
-                sv[b] = wv[b] = 0;
-                if (f[b] != kNoMark) {
-                    if (rows) {
-                        const uint32_t j0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(j[b] & ~63u));
-                        const uint32_t s0 = slot_of_index(P, j0), z0 = j0 % (uint32_t)P.dims[2];
-                        // (the slot of the run's row and its z, wrapped per lane)
-                        int32_t z = (int32_t)(z0 + (j[b] & 63u)) + P.ring0[2];
-                        z -= z >= P.dims[2] ? P.dims[2] : 0;
-                        sl[b] = s0 / (uint32_t)P.dims[2] * (uint32_t)P.dims[2] + (uint32_t)z;
-                    } else {
-                        sl[b] = slot_of_index(P, j[b]);
+                for (int b = 0; b < kMergeBatch; ++b) {
+                    f[b] = kNoMark;
+                    j[b] = 0;
+                    if (mask) {
+                        const uint32_t run = (uint32_t)__builtin_ctzll(mask);
+                        j[b] = (uint32_t)(gi * kMarkGroup) + run * 64u + (uint32_t)lane;
+                        mask &= mask - 1;
+                        f[b] = bytes[run * 64u + (uint32_t)lane];
                     }
-                    if (f[b] != kMarkFree) key[b] = P.keys32[sl[b]];
-                    sv[b] = P.sdf[sl[b]];
-                    wv[b] = P.w[sl[b]];
+                }
+                uint32_t sl[kMergeBatch], key[kMergeBatch];
+                int16_t sv[kMergeBatch], wv[kMergeBatch];
+                // (where a row is whole runs, a run's row is the wave's: its
+                // divisions are scalar)
+#pragma unroll
+                for (int b = 0; b < kMergeBatch; ++b) {
+                    sl[b] = 0;
+                    key[b] = (uint32_t)P.rp.tau << P.key_shift;
+                    sv[b] = wv[b] = 0;
+                    if (f[b] != kNoMark) {
+                        if (rows) {
+                            const uint32_t j0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(j[b] & ~63u));
+                            const uint32_t s0 = slot_of_index(P, j0), z0 = j0 % (uint32_t)P.dims[2];
+                            // (the slot of the run's row and its z, wrapped per lane)
+                            int32_t z = (int32_t)(z0 + (j[b] & 63u)) + P.ring0[2];
+                            z -= z >= P.dims[2] ? P.dims[2] : 0;
+                            sl[b] = s0 / (uint32_t)P.dims[2] * (uint32_t)P.dims[2] + (uint32_t)z;
+                        } else {
+                            sl[b] = slot_of_index(P, j[b]);
+                        }
+                        if (f[b] != kMarkFree) key[b] = P.keys32[sl[b]];
+                        sv[b] = P.sdf[sl[b]];
+                        wv[b] = P.w[sl[b]];
+                    }
+                }
+#pragma unroll
+                for (int b = 0; b < kMergeBatch; ++b) {
+                    if (f[b] == kNoMark) continue;
+                    const int32_t gw = wv[b];
+                    P.sdf[sl[b]] = (int16_t)rdiv_small(sv[b] * gw + tile_key_sdf(key[b], P.key_shift), gw + 1);
+                    P.w[sl[b]] = (int16_t)(gw + 1 < P.w_max ? gw + 1 : P.w_max);
+                    if (f[b] != kMarkFree) P.keys32[sl[b]] = 0xffffffffu;
+                    ++updated;
                 }
             }
-#pragma unroll
-            for (int b = 0; b < kMergeBatch; ++b) {
-                if (f[b] == kNoMark) continue;
-                const int32_t gw = wv[b];
-                P.sdf[sl[b]] = (int16_t)rdiv_small(sv[b] * gw + tile_key_sdf(key[b], P.key_shift), gw + 1);
-                P.w[sl[b]] = (int16_t)(gw + 1 < P.w_max ? gw + 1 : P.w_max);
-                if (f[b] != kMarkFree) P.keys32[sl[b]] = 0xffffffffu;
-                ++updated;
-            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
     block_add(updated, P, kCtrUpdated);
 }
@@ -818,20 +854,30 @@ void launch_interp_scan(const InterpScan &P, uint32_t blocks, hipStream_t stream
     }
 }
 
+// The band and the free space of a carving scan with 32-bit keys.
+template <bool kGrouped>
+void launch_carve(const InterpScan &P, hipStream_t stream)
+{
+    hipLaunchKernelGGL(k_carve_band<kGrouped>, dim3((uint32_t)((P.n + kKeyRays - 1) / kKeyRays)), dim3(kKeyRays * kBandLanes), 0,
+                       stream, P);
+    const int64_t total = (P.n + 63) / 64 * kCarvePieces * 64 / kInterpBlock + 1, per = (int64_t)1 << 23;
+    for (int64_t b0 = 0; b0 < total; b0 += per) {
+        const int64_t nb = total - b0 < per ? total - b0 : per;
+        hipLaunchKernelGGL(k_carve_free<kGrouped>, dim3((uint32_t)nb), dim3(kInterpBlock), 0, stream, P, b0);
+    }
+}
+
 }  // namespace
 
 hipError_t launch_interp(const InterpScan &P, int64_t nvox, hipStream_t stream)
 {
+    const int32_t side = std::max(P.dims[0], std::max(P.dims[1], P.dims[2]));
+    const bool grouped = nvox > kGroupedWindow && nvox / 3 > P.n * side;
     if (P.n > 0) {
         const int64_t blocks = (P.n + kInterpBlock - 1) / kInterpBlock;
         if (P.carve && P.key_shift) {
-            hipLaunchKernelGGL(k_carve_band, dim3((uint32_t)((P.n + kKeyRays - 1) / kKeyRays)), dim3(kKeyRays * kBandLanes), 0,
-                               stream, P);
-            const int64_t total = (P.n + 63) / 64 * kCarvePieces * 64 / kInterpBlock + 1, per = (int64_t)1 << 23;
-            for (int64_t b0 = 0; b0 < total; b0 += per) {
-                const int64_t nb = total - b0 < per ? total - b0 : per;
-                hipLaunchKernelGGL(k_carve_free, dim3((uint32_t)nb), dim3(kInterpBlock), 0, stream, P, b0);
-            }
+            if (grouped) launch_carve<true>(P, stream);
+            else launch_carve<false>(P, stream);
         } else if (P.carve) {
             // chunks of a ray: as many slabs as the window's longest side
             // spans, plus one for a slab boundary inside it
@@ -853,7 +899,9 @@ hipError_t launch_interp(const InterpScan &P, int64_t nvox, hipStream_t stream)
     if (mblocks > 8192) mblocks = 8192;
     if (P.carve && P.key_shift) {
         mblocks = (nvox + 4 * kMarkGroup - 1) / (4 * kMarkGroup);
-        hipLaunchKernelGGL(k_carve_merge, dim3((uint32_t)(mblocks < 8192 ? mblocks : 8192)), dim3(256), 0, stream, P, nvox);
+        const dim3 grid((uint32_t)(mblocks < 8192 ? mblocks : 8192));
+        if (grouped) hipLaunchKernelGGL(k_carve_merge<true>, grid, dim3(256), 0, stream, P, nvox);
+        else hipLaunchKernelGGL(k_carve_merge<false>, grid, dim3(256), 0, stream, P, nvox);
         return hipGetLastError();
     }
     const dim3 mg((uint32_t)(mblocks > 0 ? mblocks : 1));

@@ -279,3 +279,28 @@ def test_key_widths_of_the_key_volume(dims, tau, widths):
         assert same(gm, om, dims)
     gm.close()
     om.close()
+
+
+@pytest.mark.parametrize("dims", [(640, 512, 412), (576, 512, 512)])
+def test_carving_in_windows_whose_marks_are_grouped(dims):
+    """Windows of more than 2^27 voxels, where the merge goes by groups of marks:
+    carving scans, an interpolating one between (the bytes of groups are its
+    bytes of runs), rows that are whole runs and rows that are not."""
+    from paper_2310_05766_amd.tsdf import TsdfMap
+    assert dims[0] * dims[1] * dims[2] > 1 << 27
+    origin = tuple(-(n // 2) + 3 for n in dims)
+    spec = (dims, origin, 0.05, 4096, 64)
+    gm, om = TsdfMap(*spec), oracle.OracleMap(*spec)
+    for k, mode in enumerate(("carve", "carve", "interpolate", "carve")):
+        for m in (gm, om):
+            m.set_carving(False)
+            m.set_interpolation(*((30.0, 64) if mode == "interpolate" else (0.0, 0)))
+            m.set_carving(mode == "carve")
+        xyz, pose = synth.fuzz_scan((113, k), 3000, extent_m=18.0, nan_frac=0.05), synth.fuzz_pose((114, k), 2.0)
+        say(dims, mode)
+        assert gm.integrate(xyz, pose, stats=True) == om.integrate(xyz, pose), k
+    hi = tuple(origin[a] + dims[a] for a in range(3))
+    g, o = gm.readback(origin, hi), om.readback(origin, hi)
+    assert np.array_equal(g[0], o[0]) and np.array_equal(g[1], o[1])
+    gm.close()
+    om.close()
