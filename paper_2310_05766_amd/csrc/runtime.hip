@@ -198,6 +198,33 @@ constexpr int kCrewHelpers = 7;
 constexpr uint64_t kDirectBytes = (uint64_t)1 << 21;
 // Below this a map's first mesh takes no staging.
 constexpr uint64_t kFirstBytes = (uint64_t)32 << 20;
+// What a map keeps from one mesh to the next, at most: two pieces of triangles
+// (two times 16 slots of 2 MiB) and 16 MiB each of counts and places; and the
+// staging that a mesh may ask for.
+constexpr size_t kMeshKeepTris = (size_t)64 << 20, kMeshKeep = (size_t)16 << 20, kMeshStage = (size_t)64 << 20;
+
+// Gives back what lies above that when a mesh ends.
+struct MeshKept {
+    tsdf_map *m;
+    ~MeshKept()
+    {
+        if (m->mesh_tris_cap > kMeshKeepTris) {
+            (void)hipFree(m->mesh_tris);
+            m->mesh_tris = nullptr;
+            m->mesh_tris_cap = 0;
+        }
+        if (m->mesh_dev_cap > kMeshKeep) {
+            (void)hipFree(m->mesh_dev);
+            m->mesh_dev = nullptr;
+            m->mesh_dev_cap = 0;
+        }
+        if (m->mesh_host_cap > kMeshKeep) {
+            (void)hipHostFree(m->mesh_host);
+            m->mesh_host = nullptr;
+            m->mesh_host_cap = 0;
+        }
+    }
+};
 
 // Staging of whole-chunk shifts: kShiftChunks chunks out and kShiftChunks in
 // per round trip.
@@ -871,6 +898,7 @@ tsdf_status tsdf_mesh(tsdf_map *m, const int32_t lo[3], const int32_t hi[3], flo
     *n_tris = 0;
     if (nrows == 0 || A.n[2] == 0) return TSDF_OK;
     // counts per group of rows and per unit of groups; the units' places
+    const MeshKept kept{m};
     mesh_groups(A);
     const uint32_t units = mesh_units(A);
     const size_t off_units = (size_t)A.groups * 4, off_base = (off_units + (size_t)units * 4 + 7) / 8 * 8;
@@ -913,11 +941,13 @@ tsdf_status tsdf_mesh(tsdf_map *m, const int32_t lo[3], const int32_t hi[3], flo
     constexpr size_t kPieceSlots = 16;
     constexpr uint64_t kTri = 9 * sizeof(float);
     const int64_t stage = std::max<int64_t>(16 * kChunkVox, (int64_t)(most * kTri + 16) * kSlots / 4);
-    if (m->stage_cap < stage && (total * kTri < kCrewBytes || (total * kTri < kFirstBytes && !m->meshed))) {
+    if (m->stage_cap < stage &&
+        (total * kTri < kCrewBytes || (total * kTri < kFirstBytes && !m->meshed) || (uint64_t)stage * 4 > kMeshStage)) {
         // no staging yet, whose 16 MiB of pinned memory cost more than a
         // millisecond: few triangles, and a map's first ones up to kFirstBytes,
         // take one launch and one copy (0.5 MB: first 381 -> 256 us, later 126 ->
-        // 106; 5 MB: first 0.95 -> 0.58 ms, later, with staging, 0.37)
+        // 106; 5 MB: first 0.95 -> 0.58 ms, later, with staging, 0.37). So do units
+        // of more triangles than a slot should hold (tall windows).
         m->meshed = true;
         if (total * kTri > m->mesh_tris_cap) {
             if (m->mesh_tris) HIPCHK(m, hipFree(m->mesh_tris));

@@ -159,9 +159,13 @@ def test_mesh_of_a_thin_wide_window():
         small.close()
     say("mesh of", dims, "triangles", [p.shape[0] for p in parts])
     assert min(p.shape[0] for p in parts) > 1000
+    import torch
+    gm.synchronize()
+    free = torch.cuda.mem_get_info()[0]
     g = gm.mesh(origin, tuple(origin[a] + dims[a] for a in range(3)))
     want = np.concatenate(parts)
     assert g.shape == want.shape and np.array_equal(g, want)
+    assert free - torch.cuda.mem_get_info()[0] < 40 << 20  # (counts of all rows are given back)
     gm.close()
 
 
@@ -178,5 +182,23 @@ def test_mesh_of_thin_boxes(rows, layers):
     g, o = gm.mesh(lo, hi), om.mesh(lo, hi)
     say(rows, layers, g.shape)
     assert g.shape == o.shape and np.array_equal(g, o)
+    gm.close()
+    om.close()
+
+
+def test_mesh_of_a_tall_window():
+    """Units of more triangles than a staging slot should hold (16 rows of 9,000
+    cubes) leave without staging, and their memory is given back; twice."""
+    import torch
+    dims, origin = (5, 5, 9000), (-2, -3, -4500)
+    gm, om = _random_pair(dims, origin, 0.97, 9)
+    hi = tuple(origin[a] + dims[a] for a in range(3))
+    o = om.mesh(origin, hi)
+    free = torch.cuda.mem_get_info()[0]
+    for k in range(2):
+        g = gm.mesh(origin, hi)
+        say(dims, g.shape, g.nbytes)
+        assert g.shape == o.shape and np.array_equal(g, o)
+    assert g.nbytes * 8 > 64 << 20 and free - torch.cuda.mem_get_info()[0] < 80 << 20
     gm.close()
     om.close()
