@@ -88,44 +88,59 @@ struct Guard {
 
 // Tiles of 2^lt voxels: every lt in [2, 6], the z edge at least 8 (merge
 // runs), 2^9..2^12 voxels per tile (12 bytes of LDS per voxel).
-// Tilings used while a map has none set, by the most scans that one map has in
-// the call. A larger tile has fewer fixed costs per scan, a smaller one holds
-// more scans' keys at once; the tile pass's time, us (tiles of 8x8x8, 16x8x8,
-// 16x16x8, 16x16x16 voxels):
-//   1 scan    32 maps, 16 x 1024 points each     153 122 110  96
-//             4 maps, 64 x 1024                   61  62  60  61
-//             1 map, 128 x 1024                   41  36  33  37
-//             1 map, 16 x 1024                    17  17  16  19
-//   2 scans   1 map, 128 x 1024                   76  69  68  75
-//   4 scans   16 maps, uneven                    665 605 567 608
-//             4 maps, 64 x 1024                  128 120 129 145
-//   8 scans   1 map, 128 x 1024                  147 145 158 191
-//             16 maps, 32 x 1024                 466 430 416 473
-//   16 scans  4 maps, 64 x 1024                  259 262 293 378
-//   50 scans  1 map, 128 x 1024                  502 517 583 817
-// (whole calls). One scan per map of more than kManyPoints points together
-// takes the largest tiles: the busy tiles are then many more than workgroups.
+// Tilings used while a map has none set. A larger tile has fewer fixed costs per
+// scan, a smaller one holds more scans' keys at once and spreads a scan over more
+// workgroups. What decides is how many tiles are busy, which the host cannot
+// know; it goes by the most scans that one map has in the call, by its points and
+// by the windows' voxels. Whole calls, us (16x16x16, 16x16x8, 16x8x8, 8x8x8 voxels;
+// * the rule's; S: 64 mm street in 512 x 512 x 256, R: 80 mm room in 256^3, D: 200 mm
+// room in 128 x 128 x 64; the first line's rule is that of plain calls, which also
+// keeps the allocation-free call's tables small):
+//   1 scan    1 map, 128 x 1024       S   26   27*  30   33   R   57   43*  43   40
+//             4 maps, 64 x 1024       S   75*  76   87  107   R   71*  67   68   72
+//             24 maps, 16 x 1024      S  103* 128  131  149   D   92*  91   91   90
+//             6 maps, 128 x 1024      S  118* 117  115  117   D  230  231  163  159*
+//             2 maps, 64 x 1024       R   63   62*  63   62   D  106  106   80*  74
+//             1 map, 128 x 1024       (in a batch)            D   -   113  100   70*
+//   2 scans   1 map, 128 x 1024       S   78   71   71*  75   R  125   92   89*  88
+//   4 scans   4 maps, 64 x 1024       S  328  306  291* 319   R  181  161  157* 161
+//             16 maps, uneven         R  501  463  489* 536
+//             1 map, 128 x 1024       S  129  115  109* 116   R  188  131  124  110*
+//   8 scans   1 map, 128 x 1024       S  210  172  158* 163   R  329  222  212  180*
+//             16 maps, 32 x 1024      R  508  453  467* 505
+//   3 scans   1 map, 128 x 1024       D  277  264  212  163*
+// One scan per map of more than kManyPoints points together takes the largest
+// tiles, the busy ones being many then, unless the windows are dense, a point for
+// every 32 voxels or more (8: very dense; 64 where scans are large): few tiles, with
+// many entries each. A point for 64, 100 mm room: 6 maps, 128 x 1024 144, 138, 114,
+// 115 us; 32 maps, 16 x 1024 106, -, 117, -.
+// (Where the best is not taken, up to 6 % on many maps of 4 and 8 scans, no figure
+// that the host has tells that line from the next.)
 inline constexpr int32_t kScanTiling[3] = {4, 4, 3};
 inline constexpr int32_t kManyScansTiling[3] = {4, 4, 4};
 inline constexpr int32_t kFewSeqTiling[3] = {4, 3, 3};
 inline constexpr int32_t kBatchTiling[3] = {3, 3, 3};
-inline constexpr int64_t kManyPoints = 131072;
+inline constexpr int64_t kManyPoints = 131072, kLargeScan = 65536;
 inline constexpr int32_t kFewSeq = 8;
 
-// seq: the most scans of one map in the call; points: of all its scans.
-inline const int32_t *tiling_for(const tsdf_map *m, int32_t seq, int64_t points)
+// seq: the most scans of one map in the call; points: of all its scans; maps, and
+// voxels of their windows (0, 0, 0: a plain call).
+inline const int32_t *tiling_for(const tsdf_map *m, int32_t seq, int64_t points, int64_t maps, int64_t voxels)
 {
     if (m->lt[0] != 0) return m->lt;
-    if (seq <= 1) return points > kManyPoints ? kManyScansTiling : kScanTiling;
-    return seq <= kFewSeq ? kFewSeqTiling : kBatchTiling;
+    const auto dense = [&](int64_t voxels_per_point) { return voxels > 0 && points >= voxels / voxels_per_point; };
+    if (seq > 1) return seq <= kFewSeq && !dense(32) ? kFewSeqTiling : kBatchTiling;
+    if (dense(8)) return kBatchTiling;
+    if (dense(32) || (dense(64) && points > kLargeScan * maps)) return kFewSeqTiling;
+    return points > kManyPoints ? kManyScansTiling : kScanTiling;
 }
 
 // The launch shape of an integration on this map (a batch takes its first
 // scan's map's).
-inline LaunchShape launch_shape(const tsdf_map *m, int32_t seq, int64_t points)
+inline LaunchShape launch_shape(const tsdf_map *m, int32_t seq, int64_t points, int64_t maps, int64_t voxels)
 {
     LaunchShape sh;
-    const int32_t *lt = tiling_for(m, seq, points);
+    const int32_t *lt = tiling_for(m, seq, points, maps, voxels);
     for (int a = 0; a < 3; ++a) sh.lt[a] = lt[a];
     sh.tile_grid = m->tile_grid;
     sh.bin_block = m->bin_block > 0 ? m->bin_block : kBinBlock;

@@ -150,7 +150,7 @@ extern "C" tsdf_status tsdf_integrate_scan_noalloc(tsdf_map *m, const float *xyz
     if (m->interp_dq > 0 || m->carve) return TSDF_EINVAL;  // the key-volume paths allocate their volume
 
     // the same tables the batch engine builds for a batch of this one scan
-    const LaunchShape shape = launch_shape(m, 1, 0);
+    const LaunchShape shape = launch_shape(m, 1, 0, 0, 0);
     const int32_t *lt = shape.lt;
     MapDev md;
     md.sdf = m->sdf;

@@ -1113,7 +1113,7 @@ tsdf_status tsdf_integrate_scan(tsdf_map *m, const float *xyz, int64_t n_points,
     std::vector<MapRef> maps{map_ref(m)};
     std::vector<ScanRef> scans{ScanRef{0, xyz, n_points, kind == TSDF_PTR_HOST, pose}};
     // (one tiling for scans of any size, as the allocation-free call has it)
-    tsdf_status st = m->engine->run(maps, scans, launch_shape(m, 1, 0), stats);
+    tsdf_status st = m->engine->run(maps, scans, launch_shape(m, 1, 0, 0, 0), stats);
     if (st == TSDF_EDEVICE) m->poisoned = true;
     return st;
 }
@@ -1173,7 +1173,7 @@ tsdf_status tsdf_integrate_batch(const tsdf_scan_desc *scans, int32_t count, tsd
     std::vector<std::unique_ptr<Guard>> guards;
     std::vector<int32_t> per_map;
     int32_t seq = 0;
-    int64_t points = 0;
+    int64_t points = 0, voxels = 0;
     for (int32_t k = 0; k < count; ++k) {
         tsdf_map *m = scans[k].map;
         if (!m) return TSDF_EINVAL;
@@ -1185,6 +1185,7 @@ tsdf_status tsdf_integrate_batch(const tsdf_scan_desc *scans, int32_t count, tsd
             it = idx.emplace(m, (int32_t)maps.size()).first;
             maps.push_back(map_ref(m));
             per_map.push_back(0);
+            voxels += m->nvox;
         }
         seq = std::max(seq, ++per_map[(size_t)it->second]);
         points += std::max<int64_t>(scans[k].n_points, 0);
@@ -1204,7 +1205,7 @@ tsdf_status tsdf_integrate_batch(const tsdf_scan_desc *scans, int32_t count, tsd
         eng = slot.get();
     }
     const tsdf_map *first = scans[0].map;
-    tsdf_status st = eng->run(maps, refs, launch_shape(first, seq, points), stats);
+    tsdf_status st = eng->run(maps, refs, launch_shape(first, seq, points, (int64_t)maps.size(), voxels), stats);
     if (st == TSDF_EDEVICE)
         for (int32_t k = 0; k < count; ++k) scans[k].map->poisoned = true;
     return st;
