@@ -432,7 +432,7 @@ tsdf_status Engine::run_chunk(const std::vector<MapRef> &maps, const std::vector
         d.map = slot_of[s.map];
         d.seq = seq[k];
         d.block0 = block0[k];
-        d.row = row_lengths(s.n, kBinPatch, d.lengths);
+        d.row = row_lengths(!once && emit > kPatchTiles ? 0 : s.n, kBinPatch, d.lengths);
         rows = rows || (!one && d.lengths[0].length);
         d.pad = 0;
         const uint32_t nb = (uint32_t)((s.n + bb - 1) / bb);

@@ -53,6 +53,14 @@ struct ScanDev {
     uint32_t pad;
 };
 constexpr PatchKind kBinPatch = {32, 32768, 3.5f};
+// Where a band may cross more tiles than this, two binning passes take runs: what a
+// ray has beyond kMaxEmit goes to its run by an atomic of its own, and the points of
+// a patch meet in the same runs. 20 scans of 64 x 1024 and 128 x 1024 points into one
+// map, us, patches / runs: at most 9 tiles, room 378 and 714 / 350 and 654, street 341
+// and 493 / 354 and 519; 12 tiles, room 674 and 1378 / 575 and 1180, street 648 and
+// 851 / 497 and 816; 17 tiles, street 1555 and 1752 / 1137 and 1709. (One pass, 128 x
+// 1024 points, 17 tiles, room: 210 / 219.)
+constexpr uint32_t kPatchTiles = 10;
 
 struct BatchHdr {
     int32_t lt[3];

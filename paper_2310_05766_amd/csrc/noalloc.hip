@@ -179,7 +179,7 @@ extern "C" tsdf_status tsdf_integrate_scan_noalloc(tsdf_map *m, const float *xyz
     sd.map = 0;
     sd.seq = 0;
     sd.block0 = 0;
-    sd.row = row_lengths(n_points, kBinPatch, sd.lengths);
+    sd.row = row_lengths(max_tiles_per_ray(m->d.tau_q10, lt) > (int32_t)kPatchTiles ? 0 : n_points, kBinPatch, sd.lengths);
     sd.pad = 0;
     const uint64_t nblocks = (uint64_t)((n_points + shape.bin_block - 1) / shape.bin_block);
     const uint64_t cap = (uint64_t)n_points * (uint64_t)max_tiles_per_ray(m->d.tau_q10, lt) + 1024;
