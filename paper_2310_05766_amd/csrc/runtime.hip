@@ -517,10 +517,17 @@ hipError_t through_slots(size_t parts, Crew &crew, const hipEvent_t copied[kSlot
     return e;
 }
 
+// (256 voxels between tests, so that the loop is vector code: voxel by voxel a
+// shift by a chunk of a window off the chunk grid took 1.8 or 2.4 ms, by where in a
+// cache line the loop lay)
 bool all_zero(const int16_t *a, const int16_t *b, int64_t n)
 {
-    for (int64_t i = 0; i < n; ++i)
-        if (a[i] | b[i]) return false;
+    for (int64_t i = 0; i < n;) {
+        const int64_t end = std::min<int64_t>(n, i + 256);
+        int16_t any = 0;
+        for (; i < end; ++i) any |= a[i] | b[i];
+        if (any) return false;
+    }
     return true;
 }
 
