@@ -772,7 +772,8 @@ static tsdf_status ensure_reg(tsdf_map *m)
 // points xyz (0 steps: the normal equations at M), on the map's stream;
 // synchronous, its outcome in m->reg_result. The launches of a run follow
 // each other without waiting for the host, kRegLaunches at a time: a run may
-// stop long before its limit.
+// stop long before its limit (of 30 steps at the first, for want of points: 87 us
+// with all 16, 34 where the host looks for the end before each).
 static tsdf_status reg_run(tsdf_map *m, const float *xyz, int64_t n, const double M[16], int32_t iterations,
                            double damping)
 {
@@ -799,7 +800,7 @@ static tsdf_status reg_run(tsdf_map *m, const float *xyz, int64_t n, const doubl
     out->done = 0;
     for (int64_t e = 0; e <= iterations && !out->done;) {
         const int64_t end = std::min<int64_t>((int64_t)iterations + 1, e + kRegLaunches);
-        for (; e < end; ++e) {
+        for (; e < end && !out->done; ++e) {
             A.first = e == 0;
             A.last = e == iterations;
             HIPCHK(m, launch_reg_step(A, m->stream));
