@@ -753,7 +753,7 @@ def main():
                     "steps": info["steps"], "ms_per_step": 1e3 * t_reg / max(info["steps"] + 1, 1),
                     "points_per_s": dev[k_reg].shape[0] * (info["steps"] + 1) / t_reg,
                     "translation_error_m": float(np.linalg.norm(P[:3, 3] - poses[k_reg][:3, 3])),
-                    "includes": "normal-equation kernel, 29-value readback and 6x6 solve per step, plus the "
+                    "includes": "normal-equation kernel with the 6x6 solve in its last block, per step, plus the "
                                 "final evaluation"}
     gm.close()
 

@@ -301,20 +301,21 @@ tsdf_status tsdf_mesh(tsdf_map *m, const int32_t lo[3], const int32_t hi[3], flo
 /* Candidate-buffer tiling of the integration: the window is cut into tiles
  * of 2^log2_tile[a] voxels per axis (each in [2, 6], z at least 3,
  * 2^9..2^12 voxels per tile; a tile's candidate keys live in 8 bytes of LDS
- * per voxel), handled by tile_workgroups persistent workgroups (0: as many
- * as fit the device). log2_tile = {0, 0, 0}, the initial setting, lets the
- * library choose per call (16 x 16 x 8 tiles for tsdf_integrate_scan; for
- * tsdf_integrate_batch by the most scans of one map, 16 x 16 x 16 down to
- * 8 x 8 x 8; a batch's tiling is that of its first scan's map);
- * tsdf_map_get_tiling then reports {0, 0, 0}. The arithmetic,
- * and so every result, is the same for every tiling. */
+ * per voxel, or 4 where tau and the point count let them fit), handled by
+ * tile_workgroups persistent workgroups (0: as many as fit the device).
+ * log2_tile = {0, 0, 0}, the initial setting, lets the library choose per
+ * call (16 x 16 x 8 tiles for tsdf_integrate_scan; for tsdf_integrate_batch
+ * by the most scans of one map, the points and the windows' voxels, 16 x 16
+ * x 16 down to 8 x 8 x 8; a batch's tiling is that of its first scan's map);
+ * tsdf_map_get_tiling then reports {0, 0, 0}. The arithmetic, and so every
+ * result, is the same for every tiling. */
 tsdf_status tsdf_map_set_tiling(tsdf_map *m, const int32_t log2_tile[3], int32_t tile_workgroups);
 tsdf_status tsdf_map_get_tiling(const tsdf_map *m, int32_t log2_tile[3], int32_t *tile_workgroups);
 
 /* Block sizes of the integration kernels: bin_block threads per binning
  * block, one scan point each (128, 256 or 512; a block's rays share one LDS
  * table of tile counts), and tile_block threads per tile workgroup (256 or
- * 512; a workgroup holds about 32 KB of candidate keys per 256 threads).
+ * 512; a workgroup holds about 25 KB of candidate keys per 256 threads).
  * 0 selects the default (256 for both); tsdf_map_get_blocks reports the
  * sizes in use. A batch uses its first scan's map's. The arithmetic, and so
  * every result, is the same for every choice; TSDF_EINVAL for other sizes. */

@@ -169,39 +169,22 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
     if (inl && kMode == kCount && threadIdx.x == 0) B.block_scan[blockIdx.x] = 0u;
     const uint32_t s = inl ? 0u : B.block_scan[blockIdx.x];
     const ScanDev &SD = inl ? I.scan : B.scans[s];
-    // one scan: the points of the likely patch are requested beside the samples
-    // that tell the row length (every block finds the same); several: k_rows has it
-    const int64_t n = SD.n;
-    const float *xyz = SD.xyz;
-    const uint32_t block = blockIdx.x - SD.block0;
-    int64_t i;
-    float px = 0.f, py = 0.f, pz = 0.f;
-    const auto request = [&](const Row &row) {
-        i = patch_point<kBinBlock, kBinPatch.rows>(block, threadIdx.x, row);
-        if (i < n) {
-            px = xyz[3 * i];
-            py = xyz[3 * i + 1];
-            pz = xyz[3 * i + 2];
-        }
-    };
-    const Row likely = uniform_row(SD.row);
-    request(likely);
+    // one scan: every block finds the same row length; several: k_rows has it
     const bool tries = inl && SD.lengths[0].length != 0;
-    if (tries && threadIdx.x < 64u) s_row = find_row(xyz, n, SD.lengths, kBinPatch.step);
+    if (tries && threadIdx.x < 64u) s_row = find_row(SD.xyz, SD.n, SD.lengths, kBinPatch.step);
     __syncthreads();
-    if (tries) {
-        const Row row = uniform_row(row_at(SD.lengths, s_row));
-        if (row.length != likely.length) request(row);
-        if (kMode == kCount && block == 0 && threadIdx.x == 0) B.scans[0].row = row;
-    }
+    const Row row = uniform_row(tries ? row_at(SD.lengths, s_row) : SD.row);
+    if (tries && kMode == kCount && blockIdx.x == 0 && threadIdx.x == 0) B.scans[0].row = row;
+    const int64_t i = patch_point<kBinBlock, kBinPatch.rows>(blockIdx.x - SD.block0, threadIdx.x, row);
     const MapDev &MD = inl ? I.map : B.maps[SD.map];
     const RayParams rp = SD.rp;
     Ray R;
     Walk W, Wv;  // the walk on the tile grid; the voxel walk's start (fill)
     bool active = false;
     int32_t q[3] = {0, 0, 0};
-    if (i < n) {
-        if (quantise(px, py, pz, rp, q) && make_ray(q, rp, R)) {
+    if (i < SD.n) {
+        const float *p = SD.xyz + 3 * i;
+        if (quantise(p[0], p[1], p[2], rp, q) && make_ray(q, rp, R)) {
             active = true;
             // the tiles of the band's voxels are the cells of the same exact
             // walk on the grid of tiles (floor of a floor division)

@@ -48,7 +48,7 @@ struct ScanDev {
     int32_t map;         // map slot in the batch
     int32_t seq;         // position among this map's scans in the batch
     uint32_t block0;     // first binning block of this scan
-    Row row;             // final, or likely until the lengths have been tried
+    Row row;             // final where there are no lengths to try; k_rows
     Row lengths[kRowLengths];
     uint32_t pad;
 };

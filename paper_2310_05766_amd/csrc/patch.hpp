@@ -49,10 +49,9 @@ inline Row row_of_length(uint32_t length, uint32_t rings, const PatchKind &kind)
     return Row{length, rings / kind.rows * length, (uint32_t)(((uint64_t)1 << 32) / length) + 1u};
 }
 
-// The row to take the points of a scan of n points by, and the lengths to try,
-// the shortest first (0: no more): n / rings for the numbers of rings that
-// sensors have, of at least 256 points. Without lengths to try the row is final,
-// else it is the likely one.
+// The row to take the points of a scan of n points by, where there are no lengths
+// to try; else these, the shortest first (0: no more): n / rings for the numbers
+// of rings that sensors have, of at least 256 points.
 inline Row row_lengths(int64_t n, const PatchKind &kind, Row lengths[kRowLengths])
 {
     static constexpr uint32_t kRings[] = {128, 64, 32, 16, 40, 80, 104, 96, 120, 112, 48, 56, 72, 88, 24, 20};
@@ -68,7 +67,7 @@ inline Row row_lengths(int64_t n, const PatchKind &kind, Row lengths[kRowLengths
         for (; at > 0 && length < lengths[at - 1].length; --at) lengths[at] = lengths[at - 1];
         lengths[at] = row_of_length(length, rings, kind);
     }
-    return lengths[0];
+    return Row{0, 0, 0};
 }
 
 // Sample j's first point: points at + length and at + kRowSpan exist for every
