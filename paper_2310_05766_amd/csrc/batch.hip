@@ -109,9 +109,9 @@ __global__ __launch_bounds__(256) void k_rows(BatchArrays B)
     const uint32_t s = blockIdx.x * 4u + threadIdx.x / 64u;
     if (s >= (uint32_t)B.hdr->nscans) return;
     ScanDev &SD = B.scans[s];
-    if (SD.lengths[0].length == 0) return;
-    const uint32_t k = find_row(SD.xyz, SD.n, SD.lengths, kBinPatch.step);
-    if (threadIdx.x % 64u == 0) SD.row = row_at(SD.lengths, k);
+    if (SD.rings == 0) return;
+    const Row row = find_row(SD.xyz, SD.n, SD.rings, kBinPatch);
+    if (threadIdx.x % 64u == 0) SD.row = row;
 }
 
 // kInline (the first pass only): the batch is one scan whose descriptors are
@@ -134,7 +134,8 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
     // per emitted entry: hash slot | crossing counts (7 bits per axis) << 10, and rank
     __shared__ uint32_t s_slot[kFill ? kMaxEmit * kBinBlock : 1];
     __shared__ uint16_t s_rank[kFill ? kMaxEmit * kBinBlock : 1];
-    __shared__ uint32_t s_valid, s_extra, s_new, s_job, s_row, s_sum[kBinBlock / 64];
+    __shared__ uint32_t s_valid, s_extra, s_new, s_job, s_sum[kBinBlock / 64];
+    __shared__ Row s_row;
     // a one-scan batch's descriptors come with the counting launch, which
     // stores them for the kernels after it
     constexpr bool inl = kFirst && kInline;
@@ -170,10 +171,10 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(BatchArrays B, InlineDesc I)
     const uint32_t s = inl ? 0u : B.block_scan[blockIdx.x];
     const ScanDev &SD = inl ? I.scan : B.scans[s];
     // one scan: every block finds the same row length; several: k_rows has it
-    const bool tries = inl && SD.lengths[0].length != 0;
-    if (tries && threadIdx.x < 64u) s_row = find_row(SD.xyz, SD.n, SD.lengths, kBinPatch.step);
+    const bool tries = inl && SD.rings != 0;
+    if (tries && threadIdx.x < 64u) s_row = find_row(SD.xyz, SD.n, SD.rings, kBinPatch);
     __syncthreads();
-    const Row row = uniform_row(tries ? row_at(SD.lengths, s_row) : SD.row);
+    const Row row = uniform_row(tries ? s_row : SD.row);
     if (tries && kMode == kCount && blockIdx.x == 0 && threadIdx.x == 0) B.scans[0].row = row;
     const int64_t i = patch_point<kBinBlock, kBinPatch.rows>(blockIdx.x - SD.block0, threadIdx.x, row);
     const MapDev &MD = inl ? I.map : B.maps[SD.map];

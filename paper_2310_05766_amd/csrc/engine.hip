@@ -432,9 +432,8 @@ tsdf_status Engine::run_chunk(const std::vector<MapRef> &maps, const std::vector
         d.map = slot_of[s.map];
         d.seq = seq[k];
         d.block0 = block0[k];
-        d.row = row_lengths(!once && emit > kPatchTiles ? 0 : s.n, kBinPatch, d.lengths);
-        rows = rows || (!one && d.lengths[0].length);
-        d.pad = 0;
+        d.row = row_rings(!once && emit > kPatchTiles ? 0 : s.n, kBinPatch, d.rings);
+        rows = rows || (!one && d.rings != 0);
         const uint32_t nb = (uint32_t)((s.n + bb - 1) / bb);
         for (uint32_t q = 0; q < nb; ++q) bs[block0[k] + q] = (uint32_t)k;
         ss[d.map * S + d.seq] = make_int4(d.rp.o[0], d.rp.o[1], d.rp.o[2], d.rp.tau);

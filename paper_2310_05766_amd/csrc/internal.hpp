@@ -49,8 +49,7 @@ struct ScanDev {
     int32_t seq;         // position among this map's scans in the batch
     uint32_t block0;     // first binning block of this scan
     Row row;             // final where there are no lengths to try; k_rows
-    Row lengths[kRowLengths];
-    uint32_t pad;
+    uint64_t rings;      // the lengths to try (row_rings), 0: none
 };
 constexpr PatchKind kBinPatch = {32, 32768, 3.5f};
 // Where a band may cross more tiles than this, two binning passes take runs: what a
@@ -152,34 +151,24 @@ struct BatchArrays {
     uint4 *nodes;          // [nblocks * nodes_per_block], one binning pass
 };
 
-// A row of a scan among the lengths to try (patch.hpp). A whole wave calls; its
-// index, or kRowLengths.
-__device__ __forceinline__ uint32_t find_row(const float *xyz, int64_t n, const Row lengths[kRowLengths], float step)
+// A scan's row among the lengths to try (patch.hpp). A whole wave calls.
+__device__ __forceinline__ Row find_row(const float *xyz, int64_t n, uint64_t rings, const PatchKind &kind)
 {
-    const uint32_t lane = __lane_id(), j = lane / kRowSamples;
-    uint32_t row = 0;
-#pragma unroll
-    for (int k = 0; k < kRowLengths; ++k) row = j == (uint32_t)k ? lengths[k].length : row;
+    const uint32_t lane = __lane_id(), j = lane / kRowSamples, mine = ring_at(rings, j);
     bool counts = false, fits = false;
-    if (row) {
-        const float *a = xyz + 3 * row_sample(n, lane % kRowSamples), *b = a + 3 * (int64_t)row, *c = a + 3 * kRowSpan;
+    if (mine) {
+        const float *a = xyz + 3 * row_sample(n, lane % kRowSamples), *b = a + 3 * (int64_t)((uint32_t)n / mine), *c = a + 3 * kRowSpan;
         const float pa[3] = {a[0], a[1], a[2]}, pb[3] = {b[0], b[1], b[2]}, pc[3] = {c[0], c[1], c[2]};
-        row_vote(pa, pb, pc, step, counts, fits);
+        row_vote(pa, pb, pc, kind.step, counts, fits);
     }
-    const uint64_t mine = ((1ull << kRowSamples) - 1) << (j * kRowSamples);
-    const int nc = __popcll(__ballot(counts) & mine), nf = __popcll(__ballot(fits) & mine);
+    const uint64_t lanes = ((1ull << kRowSamples) - 1) << (j * kRowSamples);
+    const int nc = __popcll(__ballot(counts) & lanes), nf = __popcll(__ballot(fits) & lanes);
     const uint64_t ok = __ballot(row_fits(nc, nf));
-    return ok ? (uint32_t)__builtin_ctzll(ok) / kRowSamples : kRowLengths;
+    if (!ok) return Row{0, 0, 0};
+    const uint32_t r = ring_at(rings, (uint32_t)__builtin_ctzll(ok) / kRowSamples);
+    return row_of((uint32_t)n / r, r, kind);
 }
-__device__ __forceinline__ Row row_at(const Row lengths[kRowLengths], uint32_t k)
-{
-    Row row{0, 0, 0};
-#pragma unroll
-    for (uint32_t j = 0; j < kRowLengths; ++j)
-        if (k == j) row = lengths[j];
-    return row;
-}
-// The same, held alike by all lanes, in scalar registers.
+// A row held alike by all lanes, in scalar registers.
 __device__ __forceinline__ Row uniform_row(const Row &row)
 {
     return Row{(uint32_t)__builtin_amdgcn_readfirstlane((int)row.length), (uint32_t)__builtin_amdgcn_readfirstlane((int)row.end),
@@ -254,7 +243,8 @@ struct InterpScan {
     uint32_t key_shift;
     uint32_t *keys32;
     uint8_t *marks;
-    Row row, lengths[kRowLengths];  // as in ScanDev
+    Row row;                       // as in ScanDev
+    uint64_t rings;
     Row *found;                    // from the band's kernel to the free space's
     int32_t want_stats;            // count valid points, visits and voxels updated
     unsigned long long *counters;  // [kinds][kCtrLines * kCtrStride], added to

@@ -242,11 +242,11 @@ template <typename Key>
 __global__ __launch_bounds__(kKeyRays * kFillLanes) void k_interp_scan(InterpScan P, uint32_t block0)
 {
     __shared__ KeyTable<Key, kKeyRays * kFillLanes, sizeof(Key) == 4 ? 12 : 11> T;
-    __shared__ uint32_t s_row;
-    const bool tries = P.lengths[0].length != 0;
-    if (tries && threadIdx.x < 64u) s_row = find_row(P.xyz, P.n, P.lengths, kKeyPatch.step);
+    __shared__ Row s_row;
+    const bool tries = P.rings != 0;
+    if (tries && threadIdx.x < 64u) s_row = find_row(P.xyz, P.n, P.rings, kKeyPatch);
     T.clear();
-    const Row row = tries ? uniform_row(row_at(P.lengths, s_row)) : P.row;
+    const Row row = tries ? uniform_row(s_row) : P.row;
     const int64_t i = patch_point<kKeyRays, kKeyPatch.rows>(block0 + blockIdx.x, threadIdx.x / kFillLanes, row);
     const int sub = (int)(threadIdx.x % kFillLanes);
     uint64_t valid = 0, visits = 0, atomics = 0;
@@ -580,11 +580,11 @@ template <bool kGrouped>
 __global__ __launch_bounds__(kKeyRays * kBandLanes) void k_carve_band(InterpScan P)
 {
     __shared__ KeyTable<uint32_t, kKeyRays * kBandLanes, 11> T;
-    __shared__ uint32_t s_row;
-    const bool tries = P.lengths[0].length != 0;
-    if (tries && threadIdx.x < 64u) s_row = find_row(P.xyz, P.n, P.lengths, kKeyPatch.step);
+    __shared__ Row s_row;
+    const bool tries = P.rings != 0;
+    if (tries && threadIdx.x < 64u) s_row = find_row(P.xyz, P.n, P.rings, kKeyPatch);
     T.clear();
-    const Row row = tries ? uniform_row(row_at(P.lengths, s_row)) : P.row;
+    const Row row = tries ? uniform_row(s_row) : P.row;
     if (blockIdx.x == 0 && threadIdx.x == 0) *P.found = row;
     const int64_t i = patch_point<kKeyRays, kKeyPatch.rows>(blockIdx.x, threadIdx.x / kBandLanes, row);
     const int sub = (int)(threadIdx.x % kBandLanes);

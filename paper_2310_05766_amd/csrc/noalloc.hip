@@ -179,8 +179,7 @@ extern "C" tsdf_status tsdf_integrate_scan_noalloc(tsdf_map *m, const float *xyz
     sd.map = 0;
     sd.seq = 0;
     sd.block0 = 0;
-    sd.row = row_lengths(max_tiles_per_ray(m->d.tau_q10, lt) > (int32_t)kPatchTiles ? 0 : n_points, kBinPatch, sd.lengths);
-    sd.pad = 0;
+    sd.row = row_rings(max_tiles_per_ray(m->d.tau_q10, lt) > (int32_t)kPatchTiles ? 0 : n_points, kBinPatch, sd.rings);
     const uint64_t nblocks = (uint64_t)((n_points + shape.bin_block - 1) / shape.bin_block);
     const uint64_t cap = (uint64_t)n_points * (uint64_t)max_tiles_per_ray(m->d.tau_q10, lt) + 1024;
     if (cap >= ((uint64_t)1 << 32)) return TSDF_ERANGE;
@@ -231,7 +230,7 @@ extern "C" tsdf_status tsdf_integrate_scan_noalloc(tsdf_map *m, const float *xyz
         caps.stats = stats ? 1u : 0u;
         caps.key32 = plan.key_shift ? 1u : 0u;
         caps.once = 0;
-        caps.rows = sd.lengths[0].length ? 1u : 0u;
+        caps.rows = sd.rings ? 1u : 0u;
         caps.tile_lds = plan.lds;
         caps.tile_grid = m->tile_grid > 0 ? m->tile_grid : plan.grid;
         if (launch_noalloc_setup(B, hdr, md, sd, m->stream) != hipSuccess ||

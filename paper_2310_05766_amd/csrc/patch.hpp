@@ -9,7 +9,7 @@
 //
 // The calls do not say how long a row is, and patches cut at a wrong length
 // scatter a block's points. So the host lists the row lengths that a scan of n
-// points may have (row_lengths), and the device tries them on a few samples
+// points may have (row_rings), and the device tries them on a few samples
 // (row_vote); where none fits, blocks take runs. Count and fill of 32 street scans
 // of 128 x 900 points: 54 + 61 us in runs, 76 + 78 cut at 1024, 51 + 54 at 900.
 //
@@ -25,7 +25,7 @@
 
 namespace tsdf {
 
-constexpr int kRowLengths = 4, kRowSamples = 16;  // of a scan: a wave tries all at once
+constexpr int kRowLengths = 8, kRowSamples = 8;  // of a scan: a wave tries all at once
 static_assert(kRowLengths * kRowSamples == 64, "a lane per length and sample");
 constexpr uint32_t kRowSpan = 32;  // points of a row that a step from row to row is compared with (row_vote)
 
@@ -41,34 +41,41 @@ struct PatchKind {
 struct Row {
     uint32_t length;  // points, 0: the scan is taken in runs
     uint32_t end;     // columns of all whole bands, one after another
-    uint32_t inverse; // floor(2^32 / length) + 1
+    uint32_t inverse; // 2^32 / length, rounded up
 };
 
-inline Row row_of_length(uint32_t length, uint32_t rings, const PatchKind &kind)
+__host__ __device__ __forceinline__ Row row_of(uint32_t length, uint32_t rings, const PatchKind &kind)
 {
-    return Row{length, rings / kind.rows * length, (uint32_t)(((uint64_t)1 << 32) / length) + 1u};
+    return Row{length, rings / kind.rows * length, 0xffffffffu / length + 1u};
 }
 
 // The row to take the points of a scan of n points by, where there are no lengths
-// to try; else these, the shortest first (0: no more): n / rings for the numbers
-// of rings that sensors have, of at least 256 points.
-inline Row row_lengths(int64_t n, const PatchKind &kind, Row lengths[kRowLengths])
+// to try; else these, as numbers of rings (length n / rings, of at least 256
+// points), a byte each from the low end, the most first (0: no more): the usual
+// numbers, then any from 128 down to 16. (Eight Rows in the kernels' arguments,
+// 96 bytes, cost every call 0.4 us: 17.5 -> 18.0 for a scan of 16 x 1024 points.)
+inline Row row_rings(int64_t n, const PatchKind &kind, uint64_t &rings)
 {
-    static constexpr uint32_t kRings[] = {128, 64, 32, 16, 40, 80, 104, 96, 120, 112, 48, 56, 72, 88, 24, 20};
-    for (int k = 0; k < kRowLengths; ++k) lengths[k] = Row{0, 0, 0};
+    rings = 0;
     if (n < kind.points || n >= (int64_t)1 << 32) return Row{0, 0, 0};
-    if ((n & (n - 1)) == 0) return row_of_length(1024, (uint32_t)(n / 1024), kind);
+    if ((n & (n - 1)) == 0) return row_of(1024, (uint32_t)(n / 1024), kind);
+    const uint32_t points = (uint32_t)n, most = points / 256 < 128 ? points / 256 : 128;
+    uint32_t found[kRowLengths];
     int k = 0;
-    for (uint32_t rings : kRings) {
-        if (k == kRowLengths) break;
-        if (rings < kind.rows || n % rings != 0 || n / rings < 256) continue;
-        const uint32_t length = (uint32_t)(n / rings);
-        int at = k++;
-        for (; at > 0 && length < lengths[at - 1].length; --at) lengths[at] = lengths[at - 1];
-        lengths[at] = row_of_length(length, rings, kind);
-    }
+    const auto add = [&](uint32_t r) {
+        if (k == kRowLengths || r < kind.rows || r > most || points % r != 0) return;
+        int at = 0;
+        while (at < k && found[at] > r) ++at;
+        if (at < k && found[at] == r) return;
+        for (int j = k++; j > at; --j) found[j] = found[j - 1];
+        found[at] = r;
+    };
+    for (uint32_t r : {128u, 64u, 32u, 16u, 40u, 80u}) add(r);
+    for (uint32_t r = most; r >= 16 && k < kRowLengths; --r) add(r);
+    for (int j = 0; j < k; ++j) rings |= (uint64_t)found[j] << 8 * j;
     return Row{0, 0, 0};
 }
+__host__ __device__ __forceinline__ uint32_t ring_at(uint64_t rings, uint32_t k) { return (uint32_t)(rings >> 8 * k) & 255u; }
 
 // Sample j's first point: points at + length and at + kRowSpan exist for every
 // length (at most n / 16).
@@ -107,7 +114,7 @@ __host__ __device__ __forceinline__ void row_vote(const float a[3], const float 
 }
 
 // Whether a length is the scan's, by the samples that count and fit.
-__host__ __device__ __forceinline__ bool row_fits(int counts, int fits) { return counts >= 4 && 4 * fits >= 3 * counts; }
+__host__ __device__ __forceinline__ bool row_fits(int counts, int fits) { return counts >= 3 && 4 * fits >= 3 * counts; }
 
 // The point of thread t of a scan's block b (runs where row.length is 0). Block
 // by block, kRun columns of a band of kRows rows, the bands' columns in one

@@ -659,7 +659,7 @@ static tsdf_status integrate_interp(tsdf_map *m, const float *xyz, int64_t n, bo
     P.touched = m->interp_touched;
     P.counters = m->interp_ctr;
     P.want_stats = stats ? 1 : 0;
-    P.row = row_lengths(n, kKeyPatch, P.lengths);
+    P.row = row_rings(n, kKeyPatch, P.rings);
     P.found = (Row *)(m->interp_ctr + kCtrKinds * kCtrWords);
     P.key_shift = key32_shift(P.rp.tau, n);
     P.keys32 = (uint32_t *)m->interp_keys;

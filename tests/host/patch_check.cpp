@@ -72,24 +72,25 @@ static Scan room(int rings, int cols, double fov, double missing, std::mt19937_6
 // as a wave finds it on the device
 static Row find_row(const Scan &s, const PatchKind &kind)
 {
-    Row len[kRowLengths];
-    const Row row = row_lengths(s.n(), kind, len);
-    if (!len[0].length) return row;
-    for (int k = 0; k < kRowLengths; ++k) {
-        if (!len[k].length) continue;
-        CHECK(k == 0 || len[k].length > len[k - 1].length, "lengths out of order");
+    uint64_t rings;
+    const Row row = row_rings(s.n(), kind, rings);
+    uint32_t last = 0;
+    for (int k = 0; k < kRowLengths && ring_at(rings, k); ++k) {
+        const Row len = row_of((uint32_t)s.n() / ring_at(rings, k), ring_at(rings, k), kind);
+        CHECK(len.length > last, "lengths out of order");
+        last = len.length;
         int nc = 0, nf = 0;
         for (uint32_t j = 0; j < kRowSamples; ++j) {
             const int64_t i = row_sample(s.n(), j);
             bool c, f;
-            CHECK(i >= 0 && i + len[k].length < s.n() && i + kRowSpan < s.n(), "sample past the scan");
-            row_vote(&s.p[3 * i], &s.p[3 * (i + len[k].length)], &s.p[3 * (i + kRowSpan)], kind.step, c, f);
+            CHECK(i >= 0 && i + len.length < s.n() && i + kRowSpan < s.n(), "sample past the scan");
+            row_vote(&s.p[3 * i], &s.p[3 * (i + len.length)], &s.p[3 * (i + kRowSpan)], kind.step, c, f);
             nc += c;
             nf += f;
         }
-        if (row_fits(nc, nf)) return len[k];
+        if (row_fits(nc, nf)) return len;
     }
-    return Row{0, 0, 0};
+    return row;
 }
 static uint32_t find(const Scan &s, const PatchKind &kind) { return find_row(s, kind).length; }
 
@@ -117,9 +118,14 @@ int main()
     for (int64_t n : {(int64_t)1, (int64_t)255, (int64_t)8192, (int64_t)32768, (int64_t)57616, (int64_t)131072, (int64_t)65344,
                       (int64_t)115200, (int64_t)100003, (int64_t)128 * 2083, (int64_t)40 * 1800, (int64_t)1 << 22})
         for (const bool key : {false, true}) {
-            Row len[kRowLengths + 1];
-            len[0] = row_lengths(n, key ? keys : bin, len + 1);
-            for (const Row &row : len) {
+            uint64_t rings;
+            Row row = row_rings(n, key ? keys : bin, rings);
+            for (int k = 0; k <= kRowLengths; ++k) {
+                if (k > 0) {
+                    const uint32_t r = ring_at(rings, k - 1);
+                    if (r == 0) break;
+                    row = row_of((uint32_t)n / r, r, key ? keys : bin);
+                }
                 if (key) {
                     once_each<64, 8>(n, row);
                 } else {
@@ -133,7 +139,7 @@ int main()
     for (int k = 0; k < 2000000; ++k) {
         const uint32_t length = std::uniform_int_distribution<uint32_t>(256, 1u << 28)(rng), kRun = 8;
         const uint32_t end = std::uniform_int_distribution<uint32_t>(1, 0x7ffffffu / (length < 0x7ffffffu ? length : 0x7ffffffu))(rng) * length;
-        const Row row{length, end, (uint32_t)(((uint64_t)1 << 32) / length) + 1u};
+        const Row row{length, end, row_of(length, 32, bin).inverse};
         if (end <= kRun) continue;
         const uint32_t col = std::uniform_int_distribution<uint32_t>(0, end - 1)(rng) / kRun * kRun;
         CHECK((patch_point<256, 32>(col / kRun, 0, row) == (int64_t)(col / length * 32) * length + col % length), "column %u of rows of %u", col,
@@ -144,7 +150,7 @@ int main()
         double fov;
     } scans[] = {{128, 1024, 45}, {128, 512, 45}, {128, 2048, 45}, {64, 1024, 33}, {64, 2048, 33}, {32, 1024, 40}, {32, 2083, 40},
                  {64, 1021, 45},  {104, 554, 45}, {128, 720, 45},  {128, 900, 90}, {64, 1800, 45}, {64, 2083, 45}, {80, 1440, 40},
-                 {40, 1800, 25},  {128, 700, 45}, {128, 870, 45},  {128, 800, 45}, {96, 1000, 45}, {128, 333, 45}, {64, 512, 45}};
+                 {40, 1800, 25},  {57, 743, 45}, {93, 512, 45}, {128, 700, 45}, {128, 870, 45},  {128, 800, 45}, {96, 1000, 45}, {128, 333, 45}, {64, 512, 45}};
     for (auto &c : scans)
         for (double missing : {0.0, 0.3}) {
             const Scan s = room(c.rings, c.cols, c.fov, missing, rng);
@@ -157,7 +163,7 @@ int main()
             CHECK(tried ? row == 0 || row % c.cols == 0 : row == 1024, "%d x %d: row %u", c.rings, c.cols, row);
             CHECK(patch <= (tried ? 1.0 : 1.05) * run, "%d x %d: tiles %.1f -> %.1f", c.rings, c.cols, run, patch);
         }
-    for (auto &c : {scans[0], scans[7], scans[8], scans[10], scans[14]}) CHECK(find(room(c.rings, c.cols, c.fov, 0.1, rng), bin) == (uint32_t)c.cols, "%d x %d", c.rings, c.cols);
+    for (auto &c : {scans[0], scans[7], scans[8], scans[10], scans[16]}) CHECK(find(room(c.rings, c.cols, c.fov, 0.1, rng), bin) == (uint32_t)c.cols, "%d x %d", c.rings, c.cols);
     // no rows: shuffled points, one ring of many points, too few points, no returns
     Scan s = room(128, 1000, 45, 0.0, rng);
     for (int64_t i = s.n() - 1; i > 0; --i) {
@@ -170,6 +176,8 @@ int main()
     CHECK(find(room(16, 1000, 30, 0.0, rng), bin) == 0, "rows of a small scan");
     CHECK(find(room(128, 1000, 45, 1.0, rng), bin) == 0, "rows without returns");
     CHECK(find(room(16, 1000, 30, 0.0, rng), keys) == 1000, "16 rings in patches of 8 rows");
+    CHECK(find(room(17, 584, 30, 0.0, rng), keys) == 584, "17 rings in patches of 8 rows");
+    CHECK(find(room(93, 512, 45, 0.0, rng), bin) == 512, "93 rings");
     CHECK(find(room(64, 1800, 45, 0.0, rng), keys) == 1800, "64 rings in patches of 8 rows");
     printf("mismatches %ld\n", bad);
     return bad != 0;
