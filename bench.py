@@ -671,6 +671,8 @@ def main():
         torch.cuda.synchronize()
     log("batched steps")
     dt = timed(step_batched)
+    # (the result is the window above; four more show what a stall of the host would do to it)
+    dt_again = [timed(step_batched) for _ in range(4)]
     log("plain per-scan steps")
     dt_plain = timed(step_plain)
 
@@ -794,6 +796,7 @@ def main():
         "steps": args.steps,
         "warmup": args.warmup,
         "ms_per_step": dt * 1e3 / args.steps,
+        "ms_per_step_again": [t * 1e3 / args.steps for t in dt_again],
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
